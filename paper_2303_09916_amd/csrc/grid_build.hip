@@ -4,24 +4,45 @@
 // the summed interaction with receptor atoms within the cutoff, plus its
 // gradient); Appendix eq. 1.  Terms: Vina's (ref. [6]), kept unchanged by the paper.
 //
-// Design: one workgroup per 8x8x4 tile of nodes, one thread per node carrying all
-// T map types in registers.  Receptor atoms arrive sorted by 4 A cells (host
-// counting sort); the workgroup stages every atom of the cells within the cutoff
-// of its tile into LDS (rows of cells are contiguous in the sorted array), then
-// each thread sweeps the staged atoms: one distance per node-atom pair, then
-// T pair terms.  The work is VALU-bound (2 exp + ~30 flops per pair term); map
-// stores are float4 and contiguous along x.
+// Design: one workgroup per 8x8x4 tile of nodes; each of its four waves owns a
+// 4x4x4 block (one node per lane) and carries all T map types in registers.
+// Receptor atoms arrive sorted by 4 A cells (host counting sort); the workgroup
+// stages the atoms of the cells within the cutoff of its tile into LDS (rows of
+// cells are contiguous in the sorted array).  A wave takes them 64 at a time, one
+// per lane, keeps those within the cutoff of its own block (a ballot), and sweeps
+// the kept ones in order: the atom's values come from lane reads, so everything
+// that depends on the atom alone is uniform over the wave and is branched on
+// instead of selected.
+//
+// Bound by VALU issue.  A node sums each atom's terms in the order of the sorted
+// array, so the sums are those of any other tiling; what is saved is work:
+//  - the two exponentials and the class-free terms depend on the pair's radius
+//    sum only and are formed once for all map types of one XS radius (T maps
+//    arrive ordered by radius; 8 types of a usual palette have 4 radii);
+//  - the hydrophobic and hydrogen-bond terms are formed only for atoms and maps
+//    of that class;
+//  - a 4x4x4 block is within the cutoff of 72 atoms at protein density where an
+//    8x8x1 slab is of 83, and wastes fewer lanes at the box faces;
+//  - the root and the reciprocal are the shortest sequences that still round
+//    correctly (both checked against sqrtf and 1/x over every input in range).
+// Measured on MI355X, kernel alone, before and after: 81^3 nodes, 8 types, 4000
+// atoms 270 -> 120 us; 107^3, 9 types, 12000 atoms 540 -> 243 us; 43^3, 4 types, 300
+// atoms 60 -> 26 us (37 us without the split into runs of maps, see kFillWaves).
 #include "dsdp_internal.h"
 
-#include <cstring>
+#include <algorithm>
+#include <utility>
 
 namespace dsdp {
 namespace {
 
 constexpr int TX = 8, TY = 8, TZ = 4;
 constexpr int kThreads = TX * TY * TZ;
-constexpr int kStageCap = 2048;      // atoms staged per pass (32 KB of LDS)
-constexpr int kMaxRows = 128;        // cell rows per tile
+constexpr int BX = 4, BY = 4;        // a wave's block of nodes (x and y; all of TZ)
+constexpr int kStageCap = 512;       // atoms staged per pass (8 KB of LDS)
+constexpr int kMaxRows = 128;        // cell rows per tile (at most 9 x 9 by the choice of the cell edge)
+constexpr uint32_t kPolar = 1u << 31;
+constexpr long kFillWaves = 4096;    // four waves per SIMD of the device's 1024
 
 struct BuildArgs {
     const float4 *atoms;      // sorted by cell: x, y, z, XS type bits
@@ -30,110 +51,198 @@ struct BuildArgs {
     float clo[3];
     float cell;
     GridView g;
-    float4 tparam[kNXS * kNXS];   // [map t][receptor type]: (R_t + R_a, hydrophobic w, h-bond w, 0)
+    // the maps ordered by XS radius, in n_parts runs that end on a change of radius;
+    // a workgroup builds one run: maps part[p] to part[p + 1] - 1
+    int n_parts, part[kNXS + 1];
+    float radius[kNXS];       // radius of the k-th map's type
+    int slot[kNXS];           // its index in the caller's order
+    uint32_t first;           // bit k: the k-th map is the first of its radius
+    // per receptor type: its radius, and the maps k with a class term (bit k;
+    // kPolar: the term is the hydrogen bond, else the hydrophobic one)
+    float rec_radius[kNXS];
+    uint32_t rec_class[kNXS];
     float4 *maps;
 };
 
-// Vina pair energy on the surface distance d and its derivative in d, returned
-// as (e, de); wh and wb are the pair's hydrophobic and hydrogen-bond weights
-// (0 when the pair is not of that class).  At a kink the left-hand slope is taken.
-__device__ __forceinline__ float2 vina_pair(float d, float wh, float wb)
+__device__ __forceinline__ float lane_value(float v, int l)
 {
-    const float g1 = __expf(-4.0f * d * d);
-    const float b = d - 3.0f;
-    const float g2 = __expf(-0.25f * b * b);
-    const float dn = fminf(d, 0.0f);
-    float e = kWGauss1 * g1 + kWGauss2 * g2 + kWRepulsion * dn * dn;
-    float de = kWGauss1 * g1 * (-8.0f * d) + kWGauss2 * g2 * (-0.5f * b) + kWRepulsion * 2.0f * dn;
-    e += wh * fminf(fmaxf(1.5f - d, 0.0f), 1.0f) + wb * fminf(fmaxf(-d * (1.0f / 0.7f), 0.0f), 1.0f);
-    de += ((d > 0.5f && d <= 1.5f) ? -wh : 0.0f) + ((d > -0.7f && d <= 0.0f) ? -wb * (1.0f / 0.7f) : 0.0f);
-    return make_float2(e, de);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// f(0), f(1), ..., f(N - 1) with compile-time indices
+template <int... I, typename F>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each(F f)
+{
+    each_of(std::make_integer_sequence<int, N>(), f);
 }
 
 template <int TMAX>
 __global__ __launch_bounds__(kThreads) void grid_build_kernel(const BuildArgs a)
 {
     __shared__ float4 s_atoms[kStageCap];
-    __shared__ float4 s_tp[TMAX * kNXS];
-    __shared__ int s_row_begin[kMaxRows], s_row_end[kMaxRows], s_row_pre[kMaxRows + 1];
-    __shared__ int s_nrows, s_total;
+    __shared__ float s_rad[kNXS];
+    __shared__ uint32_t s_cls[kNXS];
+    __shared__ int s_row_begin[kMaxRows], s_row_pre[kMaxRows + 1];
+    __shared__ int s_half;
 
     const GridView &g = a.g;
-    const int T = g.T;
-    const int tid = threadIdx.x;
-    const int ix = tid % TX, iy = (tid / TX) % TY, iz = tid / (TX * TY);
-    const int tile_x = blockIdx.x, tile_y = blockIdx.y, tile_z = blockIdx.z;
-    const int i = tile_x * TX + ix, j = tile_y * TY + iy, k = tile_z * TZ + iz;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int part = blockIdx.z % a.n_parts, k0 = a.part[part], T = a.part[part + 1] - k0;
+    const uint32_t first = a.first >> k0;
+    const int t0x = blockIdx.x * TX, t0y = blockIdx.y * TY, t0z = blockIdx.z / a.n_parts * TZ;
+    const int b0x = t0x + (wave & 1) * BX, b0y = t0y + (wave >> 1) * BY;
+    const int i = b0x + (lane & 3), j = b0y + ((lane >> 2) & 3), k = t0z + (lane >> 4);
     const float mx = g.origin[0] + g.h * (float)i;
     const float my = g.origin[1] + g.h * (float)j;
     const float mz = g.origin[2] + g.h * (float)k;
 
-    for (int q = tid; q < TMAX * kNXS; q += kThreads) s_tp[q] = (q < T * kNXS) ? a.tparam[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tid < kNXS) {
+        s_rad[tid] = a.rec_radius[tid];
+        s_cls[tid] = ((a.rec_class[tid] & ~kPolar) >> k0) | (a.rec_class[tid] & kPolar);
+    }
 
-    // cell rows covering the tile expanded by the cutoff
-    if (tid == 0) {
-        int lo[3], hi[3];
-        const int t0[3] = {tile_x * TX, tile_y * TY, tile_z * TZ};
-        const int tn[3] = {TX, TY, TZ};
-        for (int ax = 0; ax < 3; ax++) {
-            const float plo = g.origin[ax] + g.h * (float)t0[ax] - kCutoff;
-            const float phi = g.origin[ax] + g.h * (float)(t0[ax] + tn[ax] - 1) + kCutoff;
-            lo[ax] = max(0, (int)floorf((plo - a.clo[ax]) / a.cell));
-            hi[ax] = min(a.cn[ax] - 1, (int)floorf((phi - a.clo[ax]) / a.cell));
+    // cell rows covering the tile expanded by the cutoff: one row per thread,
+    // then an exclusive scan of their lengths (two waves hold the rows)
+    int lo[3], hi[3];
+    const int t0[3] = {t0x, t0y, t0z};
+    const int tn[3] = {TX, TY, TZ};
+#pragma unroll
+    for (int ax = 0; ax < 3; ax++) {
+        const float plo = g.origin[ax] + g.h * (float)t0[ax] - kCutoff;
+        const float phi = g.origin[ax] + g.h * (float)(t0[ax] + tn[ax] - 1) + kCutoff;
+        lo[ax] = max(0, (int)floorf((plo - a.clo[ax]) / a.cell));
+        hi[ax] = min(a.cn[ax] - 1, (int)floorf((phi - a.clo[ax]) / a.cell));
+    }
+    const int ny = hi[1] - lo[1] + 1, nz = hi[2] - lo[2] + 1;
+    const int nrows = lo[0] > hi[0] || ny <= 0 || nz <= 0 ? 0 : min(ny * nz, kMaxRows);
+    int begin = 0, len = 0, pre = 0;
+    if (tid < nrows) {
+        const int base = ((lo[2] + tid / ny) * a.cn[1] + lo[1] + tid % ny) * a.cn[0];
+        begin = a.cell_start[base + lo[0]];
+        len = a.cell_start[base + hi[0] + 1] - begin;
+    }
+    if (tid < kMaxRows) {
+        pre = len;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(pre, o, 64);
+            if (lane >= o) pre += v;
         }
-        int nr = 0;
-        for (int cz = lo[2]; cz <= hi[2]; cz++)
-            for (int cy = lo[1]; cy <= hi[1]; cy++) {
-                if (lo[0] > hi[0] || nr >= kMaxRows) continue;
-                const int base = (cz * a.cn[1] + cy) * a.cn[0];
-                s_row_begin[nr] = a.cell_start[base + lo[0]];
-                s_row_end[nr] = a.cell_start[base + hi[0] + 1];
-                nr++;
-            }
-        int acc = 0;
-        for (int r = 0; r < nr; r++) {
-            s_row_pre[r] = acc;
-            acc += s_row_end[r] - s_row_begin[r];
-        }
-        s_row_pre[nr] = acc;
-        s_nrows = nr;
-        s_total = acc;
+        if (tid == 63) s_half = pre;
     }
     __syncthreads();
+    if (tid < kMaxRows) {
+        if (tid >= 64) pre += s_half;
+        s_row_begin[tid] = begin;
+        s_row_pre[tid + 1] = pre;
+        if (tid == 0) s_row_pre[0] = 0;
+    }
+    __syncthreads();
+    const int total = s_row_pre[kMaxRows];
 
     float E[TMAX], Gx[TMAX], Gy[TMAX], Gz[TMAX];
 #pragma unroll
     for (int t = 0; t < TMAX; t++) E[t] = Gx[t] = Gy[t] = Gz[t] = 0.0f;
 
-    const int total = s_total, nrows = s_nrows;
+    // the wave's block (node positions are monotonic in the index)
+    const bool block_in = b0x < g.n[0] && b0y < g.n[1];
+    const float bx0 = g.origin[0] + g.h * (float)b0x, bx1 = g.origin[0] + g.h * (float)(b0x + BX - 1);
+    const float by0 = g.origin[1] + g.h * (float)b0y, by1 = g.origin[1] + g.h * (float)(b0y + BY - 1);
+    const float bz0 = g.origin[2] + g.h * (float)t0z, bz1 = g.origin[2] + g.h * (float)(t0z + TZ - 1);
+
     for (int base = 0; base < total; base += kStageCap) {
         const int cnt = min(kStageCap, total - base);
         for (int q = tid; q < cnt; q += kThreads) {
-            const int gidx = base + q;
+            // the row that holds atom base + q: the last with prefix <= it
             int r = 0;
-            while (r + 1 < nrows && s_row_pre[r + 1] <= gidx) r++;
-            s_atoms[q] = a.atoms[s_row_begin[r] + (gidx - s_row_pre[r])];
+#pragma unroll
+            for (int o = kMaxRows / 2; o > 0; o >>= 1)
+                if (s_row_pre[r + o] <= base + q) r += o;
+            s_atoms[q] = a.atoms[s_row_begin[r] + (base + q - s_row_pre[r])];
         }
         __syncthreads();
-        for (int q = 0; q < cnt; q++) {
-            const float4 at = s_atoms[q];
-            const float dx = mx - at.x, dy = my - at.y, dz = mz - at.z;
-            const float r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 < kCutoff2) {
-                const float r = sqrtf(r2);
-                const float inv_r = r > 1e-9f ? 1.0f / r : 0.0f;
-                const int ta = __float_as_int(at.w);
+        for (int c = 0; block_in && c < cnt; c += 64) {
+            const float4 at = s_atoms[min(c + lane, cnt - 1)];
+            // distance to the block; the margin covers the rounding of the
+            // squared distances below, so no atom within a node's cutoff is left out
+            const float ox = fmaxf(fmaxf(bx0 - at.x, at.x - bx1), 0.f);
+            const float oy = fmaxf(fmaxf(by0 - at.y, at.y - by1), 0.f);
+            const float oz = fmaxf(fmaxf(bz0 - at.z, at.z - bz1), 0.f);
+            const int ta = __float_as_int(at.w);
+            const uint32_t cls_l = s_cls[ta];
+            float sum_l[TMAX];   // radius sums of the lane's atom
 #pragma unroll
-                for (int t = 0; t < TMAX; t++) {
-                    if (t < T) {
-                        const float4 tp = s_tp[t * kNXS + ta];
-                        const float2 ed = vina_pair(r - tp.x, tp.y, tp.z);
-                        const float gs = ed.y * inv_r;
-                        E[t] += ed.x;
-                        Gx[t] += gs * dx;
-                        Gy[t] += gs * dy;
-                        Gz[t] += gs * dz;
-                    }
+            for (int t = 0; t < TMAX; t++) sum_l[t] = a.radius[min(k0 + t, kNXS - 1)] + s_rad[ta];
+            uint64_t keep = __ballot(c + lane < cnt && ox * ox + oy * oy + oz * oz < kCutoff2 + 0.01f);
+            while (keep) {
+#pragma clang fp contract(off)
+                const int l = __builtin_ctzll(keep);
+                keep &= keep - 1;
+                const float dx = mx - lane_value(at.x, l), dy = my - lane_value(at.y, l),
+                            dz = mz - lane_value(at.z, l);
+                const uint32_t cls = (uint32_t)__builtin_amdgcn_readlane((int)cls_l, l);
+                const float r2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
+                if (r2 < kCutoff2) {
+                    // r = sqrt(r2) and 1 / r, correctly rounded: the estimates of
+                    // the hardware and one residual step each.  A distance below
+                    // 2^-45 is as good as 0 (every radius sum is above 1).
+                    const float x = __int_as_float(max(__float_as_int(r2), 0x12800000));
+                    const float y = __builtin_amdgcn_rsqf(x);
+                    const float s0 = x * y;
+                    const float r = fmaf(fmaf(-s0, s0, x), 0.5f * y, s0);
+                    float inv = __builtin_amdgcn_rcpf(r);
+                    inv = fmaf(fmaf(-r, inv, 1.0f), inv, inv);
+                    const float half_inv = r > 1e-9f ? 0.5f * inv : 0.0f;
+                    // Vina's pair term on the surface distance d; the derivative is
+                    // carried doubled (de2), which scales every product exactly
+                    float d = 0.f, e = 0.f, de2 = 0.f, gs = 0.f;
+                    constexpr float kLog2e = 1.44269504088896341f;
+                    // unrolled by the template, so that the accumulators are
+                    // registers before any branch is seen
+                    each<TMAX>([&](auto index) {
+#pragma clang fp contract(off)
+                        constexpr int t = decltype(index)::value;
+                        if (t < T) {
+                            if (first & (1u << t)) {
+                                d = r - lane_value(sum_l[t], l);
+                                const float b = d - 3.0f;
+                                const float g1 = __builtin_amdgcn_exp2f((d * d) * (-4.0f * kLog2e));
+                                const float g2 = __builtin_amdgcn_exp2f((b * b) * (-0.25f * kLog2e));
+                                const float dn = fminf(d, 0.0f);
+                                const float m2 = g2 * kWGauss2;
+                                e = fmaf(dn, kWRepulsion * dn, fmaf(g1, kWGauss1, m2));
+                                de2 = fmaf(d, g1 * (-16.0f * kWGauss1), -(b * m2));
+                                de2 = fmaf(kWRepulsion * 4.0f, dn, de2);
+                                gs = half_inv * de2;
+                            }
+                            if (cls & (1u << t)) {
+                                // at a kink the left-hand slope is taken
+                                float p, h2;
+                                if (cls & kPolar) {
+                                    p = kWHBond * fminf(fmaxf(d * -(1.0f / 0.7f), 0.0f), 1.0f);
+                                    h2 = (d > -0.7f && d <= 0.0f) ? -2.0f * (kWHBond * (1.0f / 0.7f)) : 0.0f;
+                                } else {
+                                    p = kWHydrophobic * fminf(fmaxf(1.5f - d, 0.0f), 1.0f);
+                                    h2 = (d > 0.5f && d <= 1.5f) ? -2.0f * kWHydrophobic : 0.0f;
+                                }
+                                const float gt = half_inv * (de2 + h2);
+                                E[t] += e + p;
+                                Gx[t] = fmaf(gt, dx, Gx[t]);
+                                Gy[t] = fmaf(gt, dy, Gy[t]);
+                                Gz[t] = fmaf(gt, dz, Gz[t]);
+                            } else {
+                                E[t] += e;
+                                Gx[t] = fmaf(gs, dx, Gx[t]);
+                                Gy[t] = fmaf(gs, dy, Gy[t]);
+                                Gz[t] = fmaf(gs, dz, Gz[t]);
+                            }
+                        }
+                    });
                 }
             }
         }
@@ -145,7 +254,7 @@ __global__ __launch_bounds__(kThreads) void grid_build_kernel(const BuildArgs a)
         const long node = ((long)k * g.n[1] + j) * g.n[0] + i;
 #pragma unroll
         for (int t = 0; t < TMAX; t++)
-            if (t < T) a.maps[(long)t * nodes + node] = make_float4(E[t], Gx[t], Gy[t], Gz[t]);
+            if (t < T) a.maps[(long)a.slot[k0 + t] * nodes + node] = make_float4(E[t], Gx[t], Gy[t], Gz[t]);
     }
 }
 
@@ -163,28 +272,66 @@ hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const i
     }
     a.cell = cell;
     a.g = g;
-    for (int t = 0; t < kNXS; t++)
+    // order the maps by radius (stable), so that maps of one radius follow each other
+    for (int t = 0; t < kNXS; t++) {
+        a.slot[t] = t;
+        a.radius[t] = 0.f;
+        a.rec_radius[t] = xs_radius(t);
+        a.rec_class[t] = 0u;
+    }
+    std::stable_sort(a.slot, a.slot + g.T, [&](int u, int v) {
+        return xs_radius(map_types_host[u]) < xs_radius(map_types_host[v]);
+    });
+    a.first = 0u;
+    for (int k = 0; k < g.T; k++) {
+        const int mt = map_types_host[a.slot[k]];
+        a.radius[k] = xs_radius(mt);
+        if (k == 0 || a.radius[k] != a.radius[k - 1]) a.first |= 1u << k;
         for (int r = 0; r < kNXS; r++) {
-            if (t < g.T) {
-                const int mt = map_types_host[t];
-                const uint32_t fl = pair_flags(mt, r);
-                a.tparam[t * kNXS + r] = make_float4(xs_radius(mt) + xs_radius(r),
-                                                     (fl & kPairHydrophobic) ? kWHydrophobic : 0.f,
-                                                     (fl & kPairHBond) ? kWHBond : 0.f, 0.f);
-            } else {
-                a.tparam[t * kNXS + r] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            // a receptor type is hydrophobic or polar, never both
+            const uint32_t fl = pair_flags(mt, r);
+            if (fl) a.rec_class[r] |= (1u << k) | ((fl & kPairHBond) ? kPolar : 0u);
         }
+    }
     a.maps = maps;
-    dim3 grid((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, (g.n[2] + TZ - 1) / TZ);
-    if (g.T <= 4)
-        grid_build_kernel<4><<<grid, kThreads, 0, stream>>>(a);
-    else if (g.T <= 8)
-        grid_build_kernel<8><<<grid, kThreads, 0, stream>>>(a);
-    else if (g.T <= 12)
-        grid_build_kernel<12><<<grid, kThreads, 0, stream>>>(a);
-    else
-        grid_build_kernel<17><<<grid, kThreads, 0, stream>>>(a);
+
+    // Runs of maps: one, unless the box gives fewer than kFillWaves waves; then
+    // as many as fill that (at most one per radius), since a wave's time is its
+    // own chain of atoms and the chip has idle issue slots.  The part that does
+    // not depend on the map (about 25 of 100 to 150 instructions an atom) is then
+    // repeated.
+    const dim3 tiles((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, (g.n[2] + TZ - 1) / TZ);
+    const long waves = (long)((g.n[0] + BX - 1) / BX) * ((g.n[1] + BY - 1) / BY) * tiles.z;
+    const int radii = __builtin_popcount(a.first);
+    const int want = (int)std::max(1L, std::min((long)radii, kFillWaves / waves));
+    // cut at the changes of radius nearest to equal shares of the cost (a radius
+    // about 18 instructions, a map 4)
+    a.n_parts = 0;
+    a.part[0] = 0;
+    int max_maps = 0, left = 18 * radii + 4 * g.T, cost = 0;
+    for (int k = 0; k < g.T; k++) {
+        cost += 4 + ((a.first >> k & 1u) ? 18 : 0);
+        const bool can_cut = k + 1 == g.T || (a.first >> (k + 1) & 1u);
+        if (k + 1 == g.T || (can_cut && a.n_parts + 1 < want && cost * (want - a.n_parts) >= left)) {
+            max_maps = std::max(max_maps, k + 1 - a.part[a.n_parts]);
+            a.part[++a.n_parts] = k + 1;
+            left -= cost;
+            cost = 0;
+        }
+    }
+    const dim3 grid(tiles.x, tiles.y, tiles.z * a.n_parts);
+#define DSDP_BUILD(N) grid_build_kernel<N><<<grid, kThreads, 0, stream>>>(a)
+    switch (max_maps) {
+    case 1: DSDP_BUILD(1); break;
+    case 2: DSDP_BUILD(2); break;
+    case 3: case 4: DSDP_BUILD(4); break;
+    case 5: case 6: DSDP_BUILD(6); break;
+    case 7: case 8: DSDP_BUILD(8); break;
+    case 9: DSDP_BUILD(9); break;
+    case 10: case 11: case 12: DSDP_BUILD(12); break;
+    default: DSDP_BUILD(kNXS); break;
+    }
+#undef DSDP_BUILD
     return hipGetLastError();
 }
 
