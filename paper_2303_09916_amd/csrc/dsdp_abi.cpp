@@ -139,31 +139,91 @@ dsdp_status validate_ligand(const dsdp_ligand *lig)
     return DSDP_OK;
 }
 
-// Layout of the intra-ligand term for a launch context (both give the same
-// bits, so this only moves speed).  Measured on MI355X: pair lists are faster
-// for one ligand's chains unless the ligand has many pairs and the chains fill
-// the device; launches that mix ligands (batches, the scheduler) run faster
-// with atom lists, whose smaller register and LDS footprint lets more
-// workgroups share a compute unit.
-int choose_intra_form(int n_pairs, long chains, bool mixed)
+// Layout of the intra-ligand term for a launch context (all give the same bits, so
+// this only moves speed).  A chain of one wave (the launch fills the device, or the
+// caller asks for one) takes the pair stream, which evaluates each pair once from
+// 2 KB of scratch: a 128-ligand batch of 128 chains each ran in STREAM_A ms with it and in
+// ATOMS_A ms with atom lists.  Chains of several waves take pair lists; launches that mix
+// ligands and do not fill the device take atom lists, whose smaller LDS footprint
+// lets more workgroups share a compute unit.
+int choose_intra_form(const IntraCtx &ctx)
 {
-    if (mixed) return kFormAtoms;
-    return (n_pairs > 600 && chains >= 2048) ? kFormAtoms : kFormPairs;
+    const bool one_wave = ctx.waves == 1 || (ctx.waves == 0 && ctx.chains > 4L * device_cus());
+    if (ctx.form == DSDP_INTRA_ATOMS) return kFormAtoms;
+    if (one_wave) return kFormStream;
+    return ctx.form == DSDP_INTRA_AUTO && ctx.mixed ? kFormAtoms : kFormPairs;
 }
 
 IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed)
 {
     IntraCtx c;
     c.form = prm ? prm->intra_form : DSDP_INTRA_AUTO;
+    c.waves = prm ? prm->waves_per_chain : 0;
     c.chains = chains;
     c.mixed = mixed;
     return c;
 }
 
+// One chunk of the pair stream, in the order its pairs are stored: those without a
+// class first (each part in list order).  Pair p of the list is entry `at[p]` of
+// chunk p / kStreamPairs.
+struct StreamChunks {
+    std::vector<int> at;
+    std::vector<uint32_t> words;              // stored pair words, whole slots
+    std::vector<std::vector<uint8_t>> list;   // per chunk: [entry][lane]
+    uint32_t chunk_words[2] = {0, 0}, plain = 0;
+    int n_chunks = 0, list_words = 0;
+};
+StreamChunks stream_chunks(const std::vector<uint32_t> &pairs, const std::vector<std::vector<uint16_t>> &lane_list)
+{
+    StreamChunks sc;
+    const int np = (int)pairs.size();
+    sc.n_chunks = (np + kStreamPairs - 1) / kStreamPairs;
+    sc.at.assign((size_t)np, 0);
+    for (int c = 0; c < sc.n_chunks; c++) {
+        const int p0 = c * kStreamPairs, p1 = std::min(np, p0 + kStreamPairs), n = p1 - p0;
+        const int slots = n > 63 ? 2 : 1, zero = 64 * slots - 1;
+        int k = 0;
+        std::vector<uint32_t> w((size_t)64 * slots, 0x80000000u);   // no pair
+        for (int pass = 0; pass < 2; pass++) {
+            for (int p = p0; p < p1; p++)
+                if (((pairs[(size_t)p] >> 16) != 0) == (pass == 1)) {
+                    sc.at[(size_t)p] = k;
+                    w[(size_t)k++] = pairs[(size_t)p];
+                }
+            // slots of class-free pairs only (a short last slot without a class pair counts)
+            if (pass == 0) sc.plain |= (uint32_t)(k == n ? slots : k / 64) << (2 * c);
+        }
+        sc.words.insert(sc.words.end(), w.begin(), w.end());
+        size_t longest = 0;
+        std::vector<std::vector<uint8_t>> lanes(64);
+        for (int l = 0; l < 64; l++) {
+            for (uint16_t e : lane_list[(size_t)l]) {
+                const int p = e & 0x7fff;
+                if (p >= p0 && p < p1) lanes[(size_t)l].push_back((uint8_t)(sc.at[(size_t)p] | ((e & 0x8000) ? 128 : 0)));
+            }
+            longest = std::max(longest, lanes[(size_t)l].size());
+        }
+        const int words = (int)((longest + 3) / 4);
+        for (auto &v : lanes) v.resize((size_t)4 * words, (uint8_t)zero);
+        std::vector<uint8_t> flat;
+        for (int m = 0; m < words; m++)
+            for (int l = 0; l < 64; l++)
+                for (int b = 0; b < 4; b++) flat.push_back(lanes[(size_t)l][(size_t)4 * m + b]);
+        sc.list.push_back(std::move(flat));
+        if (words > 15) {
+            sc.n_chunks = -1;   // does not fit the format: the caller takes another layout
+            return sc;
+        }
+        sc.chunk_words[c / 8] |= (uint32_t)words << (4 * (c % 8));
+        sc.list_words += words;
+    }
+    return sc;
+}
+
 // map_of_type == nullptr: map indices are left 0 (used only for sizing).
 dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepared &out, const IntraCtx &ctx)
 {
-    const int form = ctx.form;
     dsdp_status st = validate_ligand(lig);
     if (st) return st;
     const int na = lig->n_atoms, nf = lig->n_frags;
@@ -288,16 +348,15 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
     h.off_frag_anc = take(nf, 1);
     const int lpa = na <= 32 ? 2 : 1;
     h.lanes_per_atom = lpa;
-    h.intra_form = form == DSDP_INTRA_PAIRS ? kFormPairs
-                   : form == DSDP_INTRA_ATOMS ? kFormAtoms
-                                              : choose_intra_form(np, ctx.chains, ctx.mixed);
+    h.intra_form = choose_intra_form(ctx);
 
     // per-lane lists of the chosen form.  Lane l serves atom l % 32 (every other
     // entry of the atom's list, from l / 32) when there are at most 32 atoms,
     // else atom l.
     //   pair lists: pair indices with a sign bit (set when the atom is the pair's
     //   second atom), padded with the zero slot n_pairs, 8 per 16-byte chunk;
-    //   atom lists: partner bytes j | flags << 6, padded with kNbrNone, 4 per word
+    //   atom lists: partner bytes j | flags << 6, padded with kNbrNone, 4 per word;
+    //   pair stream: the pair lists cut at the chunks, 4 bytes per word
     std::vector<std::vector<uint16_t>> lane_list(64);
     std::vector<std::vector<uint8_t>> lane_nbr(64);
     size_t maxlen = 0;
@@ -323,7 +382,22 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
         }
     }
     h.off_atom_rad = take(na, 1);
-    if (h.intra_form == kFormPairs) {
+    StreamChunks sc;
+    if (h.intra_form == kFormStream) {
+        // a workspace or pool is sized for the other layouts: a (small) ligand whose
+        // stream would be larger than its pair lists takes those
+        sc = stream_chunks(pairs, lane_list);
+        if (sc.n_chunks < 0 || (int)sc.words.size() + 64 * sc.list_words > np + (int)((maxlen + 7) / 8) * 256)
+            h.intra_form = kFormPairs;
+    }
+    if (h.intra_form == kFormStream) {
+        h.n_chunks = sc.n_chunks;
+        h.chunk_words[0] = sc.chunk_words[0];
+        h.chunk_words[1] = sc.chunk_words[1];
+        h.chunk_plain = sc.plain;
+        h.off_pair = take((int)sc.words.size(), 1);
+        h.off_slist = take(64 * sc.list_words, 1);
+    } else if (h.intra_form == kFormPairs) {
         h.off_pair = take(np, 1);
         h.n_chunks = (int)((maxlen + 7) / 8);
         h.off_plist = take(h.n_chunks * 64 * 4, 4);
@@ -379,7 +453,14 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
             anc |= (uint32_t)m << (8 * b);
         blob[(size_t)h.off_frag_anc + k] = anc;
     }
-    if (h.intra_form == kFormPairs) {
+    if (h.intra_form == kFormStream) {
+        std::copy(sc.words.begin(), sc.words.end(), blob.begin() + h.off_pair);
+        size_t o = (size_t)h.off_slist;
+        for (const std::vector<uint8_t> &v : sc.list) {
+            if (!v.empty()) std::memcpy(&blob[o], v.data(), v.size());
+            o += v.size() / 4;
+        }
+    } else if (h.intra_form == kFormPairs) {
         for (int p = 0; p < np; p++) blob[(size_t)h.off_pair + p] = pairs[p];
         for (int c = 0; c < h.n_chunks; c++)
             for (int l = 0; l < 64; l++)
@@ -410,7 +491,12 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
 size_t max_blob_words(const dsdp_ligand *lig)
 {
     Prepared a, b;
-    if (prepare_ligand(lig, nullptr, a, IntraCtx{DSDP_INTRA_PAIRS}) || prepare_ligand(lig, nullptr, b, IntraCtx{DSDP_INTRA_ATOMS})) return 0;
+    // (a pair stream is never larger than the pair lists)
+    IntraCtx pairs, atoms;
+    pairs.form = DSDP_INTRA_PAIRS;
+    pairs.waves = 2;
+    atoms.form = DSDP_INTRA_ATOMS;
+    if (prepare_ligand(lig, nullptr, a, pairs) || prepare_ligand(lig, nullptr, b, atoms)) return 0;
     return (size_t)std::max(a.h.total_words, b.h.total_words);
 }
 
@@ -567,6 +653,10 @@ size_t device_max_lds()
 // until the workgroup's LDS fits the device's limit.
 dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains, int &waves)
 {
+    if (h.intra_form == kFormStream) {
+        waves = 1;
+        return DSDP_OK;
+    }
     int w = (prm && prm->waves_per_chain > 0) ? prm->waves_per_chain : 0;
     // Barzilai-Borwein evaluates one point per iteration: with atom lists one
     // wave does all of it (more would idle); pair lists spread its pairs over
@@ -582,6 +672,31 @@ dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains,
         return fail(DSDP_ERR_UNSUPPORTED, "ligand needs %zu bytes of LDS per chain", search_lds_bytes(h, 1));
     waves = w;
     return DSDP_OK;
+}
+
+// Waves per workgroup and its LDS for a launch of `chains` chains whose largest
+// member is h: the waves of a chain, or for the pair stream the chains that share
+// it: as many as leave four workgroups per compute unit and fit.
+dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds)
+{
+    if (h.intra_form == kFormStream)
+        waves = (int)std::max(1L, std::min((long)kStreamChains, chains / (4L * device_cus())));
+    const size_t cap = device_max_lds();
+    while (waves > 1 && search_lds_bytes(h, waves) > cap) waves--;
+    lds = search_lds_bytes(h, waves);
+    if (lds > cap) return fail(DSDP_ERR_UNSUPPORTED, "ligand needs %zu bytes of LDS per chain", lds);
+    return DSDP_OK;
+}
+
+// The workgroups of n tasks of one ligand (task `first` of the launch onwards) in a
+// pair-stream launch of `waves` chains per workgroup, written to the launch's task
+// table from entry `blocks` on.
+void fill_stream_groups(ChainTask *launch_tasks, long &blocks, long first, long n, int waves)
+{
+    for (long k = 0; k < n; k += waves, blocks++) {
+        launch_tasks[blocks].wg_first = (int32_t)(first + k);
+        launch_tasks[blocks].wg_count = (int32_t)std::min<long>(waves, n - k);
+    }
 }
 
 // HIP events released on every return path
@@ -630,13 +745,8 @@ dsdp_status plan_groups(const dsdp_params *prm, const std::vector<const LigHeade
         // waves per chain from the group's chain count (groups are launched one
         // after another), then lowered until the largest member fits
         dsdp_status st = pick_waves(prm, *hdr[worst], (int)std::min<long>(g.chains, 1L << 30), g.waves);
+        if (!st) st = launch_shape(*hdr[worst], g.chains, g.waves, g.lds);
         if (st) return st;
-        for (;;) {
-            g.lds = search_lds_bytes(*hdr[worst], g.waves);
-            if (g.lds <= device_max_lds() || g.waves == 1) break;
-            g.waves--;
-        }
-        if (g.lds > device_max_lds()) return fail(DSDP_ERR_UNSUPPORTED, "a ligand needs %zu bytes of LDS", g.lds);
         out.push_back(std::move(g));
     }
     return DSDP_OK;
@@ -1016,7 +1126,9 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
     st = upload_blob(pl, ws + w.arena, s);
     if (st) return st;
     int waves = 1;
+    size_t lds = 0;
     st = pick_waves(prm, pl.h, n_poses, waves);
+    if (!st) st = launch_shape(pl.h, n_poses, waves, lds);
     if (st) return st;
     GridView view;
     st = device_view(g, ws, w, nullptr, s, view);
@@ -1041,8 +1153,8 @@ constexpr int kTrialSteps = 4;   // timed MC steps of a tuner trial (every chain
 
 // The workspace's host-written part for one dock (blob, chain tasks from fresh
 // starts, grid view, ranking segment), uploaded on s.
-dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchWs &w, int n_chains, int n_steps,
-                        uint64_t seed, int top_k, char *ws, hipStream_t s)
+dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchWs &w, int waves, int n_chains,
+                        int n_steps, uint64_t seed, int top_k, char *ws, hipStream_t s, long &blocks)
 {
     HostImage img(w.host_end);
     std::memcpy(img.at<uint32_t>(w.arena), pl.blob.data(), pl.blob.size() * 4);
@@ -1058,6 +1170,11 @@ dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchW
         t.grid = 0;
         t.slot = c;
         t.fresh = 1;
+    }
+    blocks = n_chains;
+    if (pl.h.intra_form == kFormStream) {
+        blocks = 0;
+        fill_stream_groups(tasks, blocks, 0, n_chains, waves);
     }
     GridView view;
     dsdp_status st = device_view(g, ws, w, img.bytes.data(), s, view);
@@ -1088,14 +1205,16 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
     HIP_TRY(hipGetDevice(&dev), "device");
     const int kind = prm->optimizer == DSDP_OPT_BB ? kTuneDockBb : kTuneDockBfgs;
     const TuneKey key = tune_key(dev, n_chains, {shape_bucket(pl.h.n_atoms, pl.h.n_pairs, 6 + pl.h.n_tors)}, kind);
-    const int pl_form = pl.h.intra_form == kFormPairs ? DSDP_INTRA_PAIRS : DSDP_INTRA_ATOMS;
-    bool have_alt = false;
     dsdp_status mst = DSDP_OK;
-    auto layout = [&](int form) -> const Prepared * {
-        if (form == pl_form) return &pl;
-        if (!have_alt) {
-            if ((mst = prepare_ligand(lig, g->map_of_type, alt, IntraCtx{form}))) return nullptr;
-            have_alt = true;
+    // the layout of a candidate (pair lists with one wave per chain: the pair stream)
+    auto layout = [&](const DockCandidate &dc) -> const Prepared * {
+        const int want = dc.form == DSDP_INTRA_ATOMS ? kFormAtoms : dc.waves == 1 ? kFormStream : kFormPairs;
+        if (pl.h.intra_form == want) return &pl;
+        if (alt.blob.empty() || alt.h.intra_form != want) {
+            IntraCtx ctx;
+            ctx.form = dc.form;
+            ctx.waves = dc.waves;
+            if ((mst = prepare_ligand(lig, g->map_of_type, alt, ctx))) return nullptr;
         }
         return &alt;
     };
@@ -1105,19 +1224,22 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
     } else {
         auto measure = [&](int c) -> float {
             const DockCandidate dc = dock_candidate(c);
-            const Prepared *P = mst ? nullptr : layout(dc.form);
+            const Prepared *P = mst ? nullptr : layout(dc);
             if (!P) return -1.f;
-            const size_t lds = search_lds_bytes(P->h, dc.waves);
+            int waves_wg = dc.waves;
+            size_t lds = search_lds_bytes(P->h, dc.waves);
+            if (P->h.intra_form == kFormStream && launch_shape(P->h, n_chains, waves_wg, lds)) return -1.f;
             const SearchWs w = search_ws(P->h, n_chains);
             if (lds > device_max_lds() || w.total > ws_bytes) return -1.f;
+            long blocks = 0;
             // trial chains run 1 + kTrialSteps steps whatever the request's length,
             // so that requests of any length share the cached pick
-            if ((mst = upload_dock(g, *P, w, n_chains, 1 + kTrialSteps, seed, 0, ws, s))) return -1.f;
+            if ((mst = upload_dock(g, *P, w, waves_wg, n_chains, 1 + kTrialSteps, seed, 0, ws, s, blocks))) return -1.f;
             Events ev;
             float ms = -1.f;
             auto tick = [&](int steps, int init) {
-                return launch_tick(search_class(P->h), dc.waves, lds, (const uint32_t *)(ws + w.arena),
-                                   (const ChainTask *)(ws + w.tasks), n_chains, (const GridView *)(ws + w.grids), sp,
+                return launch_tick(search_class(P->h), waves_wg, lds, (const uint32_t *)(ws + w.arena),
+                                   (const ChainTask *)(ws + w.tasks), (int)blocks, (const GridView *)(ws + w.grids), sp,
                                    steps, init, (float *)(ws + w.state), (float *)(ws + w.records),
                                    (float4 *)(ws + w.xyz), s);
             };
@@ -1133,7 +1255,7 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
         if (!found) return DSDP_OK;   // no candidate fits: the fixed rule decides
     }
     const DockCandidate dc = dock_candidate(pick);
-    use = layout(dc.form);
+    use = layout(dc);
     if (mst) return mst;
     waves = dc.waves;
     return DSDP_OK;
@@ -1182,6 +1304,10 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
         st = pick_waves(prm, pl.h, n_chains, waves);
         if (st) return st;
     }
+    size_t lds = 0;
+    st = launch_shape(pl.h, n_chains, waves, lds);
+    if (st) return st;
+    long blocks = 0;
     const SearchWs w = search_ws(pl.h, n_chains);
     if (static_ws) {
         if (w.total > kStaticScratchBytes)
@@ -1192,7 +1318,7 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
     if (!d_ws || ws_bytes < w.total) return fail(DSDP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", w.total);
     if (!aligned256(d_ws)) return fail(DSDP_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
     char *ws = (char *)d_ws;
-    st = upload_dock(g, pl, w, n_chains, n_steps, seed, top_k, ws, s);
+    st = upload_dock(g, pl, w, waves, n_chains, n_steps, seed, top_k, ws, s, blocks);
     if (st) return st;
 
     Events ev;
@@ -1203,8 +1329,8 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
     float *rec = (float *)(ws + w.records);
     float4 *bxyz = (float4 *)(ws + w.xyz);
     int *sel = (int *)(ws + w.sel);
-    HIP_TRY(launch_tick(search_class(pl.h), waves, search_lds_bytes(pl.h, waves),
-                        (const uint32_t *)(ws + w.arena), (const ChainTask *)(ws + w.tasks), n_chains,
+    HIP_TRY(launch_tick(search_class(pl.h), waves, lds,
+                        (const uint32_t *)(ws + w.arena), (const ChainTask *)(ws + w.tasks), (int)blocks,
                         (const GridView *)(ws + w.grids), sp, n_steps, 1, (float *)(ws + w.state), rec, bxyz, s),
             "search launch");
     if (stats) HIP_TRY(hipEventRecord(ev.e[1], s), "event");
@@ -1276,7 +1402,8 @@ namespace {
 struct BatchGroup {
     int cls = 0, waves = 1;
     size_t lds = 0;
-    long first = 0, count = 0;
+    long first = 0, count = 0;   // its tasks
+    long blocks = 0;             // its workgroups (upload_plan)
 };
 struct BatchPlan {
     std::vector<BatchGroup> groups;
@@ -1287,7 +1414,8 @@ struct BatchPlan {
 // The plan of candidate `c`: each ligand's layout from its pair class, one
 // launch per (kernel variant, waves); waves lowered for a launch whose largest
 // member does not fit the LDS.  Returns false when a ligand cannot run.
-bool tuned_plan(int c, const std::vector<Prepared> &pp, const std::vector<Prepared> &pa, int n_chains, BatchPlan &out)
+bool tuned_plan(int c, const std::vector<Prepared> &pp, const std::vector<Prepared> &pa,
+                const std::vector<Prepared> &ps, int n_chains, BatchPlan &out)
 {
     const Plan pl = plan(c);
     out = BatchPlan();
@@ -1295,21 +1423,21 @@ bool tuned_plan(int c, const std::vector<Prepared> &pp, const std::vector<Prepar
     out.blob.resize((size_t)n);
     std::map<std::pair<int, int>, std::vector<int>> groups;
     for (int l = 0; l < n; l++) {
-        const Prepared &pr = plan_form(pl, pp[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS ? pp[(size_t)l] : pa[(size_t)l];
+        const bool lists = plan_form(pl, pp[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS;
+        const Prepared &pr = !lists ? pa[(size_t)l] : pl.waves == 1 ? ps[(size_t)l] : pp[(size_t)l];
         out.blob[(size_t)l] = &pr;
-        groups[{search_class(pr.h), pl.waves}].push_back(l);
+        // pair-stream launches by size, since a launch reserves its largest member's LDS
+        const int size = pr.h.intra_form == kFormStream ? (pr.h.n_pairs > 512) + (pr.h.n_pairs > 1024) : 0;
+        groups[{search_class(pr.h) + 8 * size, pl.waves}].push_back(l);
     }
     for (auto &kv : groups) {
         BatchGroup b;
-        b.cls = kv.first.first;
+        b.cls = kv.first.first % 8;
         b.waves = kv.first.second;
-        for (;;) {
-            b.lds = 0;
-            for (int l : kv.second) b.lds = std::max(b.lds, search_lds_bytes(out.blob[(size_t)l]->h, b.waves));
-            if (b.lds <= device_max_lds() || b.waves == 1) break;
-            b.waves--;
-        }
-        if (b.lds > device_max_lds()) return false;
+        int worst = kv.second[0];
+        for (int l : kv.second)
+            if (search_lds_bytes(out.blob[(size_t)l]->h, 1) > search_lds_bytes(out.blob[(size_t)worst]->h, 1)) worst = l;
+        if (launch_shape(out.blob[(size_t)worst]->h, (long)kv.second.size() * n_chains, b.waves, b.lds)) return false;
         // the largest ligands' chains first, so that the launch ends on short work
         std::vector<int> mem = kv.second;
         std::stable_sort(mem.begin(), mem.end(), [&](int a, int c) {
@@ -1326,7 +1454,7 @@ bool tuned_plan(int c, const std::vector<Prepared> &pp, const std::vector<Prepar
 
 // Upload a plan's host-written sections: blobs, tasks in the plan's order, the
 // grid view, ranking segments.
-dsdp_status upload_plan(const BatchPlan &bp, const dsdp_grids_s *g, const uint64_t *seeds, int n_chains, int n_steps,
+dsdp_status upload_plan(BatchPlan &bp, const dsdp_grids_s *g, const uint64_t *seeds, int n_chains, int n_steps,
                         int top_k, const SearchWs &w, char *ws, hipStream_t s)
 {
     const int n_ligs = (int)bp.blob.size();
@@ -1353,6 +1481,12 @@ dsdp_status upload_plan(const BatchPlan &bp, const dsdp_grids_s *g, const uint64
             t.slot = (int)((long)l * n_chains + c);
             t.fresh = 0;
         }
+    for (BatchGroup &b : bp.groups) {
+        b.blocks = b.count;
+        if (b.cls != kStreamClass) continue;
+        b.blocks = 0;
+        for (long f = 0; f < b.count; f += n_chains) fill_stream_groups(tasks + b.first, b.blocks, f, n_chains, b.waves);
+    }
     GridView view;
     dsdp_status st = device_view(g, ws, w, img.bytes.data(), s, view);
     if (st) return st;
@@ -1407,7 +1541,7 @@ hipError_t launch_plan(const BatchPlan &bp, Branches &br, const SearchWs &w, cha
         le = hipStreamWaitEvent(br.s[(size_t)i], br.e[(size_t)nb], 0);
         for (int k = 0; k < n_ticks && le == hipSuccess; k++)
             le = launch_tick(b.cls, b.waves, b.lds, (const uint32_t *)(ws + w.arena),
-                             (const ChainTask *)(ws + w.tasks) + b.first, (int)b.count,
+                             (const ChainTask *)(ws + w.tasks) + b.first, (int)b.blocks,
                              (const GridView *)(ws + w.grids), sp, spt, (k == 0 && fresh) ? 1 : 0, (float *)(ws + w.state),
                              (float *)(ws + w.records), (float4 *)(ws + w.xyz), br.s[(size_t)i]);
         if (le == hipSuccess) le = hipEventRecord(br.e[(size_t)i], br.s[(size_t)i]);
@@ -1486,22 +1620,30 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
     const dsdp_params &pp = prm ? *prm : def;
     const bool tune = pp.tune == 1 && pp.optimizer == DSDP_OPT_BFGS && pp.waves_per_chain == 0 &&
                       pp.intra_form == DSDP_INTRA_AUTO && n_steps > 0;
-    // every ligand prepared in the fixed rule's layout (atom lists for a mixed
-    // launch, unless the caller fixed one) and, when tuning, in the other one
-    std::vector<Prepared> pls((size_t)n_ligs), alt(tune ? (size_t)n_ligs : 0);
+    // every ligand prepared in the fixed rule's layout (unless the caller fixed one) or,
+    // when tuning, in all three
+    std::vector<Prepared> pls((size_t)n_ligs), atoms(tune ? (size_t)n_ligs : 0), streams(tune ? (size_t)n_ligs : 0);
     size_t words = 0;
     for (int l = 0; l < n_ligs; l++) {
-        st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], intra_ctx(prm, (long)n_ligs * n_chains, true));
-        if (!st && tune) {
-            const int other = pls[(size_t)l].h.intra_form == kFormPairs ? DSDP_INTRA_ATOMS : DSDP_INTRA_PAIRS;
-            st = prepare_ligand(&ligs[l], g->map_of_type, alt[(size_t)l], IntraCtx{other});
+        if (tune) {
+            IntraCtx ctx;
+            ctx.form = DSDP_INTRA_PAIRS;
+            ctx.waves = 2;
+            st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], ctx);
+            ctx.waves = 1;
+            if (!st) st = prepare_ligand(&ligs[l], g->map_of_type, streams[(size_t)l], ctx);
+            ctx.form = DSDP_INTRA_ATOMS;
+            if (!st) st = prepare_ligand(&ligs[l], g->map_of_type, atoms[(size_t)l], ctx);
+        } else {
+            st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], intra_ctx(prm, (long)n_ligs * n_chains, true));
         }
         if (st) {
             char msg[600];
             snprintf(msg, sizeof msg, "ligand %d: %s", l, g_error.c_str());
             return fail(st, "%s", msg);
         }
-        words += max_blob_words(&ligs[l]);
+        words += tune ? (size_t)std::max(pls[(size_t)l].h.total_words, atoms[(size_t)l].h.total_words)
+                      : max_blob_words(&ligs[l]);
     }
     const long n_slots = (long)n_ligs * n_chains;
     const SearchWs w = search_ws(words, n_slots, 1, n_ligs);
@@ -1519,9 +1661,6 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
 
     BatchPlan bp;
     if (tune) {
-        // the fixed rule's layout is in pls, the other in alt
-        const bool pls_atoms = pls[0].h.intra_form == kFormAtoms;
-        const std::vector<Prepared> &pp_pairs = pls_atoms ? alt : pls, &pp_atoms = pls_atoms ? pls : alt;
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev), "device");
         std::vector<ShapeBucket> shapes((size_t)n_ligs);
@@ -1536,7 +1675,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
         // starts afresh)
         auto measure = [&](int c) -> float {
             BatchPlan tp;
-            if (mst || !tuned_plan(c, pp_pairs, pp_atoms, n_chains, tp)) return -1.f;
+            if (mst || !tuned_plan(c, pls, atoms, streams, n_chains, tp)) return -1.f;
             // 1 + kTrialSteps steps whatever the batch's length, so that batches of
             // any length share the cached pick
             if ((mst = upload_plan(tp, g, seeds, n_chains, 1 + kTrialSteps, top_k, w, ws, cs))) return -1.f;
@@ -1557,7 +1696,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
         int pick = 0;
         const bool found = tuner().pick(key, measure, pick, n_slots, kTrialSteps);
         if (mst) return mst;
-        if (!found || !tuned_plan(pick, pp_pairs, pp_atoms, n_chains, bp))
+        if (!found || !tuned_plan(pick, pls, atoms, streams, n_chains, bp))
             return fail(DSDP_ERR_UNSUPPORTED, "no launch plan fits the batch");
     } else {
         std::vector<const LigHeader *> hdr((size_t)n_ligs);

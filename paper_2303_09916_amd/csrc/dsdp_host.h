@@ -40,15 +40,16 @@ struct Prepared {
     std::vector<int> map_index;   // per atom
 };
 // Where a prepared ligand will run: the caller's layout request
-// (DSDP_INTRA_*), the chains of the launch and whether the launch mixes
-// ligands.  With DSDP_INTRA_AUTO the layout follows choose_intra_form.
+// (DSDP_INTRA_*) and waves per chain (0: by the chain count), the chains of the
+// launch and whether the launch mixes ligands.
 struct IntraCtx {
     int form = DSDP_INTRA_AUTO;
+    int waves = 0;
     long chains = 1;
     bool mixed = false;
 };
 IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed);
-int choose_intra_form(int n_pairs, long chains, bool mixed);
+int choose_intra_form(const IntraCtx &ctx);   // kForm*
 dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepared &out, const IntraCtx &ctx);
 // blob words of the larger of the two forms (workspace sizing without params); 0 on invalid input
 size_t max_blob_words(const dsdp_ligand *lig);
@@ -58,6 +59,8 @@ SearchParams to_search(const dsdp_params *p);
 int device_cus();
 size_t device_max_lds();
 dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains, int &waves);
+dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds);
+void fill_stream_groups(ChainTask *launch_tasks, long &blocks, long first, long n, int waves);
 // One launch per kernel variant over the ligands that use it; each launch
 // reserves its largest member's LDS for every workgroup.
 struct LaunchGroup {

@@ -91,19 +91,30 @@ struct LigHeader {
     int32_t intra_form;      // kFormPairs or kFormAtoms (how the intra-ligand term is laid out)
     int32_t nbr_words;       // atom lists: words of packed partner bytes per lane
     int32_t off_nbr;         // atom lists: uint32[nbr_words][64], byte = partner | hydrophobic << 6 | hbond << 7
-    int32_t off_atom_rad;    // float[n_atoms] XS radius (both layouts)
+    int32_t off_atom_rad;    // float[n_atoms] XS radius (every layout)
+    // pair stream: n_chunks chunks of 127 pairs (the last one shorter)
+    int32_t off_slist;       // uint32[words of all chunks][64]: per lane, chunk after chunk, four
+                             // bytes each: pair's index in the chunk | 128 for its second atom
+    uint32_t chunk_words[2]; // words per chunk, four bits each
+    uint32_t chunk_plain;    // leading slots of each chunk without a class pair, two bits each
     int32_t total_words;     // multiple of 4
 };
 
-// Two layouts of the intra-ligand term.  Pair lists: lane l evaluates pairs
+// Layouts of the intra-ligand term.  Pair lists: lane l evaluates pairs
 // l + 64 k once and stores each pair's force in LDS; every atom then gathers the
 // forces of its pairs.  Atom lists: a lane owns an atom (or half of its partners
 // when there are at most 32 atoms) and evaluates each of the atom's pairs from
 // its own side, so every pair is evaluated twice but nothing per pair is kept
 // in LDS.  The second trades arithmetic for LDS and registers; which one a ligand
 // uses depends on its shape only (choose_intra_form).
+// The pair stream is the pair lists' arithmetic for chains of one wave each: the
+// pairs come in chunks whose forces fit 2 KB, and several chains of a workgroup
+// share the ligand, so that LDS holds enough chains to fill the chip.
 constexpr int kFormPairs = 0;
 constexpr int kFormAtoms = 1;
+constexpr int kFormStream = 2;
+constexpr int kStreamPairs = 127;   // pairs per chunk
+constexpr int kStreamChains = 4;    // chains per workgroup
 constexpr uint32_t kNbrNone = 0xFFu;   // empty partner byte (no pair is both hydrophobic and H-bonding)
 constexpr int kHeaderWords = (int)(sizeof(LigHeader) / 4 + 3) / 4 * 4;
 
@@ -125,7 +136,10 @@ struct ChainTask {
     int32_t grid;            // index into the GridView array
     int32_t slot;            // index of the chain's state, record and best coordinates
     int32_t fresh;           // 1: start the chain from its initial pose in this launch
-    int32_t pad[3];
+    // Pair stream: the tasks of the launch's workgroup of this task's number (counted
+    // from the launch's first task), which share a ligand.
+    int32_t wg_first, wg_count;
+    int32_t pad;
 };
 
 // Resumable chain state in device memory (words): a chain advanced in several
@@ -178,14 +192,15 @@ hipError_t launch_local_opt(const uint32_t *blob, int blob_words, const LigHeade
                             float *energy, int *evals, hipStream_t stream);
 // Advance every task by up to tick_steps MC steps (init = start chains afresh).
 // cls: search_class of every task's ligand; lds_bytes: per-workgroup LDS.
+// n_blocks: the tasks, or (pair stream) the workgroups their wg_* fields describe.
 hipError_t launch_tick(int cls, int waves, size_t lds_bytes, const uint32_t *arena, const ChainTask *tasks,
-                       int n_tasks, const GridView *grids, const SearchParams &p, int tick_steps, int init,
+                       int n_blocks, const GridView *grids, const SearchParams &p, int tick_steps, int init,
                        float *state, float *records, float4 *best_xyz, hipStream_t stream);
 hipError_t launch_rank(const float *records, const float4 *best_xyz, const RankSeg *segs, int n_segs,
                        int max_chains, float rmsd_cut, int *sel, hipStream_t stream);
 // Kernel variant of a prepared ligand: 0..2 pair lists with 8, 16, 32 pair
-// slots per lane; 3 atom lists.
-constexpr int kNumClasses = 4;
+// slots per lane; 3 atom lists; 4 pair stream.
+constexpr int kStreamClass = 4;
 int search_class(const LigHeader &h);
 // Size of the per-device static scratch array behind dsdp_dock_static, and its
 // device address on the current device (looked up on first use per device).

@@ -51,6 +51,8 @@ struct Request {
     int64_t ticket = 0;
     int receptor = 0;
     Prepared pl;
+    Prepared stream;         // the pair stream of the ligand, where the layout is the library's choice
+    bool has_stream = false; // it is in the pool too, behind pl's blob
     int n_chains = 0, n_steps = 0, top_k = 0;
     uint64_t seed = 0;
     int state = kQueued;
@@ -210,9 +212,17 @@ dsdp_status admit(dsdp_sched s)
         }
         if (blocked) break;
         size_t so = 0, ao = 0;
-        const size_t ab = align256(q->pl.blob.size() * 4);
+        const size_t first = align256(q->pl.blob.size() * 4);
+        size_t ab = first;
         bool ok = s->slots.alloc((size_t)q->n_chains, so);
-        if (ok && !s->mem.alloc(ab, ao)) {
+        q->has_stream = false;
+        if (ok && !q->stream.blob.empty()) {
+            // both layouts where the pool has room for them, else the first alone
+            const size_t both = first + align256(q->stream.blob.size() * 4);
+            q->has_stream = s->receptors[(size_t)q->receptor].resident && s->mem.alloc(both, ao);
+            if (q->has_stream) ab = both;
+        }
+        if (ok && !q->has_stream && !s->mem.alloc(ab, ao)) {
             s->slots.release(so, (size_t)q->n_chains);
             ok = false;
         }
@@ -238,6 +248,10 @@ dsdp_status admit(dsdp_sched s)
         }
         HIP_TRY(hipMemcpyAsync(s->pool + ao, q->pl.blob.data(), q->pl.blob.size() * 4, hipMemcpyHostToDevice, s->stream),
                 "ligand upload");
+        if (q->has_stream)
+            HIP_TRY(hipMemcpyAsync(s->pool + ao + first, q->stream.blob.data(), q->stream.blob.size() * 4,
+                                   hipMemcpyHostToDevice, s->stream),
+                    "ligand upload");
         q->slot0 = so;
         q->arena_off = ao;
         q->arena_bytes = ab;
@@ -395,8 +409,18 @@ dsdp_status dsdp_sched_submit(dsdp_sched s, int32_t receptor_id, const dsdp_liga
     dsdp_status st = check_work(&s->prm, n_steps);
     if (st) return st;
     std::unique_ptr<Request> q(new Request());
-    st = prepare_ligand(lig, s->receptors[(size_t)receptor_id].map_of_type, q->pl,
-                                    intra_ctx(&s->prm, s->capacity, true));
+    // the layout is chosen at each tick by the running chains, where the caller
+    // leaves it to the library: atom lists, or the pair stream from one wave per chain on
+    const bool choose = s->prm.intra_form == DSDP_INTRA_AUTO && s->prm.waves_per_chain == 0;
+    IntraCtx ctx = intra_ctx(&s->prm, s->capacity, true);
+    if (choose) {
+        ctx.waves = 1;
+        st = prepare_ligand(lig, s->receptors[(size_t)receptor_id].map_of_type, q->stream, ctx);
+        if (st) return st;
+        if (q->stream.h.intra_form != kFormStream) q->stream = Prepared();
+        ctx.form = DSDP_INTRA_ATOMS;
+    }
+    st = prepare_ligand(lig, s->receptors[(size_t)receptor_id].map_of_type, q->pl, ctx);
     if (st) return st;
     if (search_lds_bytes(q->pl.h, 1) > device_max_lds())
         return fail(DSDP_ERR_UNSUPPORTED, "ligand needs %zu bytes of LDS", search_lds_bytes(q->pl.h, 1));
@@ -450,25 +474,33 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
     // tasks of every running chain, in launch groups (kernel variant and LDS need)
     s->h_tasks.clear();
     std::vector<LaunchGroup> groups;
+    bool one_wave = false;   // enough chains for one wave each (choose_intra_form's rule)
     {
         std::vector<const LigHeader *> hdr;
         std::vector<long> ch;
+        long total = 0;
+        for (Request *q : s->running) total += q->n_chains;
+        one_wave = total > 4L * device_cus();
         for (Request *q : s->running) {
-            hdr.push_back(&q->pl.h);
+            hdr.push_back(one_wave && q->has_stream ? &q->stream.h : &q->pl.h);
             ch.push_back(q->n_chains);
         }
         st = plan_groups(&s->prm, hdr, ch, groups);
         if (st) return st;
     }
-    std::vector<long> first;
+    std::vector<long> first, blocks;
     for (const LaunchGroup &g : groups) {
         first.push_back((long)s->h_tasks.size());
+        blocks.push_back(g.chains);
         for (int m : g.members) {
             const Request *q = s->running[(size_t)m];
+            const bool stream = g.cls == kStreamClass && q->has_stream;
+            const Prepared &pl = stream ? q->stream : q->pl;
+            const size_t off = q->arena_off + (stream ? align256(q->pl.blob.size() * 4) : 0);
             for (int c = 0; c < q->n_chains; c++) {
                 ChainTask t{};
-                t.blob_off = (uint32_t)(q->arena_off / 4);
-                t.blob_words = (uint32_t)q->pl.h.total_words;
+                t.blob_off = (uint32_t)(off / 4);
+                t.blob_words = (uint32_t)pl.h.total_words;
                 t.chain = (uint32_t)c;
                 t.n_steps = q->n_steps;
                 t.seed_lo = (uint32_t)q->seed;
@@ -477,6 +509,15 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
                 t.slot = (int32_t)(q->slot0 + c);
                 t.fresh = q->fresh ? 1 : 0;
                 s->h_tasks.push_back(t);
+            }
+        }
+        if (g.cls == kStreamClass) {
+            blocks.back() = 0;
+            long f = 0;
+            for (int m : g.members) {
+                const long n = s->running[(size_t)m]->n_chains;
+                fill_stream_groups(s->h_tasks.data() + first.back(), blocks.back(), f, n, g.waves);
+                f += n;
             }
         }
     }
@@ -492,7 +533,7 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
     for (size_t k = 0; k < groups.size(); k++) {
         const LaunchGroup &g = groups[k];
         HIP_TRY(launch_tick(g.cls, g.waves, g.lds, (const uint32_t *)s->pool,
-                            (const ChainTask *)(s->pool + s->off_tasks) + first[k], (int)g.chains,
+                            (const ChainTask *)(s->pool + s->off_tasks) + first[k], (int)blocks[k],
                             (const GridView *)(s->pool + s->off_grids), s->sp, s->spt, 0,
                             (float *)(s->pool + s->off_state), (float *)(s->pool + s->off_records),
                             (float4 *)(s->pool + s->off_xyz), s->stream),

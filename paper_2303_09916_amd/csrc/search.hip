@@ -20,6 +20,7 @@
 #include "dsdp_internal.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace dsdp {
 namespace {
@@ -27,7 +28,8 @@ namespace {
 constexpr float kPi = 3.14159265358979323846f;
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
-__device__ __forceinline__ int wave_id() { return (int)(threadIdx.x >> 6); }
+// uniform over the wave, and known to be: pointers and branches by wave stay scalar
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // Make a wave's LDS writes visible to its other lanes.
 __device__ __forceinline__ void wave_sync()
@@ -58,6 +60,18 @@ __device__ __forceinline__ float wave_sum(float v)
     v += dpp<0x141>(v);   // row_half_mirror
     v += dpp<0x140>(v);   // row_mirror
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+
+// Minimum over the 64 lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+{
+    v = min(v, __float_as_uint(dpp<0xB1>(__uint_as_float(v))));
+    v = min(v, __float_as_uint(dpp<0x4E>(__uint_as_float(v))));
+    v = min(v, __float_as_uint(dpp<0x141>(__uint_as_float(v))));
+    v = min(v, __float_as_uint(dpp<0x140>(__uint_as_float(v))));
+    const int a = (int)v;
+    return min(min((uint32_t)__builtin_amdgcn_readlane(a, 0), (uint32_t)__builtin_amdgcn_readlane(a, 16)),
+               min((uint32_t)__builtin_amdgcn_readlane(a, 32), (uint32_t)__builtin_amdgcn_readlane(a, 48)));
 }
 
 template <int CTRL, int ROWS>
@@ -122,74 +136,94 @@ __device__ __forceinline__ float4 as_float4(v4f v) { return make_float4(v.x, v.y
 struct M3 {
     float a[9];
 };
+// The quaternion and vector operations are written as explicit fused
+// multiply-adds, with no others formed: a chain's path depends on every last bit,
+// and must not depend on what an inlined operation stands next to.
 __device__ __forceinline__ M3 quat_to_mat(float w, float x, float y, float z)
 {
+#pragma clang fp contract(off)
     M3 R;
-    R.a[0] = 1 - 2 * (y * y + z * z); R.a[1] = 2 * (x * y - w * z);     R.a[2] = 2 * (x * z + w * y);
-    R.a[3] = 2 * (x * y + w * z);     R.a[4] = 1 - 2 * (x * x + z * z); R.a[5] = 2 * (y * z - w * x);
-    R.a[6] = 2 * (x * z - w * y);     R.a[7] = 2 * (y * z + w * x);     R.a[8] = 1 - 2 * (x * x + y * y);
+    R.a[0] = fmaf(-2.f, fmaf(y, y, z * z), 1.f); R.a[1] = 2 * fmaf(x, y, -(w * z)); R.a[2] = 2 * fmaf(x, z, w * y);
+    R.a[3] = 2 * fmaf(x, y, w * z); R.a[4] = fmaf(-2.f, fmaf(x, x, z * z), 1.f); R.a[5] = 2 * fmaf(-w, x, y * z);
+    R.a[6] = 2 * fmaf(x, z, -(w * y)); R.a[7] = 2 * fmaf(w, x, y * z); R.a[8] = fmaf(-2.f, fmaf(x, x, y * y), 1.f);
     return R;
-}
-__device__ __forceinline__ M3 axis_angle(float ux, float uy, float uz, float th)
-{
-    const float s = __sinf(th), c = __cosf(th);
-    const float t = 1 - c;
-    M3 R;
-    R.a[0] = c + t * ux * ux;      R.a[1] = t * ux * uy - s * uz; R.a[2] = t * ux * uz + s * uy;
-    R.a[3] = t * uy * ux + s * uz; R.a[4] = c + t * uy * uy;      R.a[5] = t * uy * uz - s * ux;
-    R.a[6] = t * uz * ux - s * uy; R.a[7] = t * uz * uy + s * ux; R.a[8] = c + t * uz * uz;
-    return R;
-}
-__device__ __forceinline__ M3 mul(const M3 &A, const M3 &B)
-{
-    M3 C;
-#pragma unroll
-    for (int r = 0; r < 3; r++)
-#pragma unroll
-        for (int c = 0; c < 3; c++) C.a[3 * r + c] = A.a[3 * r] * B.a[c] + A.a[3 * r + 1] * B.a[3 + c] + A.a[3 * r + 2] * B.a[6 + c];
-    return C;
-}
-__device__ __forceinline__ float3 mv(const M3 &A, float3 v)
-{
-    return make_float3(A.a[0] * v.x + A.a[1] * v.y + A.a[2] * v.z, A.a[3] * v.x + A.a[4] * v.y + A.a[5] * v.z,
-                       A.a[6] * v.x + A.a[7] * v.y + A.a[8] * v.z);
 }
 __device__ __forceinline__ float3 cross3(float3 a, float3 b)
 {
-    return make_float3(a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x);
+#pragma clang fp contract(off)
+    return make_float3(fmaf(a.y, b.z, -(a.z * b.y)), fmaf(a.z, b.x, -(a.x * b.z)), fmaf(a.x, b.y, -(a.y * b.x)));
 }
 __device__ __forceinline__ float3 f3(float4 v) { return make_float3(v.x, v.y, v.z); }
-__device__ __forceinline__ M3 load_m3(const float4 *rows)
-{
-    const float4 r0 = rows[0], r1 = rows[1], r2 = rows[2];
-    M3 M;
-    M.a[0] = r0.x; M.a[1] = r0.y; M.a[2] = r0.z;
-    M.a[3] = r1.x; M.a[4] = r1.y; M.a[5] = r1.z;
-    M.a[6] = r2.x; M.a[7] = r2.y; M.a[8] = r2.z;
-    return M;
-}
 __device__ __forceinline__ float3 operator+(float3 a, float3 b) { return make_float3(a.x + b.x, a.y + b.y, a.z + b.z); }
 __device__ __forceinline__ float3 operator-(float3 a, float3 b) { return make_float3(a.x - b.x, a.y - b.y, a.z - b.z); }
 __device__ __forceinline__ float3 operator*(float s, float3 a) { return make_float3(s * a.x, s * a.y, s * a.z); }
 __device__ __forceinline__ float dot3(float3 a, float3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
 
+// Correctly rounded square root, quotient and reciprocal square root without the
+// compiler's handling of denormal and extreme arguments, for arguments in
+// kNormalLo..kNormalHi (a quotient also wants one there): the hardware estimate
+// and one residual step (Markstein).  Root and reciprocal were compared with
+// sqrtf and 1/x over every float in [2^-96, 64), the quotient on 1.7e10 pairs;
+// rsqrtf is the bare estimate there.  41 to 101 cycles of one wave become 9 to 40.
+constexpr float kNormalLo = 0x1p-80f, kNormalHi = 64.0f;
+__device__ __forceinline__ bool in_normal(float x)
+{
+    return __float_as_uint(x) - __float_as_uint(kNormalLo) < __float_as_uint(kNormalHi) - __float_as_uint(kNormalLo);
+}
+// whether any active lane's x lies outside the range
+__device__ __forceinline__ bool any_odd(float x) { return __builtin_amdgcn_ballot_w64(!in_normal(x)) != 0; }
+__device__ __forceinline__ float sqrt_normal(float x)
+{
+#pragma clang fp contract(off)
+    const float y = __builtin_amdgcn_rsqf(x), g = x * y;
+    return fmaf(fmaf(-g, g, x), 0.5f * y, g);
+}
+__device__ __forceinline__ float rcp_normal(float b)
+{
+#pragma clang fp contract(off)
+    const float y = __builtin_amdgcn_rcpf(b);
+    return fmaf(fmaf(-b, y, 1.0f), y, y);
+}
+__device__ __forceinline__ float div_normal(float a, float b)
+{
+#pragma clang fp contract(off)
+    const float y = rcp_normal(b);
+    const float q = a * y;
+    return fmaf(fmaf(-b, q, a), y, q);
+}
+
 // unit quaternion of rotation vector v (angle |v| about v/|v|), (w, x, y, z);
-// the identity for v = 0 (selected, no branch)
+// the identity for v = 0
 __device__ __forceinline__ float4 quat_of_rotvec(float vx, float vy, float vz)
 {
-    const float a = sqrtf(vx * vx + vy * vy + vz * vz);
+#pragma clang fp contract(off)
+    const float n2 = fmaf(vz, vz, fmaf(vx, vx, vy * vy));
+    if (!any_odd(n2)) {
+        const float a = sqrt_normal(n2);
+        const float s = __sinf(0.5f * a), c = __cosf(0.5f * a);
+        const float k = div_normal(s, a);
+        return make_float4(c, k * vx, k * vy, k * vz);
+    }
+    const float a = sqrtf(n2);
     const float s = __sinf(0.5f * a), c = __cosf(0.5f * a);
     const float k = s / a;
     const bool z = a == 0.0f;
     return make_float4(z ? 1.f : c, z ? 0.f : k * vx, z ? 0.f : k * vy, z ? 0.f : k * vz);
 }
-// Hamilton product a * b, (w, x, y, z) in (x, y, z, w) slots of float4 as w=x-slot
+// Hamilton product a * b, (w, x, y, z) in (x, y, z, w) slots of float4 as w=x-slot.
+// Two roundings of the second and fourth component: which of the first two products
+// is rounded before the fused additions (the right-hand one, or with LEFT the
+// left-hand one).  Each use keeps one.
+template <bool LEFT>
 __device__ __forceinline__ float4 quat_mul(float4 a, float4 b)
 {
-    return make_float4(a.x * b.x - a.y * b.y - a.z * b.z - a.w * b.w,
-                       a.x * b.y + a.y * b.x + a.z * b.w - a.w * b.z,
-                       a.x * b.z - a.y * b.w + a.z * b.x + a.w * b.y,
-                       a.x * b.w + a.y * b.z - a.z * b.y + a.w * b.x);
+#pragma clang fp contract(off)
+    const float y = LEFT ? fmaf(a.y, b.x, a.x * b.y) : fmaf(a.x, b.y, a.y * b.x);
+    const float w = LEFT ? fmaf(a.y, b.z, a.x * b.w) : fmaf(a.x, b.w, a.y * b.z);
+    return make_float4(fmaf(-a.w, b.w, fmaf(-a.z, b.z, fmaf(a.x, b.x, -(a.y * b.y)))),
+                       fmaf(-a.w, b.z, fmaf(a.z, b.w, y)),
+                       fmaf(a.w, b.y, fmaf(a.z, b.x, fmaf(a.x, b.z, -(a.y * b.w)))),
+                       fmaf(a.w, b.x, fmaf(-a.z, b.y, w)));
 }
 // rotation by th about the unit axis u (xyz) as a quaternion (w, x, y, z in x, y, z, w)
 __device__ __forceinline__ float4 quat_axis(float4 u, float th)
@@ -200,13 +234,19 @@ __device__ __forceinline__ float4 quat_axis(float4 u, float th)
 // R(q) v for a unit quaternion q: v + w t + r x t with t = 2 r x v, r the vector part
 __device__ __forceinline__ float3 quat_rotate(float4 q, float3 v)
 {
+#pragma clang fp contract(off)
     const float3 r = make_float3(q.y, q.z, q.w);
-    const float3 t = 2.f * cross3(r, v);
-    return v + q.x * t + cross3(r, t);
+    const float3 t = 2.f * cross3(r, v), c = cross3(r, t);
+    return make_float3(fmaf(q.x, t.x, v.x) + c.x, fmaf(q.x, t.y, v.y) + c.y, fmaf(q.x, t.z, v.z) + c.z);
 }
-__device__ __forceinline__ float4 quat_normalize(float4 q)
+// A caller's quaternion (check) may have any length; all others are unit up to
+// rounding (or not finite, which both forms pass on).
+__device__ __forceinline__ float4 quat_normalize(float4 q, bool check)
 {
-    const float k = rsqrtf(q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w);
+#pragma clang fp contract(off)
+    const float n2 = fmaf(q.w, q.w, fmaf(q.z, q.z, fmaf(q.x, q.x, q.y * q.y)));
+    float k = __builtin_amdgcn_rsqf(n2);
+    if (check && any_odd(n2)) k = rsqrtf(n2);
     return make_float4(q.x * k, q.y * k, q.z * k, q.w * k);
 }
 // into (-pi, pi]; non-finite values pass through, huge ones are reduced first
@@ -240,12 +280,14 @@ __device__ __forceinline__ float3 ball(float u1, float u2, float u3)
 // as (e, de).  wh and wb are the pair's hydrophobic and hydrogen-bond weights
 // (0 when the pair is not of that class).  Piecewise terms in branch-free form;
 // at a kink the left-hand slope is taken.
+// With PLAIN the pair has no class (both weights +0, which add nothing).
+template <bool PLAIN = false>
 __device__ __forceinline__ float2 vina_pair(float d, float wh, float wb)
 {
+#pragma clang fp contract(off)
     // The fused multiply-adds are written out and no others are formed: the two
     // intra-ligand layouts inline this in different surroundings and must round
     // alike.
-#pragma clang fp contract(off)
     // the two gauss terms |w| exp(-k x^2) as exp2(x^2 (-k log2 e) + log2 |w|), the
     // weight folded into the exponent; both weights are negative
     static_assert(kWGauss1 == -0.0356f && kWGauss2 == -0.00516f, "exponent constants below");
@@ -254,17 +296,26 @@ __device__ __forceinline__ float2 vina_pair(float d, float wh, float wb)
     constexpr float kC2 = -0.360673755f;  // -0.25 log2(e)
     constexpr float kL2 = -7.59841299f;   // log2(0.00516)
     const float a1 = __builtin_amdgcn_exp2f(fmaf(d * d, kC1, kL1));   // -w1
-    const float b = d - 3.0f;
-    const float a2 = __builtin_amdgcn_exp2f(fmaf(b * b, kC2, kL2));   // -w2
+    const float hb = fmaf(d, 0.5f, -1.5f);   // (d - 3) / 2, scaled exactly
+    const float a2 = __builtin_amdgcn_exp2f(fmaf(hb * hb, 4.0f * kC2, kL2));   // -w2
     const float dn = fminf(d, 0.0f);
     float e = fmaf(kWRepulsion * dn, dn, -(a1 + a2));
-    float de = fmaf(kWRepulsion * 2.0f, dn, fmaf(a2, 0.5f * b, a1 * (8.0f * d)));
+    float de = fmaf(kWRepulsion * 2.0f, dn, fmaf(a2, hb, a1 * (8.0f * d)));
+    if constexpr (PLAIN) return make_float2(e, de);
     e = fmaf(wh, fminf(fmaxf(1.5f - d, 0.0f), 1.0f), fmaf(wb, fminf(fmaxf(-d * (1.0f / 0.7f), 0.0f), 1.0f), e));
     de += ((d > 0.5f && d <= 1.5f) ? -wh : 0.0f) + ((d > -0.7f && d <= 0.0f) ? -wb * (1.0f / 0.7f) : 0.0f);
     return make_float2(e, de);
 }
-__device__ __forceinline__ float pair_wh(uint32_t flags) { return (flags & kPairHydrophobic) ? kWHydrophobic : 0.0f; }
-__device__ __forceinline__ float pair_wb(uint32_t flags) { return (flags & kPairHBond) ? kWHBond : 0.0f; }
+// a class weight, or +0, by the class's bit spread over a mask
+template <uint32_t BIT>
+__device__ __forceinline__ float class_weight(uint32_t flags, float w)
+{
+    constexpr int sh = BIT == 1u ? 0 : 1;
+    static_assert(BIT == 1u || BIT == 2u, "");
+    return __int_as_float(__builtin_amdgcn_sbfe((int)flags, sh, 1) & __float_as_int(w));
+}
+__device__ __forceinline__ float pair_wh(uint32_t flags) { return class_weight<kPairHydrophobic>(flags, kWHydrophobic); }
+__device__ __forceinline__ float pair_wb(uint32_t flags) { return class_weight<kPairHBond>(flags, kWHBond); }
 
 // Squared distance and the pair's (energy, dE/dr / r) for radius sum rsum and
 // class flags: one definition for both intra-ligand layouts, so that both
@@ -273,11 +324,13 @@ __device__ __forceinline__ float pair_r2(float dx, float dy, float dz)
 {
     return fmaf(dx, dx, fmaf(dy, dy, dz * dz));
 }
+template <bool PLAIN = false>
 __device__ __forceinline__ float2 pair_term(float r2, float rsum, uint32_t flags)
 {
 #pragma clang fp contract(off)
-    const float inv_r = r2 > 1e-18f ? rsqrtf(r2) : 0.f;
-    const float2 ed = vina_pair(fmaf(r2, inv_r, -rsum), pair_wh(flags), pair_wb(flags));
+    // beyond the cutoff the caller drops the pair, so the bare estimate does
+    const float inv_r = r2 > 1e-18f ? __builtin_amdgcn_rsqf(r2) : 0.f;
+    const float2 ed = vina_pair<PLAIN>(fmaf(r2, inv_r, -rsum), pair_wh(flags), pair_wb(flags));
     return make_float2(ed.x, ed.y * inv_r);
 }
 
@@ -315,16 +368,28 @@ struct LigL {
     const uint32_t *nbr;     // [nbr_words][64] packed partner bytes (atom lists)
     const float *arad;       // [na] XS radius
     int nbr_words;
+    const uint32_t *slist;   // pair stream: gather words
+    uint32_t chunk_words[2], chunk_plain;
 };
+
+// Kernel variants by how the intra-ligand term is laid out: pair slots held per
+// lane (8, 16, 32), atom lists, or the pair stream.
+constexpr int kAtoms = 0, kStream = -1;
+
+// Waves per SIMD the search kernels' registers must allow.  Register-held pair lists:
+// two, so that two workgroups of four waves share a compute unit (384 chains take
+// 1.5 a unit; with one a launch of 384 took 0.95 ms where it takes 0.61).  The
+// others: three, which the atom lists and the pair stream reach without spills to
+// speak of (four spill the stream's loop invariants).
+template <int PPL>
+constexpr int kMinWaves = PPL == 8 || PPL == 16 ? 2 : 3;
 
 // Scratch of one pose evaluation (one per wave).
 struct WaveL {
     float4 *xyz;
     float4 *pf;            // [np + 1] force of each pair on its first atom (xyz) and its energy
-                           // (w); slot np stays 0
-    float4 *af, *at;       // [64]: per lane, the forces the energy half leaves for the gradient
-                           // half, then prefix sums over atoms of force and of torque about the
-                           // root origin
+                           // (w); slot np stays 0.  Pair stream: [128], one chunk of pairs
+    float4 *af, *at;       // [na]: prefix sums over atoms of force and of torque about the root origin
     float4 *R;       // [nf][4]: rows of R_k, then origin o_k
     float *trial;    // [NXp]: this wave's trial pose
     float *gt;       // [Dp]: gradient at the trial pose
@@ -339,11 +404,13 @@ struct ChainL {
     float *cur, *cand, *best;    // [NXp] poses
     float *et;                   // [4 * kMaxWaves]: energies (total, inter, intra, wall) per trial slot
     float *misc;                 // [48]: initial draws and scalars
+    bool raw;                    // the chain's start pose is a caller's (quaternion of any length)
 };
 
 constexpr int kMaxWaves = 4;     // waves per chain (concurrent line-search trials)
 constexpr int kMiscGp = 40;      // slot of g.p in misc
 constexpr int kMiscBBa = 41;     // slots 41, 42: the Barzilai-Borwein step length (alternating rounds)
+constexpr int kMiscE = 44;       // slots 44..47: energies of the current iterate
 constexpr int kOptBB = 1;        // SearchParams::optimizer value of Barzilai-Borwein
 
 __host__ __device__ inline int rup4(int v) { return (v + 3) & ~3; }
@@ -359,11 +426,17 @@ __host__ __device__ inline Layout make_layout(int na, int nf, int np, int D, int
     c.NXp = rup4(nx);
     int w = 0;
     c.xyz = w; w += 4 * na;
-    // np = -1: no pair-force scratch (atom lists); else the pairs, the zero slot
-    // np, and entries up to a whole group of two 64-pair slots
-    c.pf = w; w += np < 0 ? 0 : 4 * max(np + 1, 128 * ((np + 127) / 128));
-    c.af = w; w += 4 * 64;   // one entry per lane (the energy half leaves its total forces here)
-    c.at = w; w += 4 * 64;
+    // np = -1: no pair-force scratch (atom lists); -2: one chunk (pair stream); else
+    // the pairs, the zero slot np, and entries up to a whole group of two 64-pair slots
+    c.pf = w; w += np == -2 ? 4 * 2 * 64 : np < 0 ? 0 : 4 * max(np + 1, 128 * ((np + 127) / 128));
+    if (np == -2) {
+        // a chunk's forces are gathered before the gradient needs its scratch
+        c.af = c.pf;
+        c.at = c.pf + 4 * na;
+    } else {
+        c.af = w; w += 4 * na;
+        c.at = w; w += 4 * na;
+    }
     c.R = w; w += 16 * nf;
     c.trial = w; w += c.NXp;
     c.gt = w; w += c.Dp;
@@ -392,9 +465,10 @@ __device__ inline WaveL make_wave(float *base, const Layout &c)
     return S;
 }
 
-__device__ inline ChainL make_chain(float *base, const Layout &c)
+__device__ inline ChainL make_chain(float *base, const Layout &c, bool raw)
 {
     ChainL C;
+    C.raw = raw;
     float *v = base + c.vec;
     C.g = v; C.p = v + c.Dp; C.s = v + 2 * c.Dp; C.y = v + 3 * c.Dp; C.Hy = v + 4 * c.Dp;
     C.H = base + c.H;
@@ -431,6 +505,10 @@ __device__ inline LigL make_lig(const uint32_t *blob, const uint32_t *hdr)
     L.nbr = blob + h->off_nbr;
     L.arad = reinterpret_cast<const float *>(blob + h->off_atom_rad);
     L.nbr_words = h->nbr_words;
+    L.slist = blob + h->off_slist;
+    L.chunk_words[0] = h->chunk_words[0];
+    L.chunk_words[1] = h->chunk_words[1];
+    L.chunk_plain = h->chunk_plain;
     return L;
 }
 
@@ -445,7 +523,11 @@ __device__ inline LigL make_lig(const uint32_t *blob, const uint32_t *hdr)
 constexpr uint32_t kPairNone = 0x80000000u;
 template <int PPL>
 constexpr bool reg_pairs() { return PPL == 8 || PPL == 16; }
-template <int PPL, int NBW>
+// np argument of make_layout for a kernel variant
+template <int PPL>
+__device__ inline int layout_pairs(int np) { return PPL > 0 ? np : (PPL == kStream ? -2 : -1); }
+
+template <int PPL>
 struct IntraRegs {
     uint32_t w[reg_pairs<PPL>() ? PPL : 1];
     uint4 pl[PPL == 8 ? 2 : 1];   // the lane's first two gather chunks
@@ -454,10 +536,10 @@ struct IntraRegs {
     int frag;         // the lane's atom: fragment
     uint32_t anc;     // the lane's fragment: ancestors below the root (LigL::frag_anc)
 };
-template <int PPL, int NBW>
-__device__ inline IntraRegs<PPL, NBW> load_intra(const LigL &L)
+template <int PPL>
+__device__ inline IntraRegs<PPL> load_intra(const LigL &L)
 {
-    IntraRegs<PPL, NBW> pr;
+    IntraRegs<PPL> pr;
     const int lane = lane_id();
     if constexpr (reg_pairs<PPL>()) {
 #pragma unroll
@@ -498,16 +580,27 @@ struct Energy {
 // for k and its first two ancestors (from anc, a per-lane list) are issued
 // together and every lane computes the rotations it needs; deeper ancestors, if
 // any, follow the parent links.
-__device__ inline void frames(const LigL &L, const WaveL &S, uint32_t anc, const float *pose)
+// The pose's position and quaternion come in registers (root), its torsions from
+// LDS.
+struct Root {
+    float4 q;   // (w, x, y, z) in the x, y, z, w slots
+    float3 p;
+    bool check;   // q may have any length
+};
+__device__ inline Root root_of(const float *pose, bool check)
+{
+    return {make_float4(pose[3], pose[4], pose[5], pose[6]), make_float3(pose[0], pose[1], pose[2]), check};
+}
+__device__ inline void frames(const LigL &L, const WaveL &S, uint32_t anc, const float *pose, const Root &root)
 {
     // composed as unit quaternions ((w, x, y, z) in the x, y, z, w slots): a
     // torsion rotation is (cos(theta/2), sin(theta/2) u), products and vector
     // rotations need fewer operations than 3x3 matrices; one matrix per fragment
     // is formed at the end
     const int lane = lane_id();
-    const float4 q0 = quat_normalize(make_float4(pose[3], pose[4], pose[5], pose[6]));
+    const float4 q0 = quat_normalize(root.q, root.check);
     float4 qR = q0;
-    float3 o = make_float3(pose[0], pose[1], pose[2]);
+    float3 o = root.p;
     if (lane > 0 && lane < L.nf) {
         constexpr int kAhead = 3;   // the fragment and two ancestors
         int mm[kAhead];
@@ -530,7 +623,7 @@ __device__ inline void frames(const LigL &L, const WaveL &S, uint32_t anc, const
             if (mm[j] > 0) {
                 const float4 qm = quat_axis(u[j], th[j]);
                 v = f3(off[j]) + quat_rotate(qm, v);
-                qM = quat_mul(qm, qM);
+                qM = j == 1 ? quat_mul<false>(qm, qM) : quat_mul<true>(qm, qM);
             }
         }
         int m = mm[kAhead - 1] > 0 ? (int)(__float_as_uint(u[kAhead - 1].w) & 0xffffu) - 1 : 0;
@@ -538,10 +631,10 @@ __device__ inline void frames(const LigL &L, const WaveL &S, uint32_t anc, const
             const float4 um = L.fu[m];
             const float4 qm = quat_axis(um, pose[6 + m]);
             v = f3(L.foff[m]) + quat_rotate(qm, v);
-            qM = quat_mul(qm, qM);
+            qM = quat_mul<false>(qm, qM);
             m = (int)(__float_as_uint(um.w) & 0xffffu) - 1;
         }
-        qR = quat_normalize(quat_mul(q0, qM));
+        qR = quat_normalize(quat_mul<true>(q0, qM), false);
         o = o + quat_rotate(q0, v);
     }
     if (lane < L.nf) {
@@ -622,30 +715,48 @@ __device__ __forceinline__ void trilinear(const float4 &c000, const float4 &c100
 // Restraint of the adaptive search space on the root position p = pose[0..2]:
 // zero inside a site ball, else wall_slope times the distance to the nearest
 // ball (the lowest index on ties); returns the energy, its gradient in g.
-__device__ inline float site_term(const GridView &G, const float *pose, float wall_slope, float3 &g)
+__device__ inline float site_term(const GridView &G, float3 p, float wall_slope, float3 &g)
 {
     const int lane = lane_id();
-    const float px = pose[0], py = pose[1], pz = pose[2];
-    uint64_t key = ~0ull;   // (squared distance bits, site index), minimised
-    for (int i = lane; i < G.n_site; i += 64) {
-        const float4 q = G.site[i];
-        const float dx = px - q.x, dy = py - q.y, dz = pz - q.z;
-        const uint64_t k = ((uint64_t)__float_as_uint(dx * dx + dy * dy + dz * dz) << 32) | (uint32_t)i;
-        key = k < key ? k : key;
-    }
+    // lane l: squared distances (as bits, which order like them) to points l,
+    // l + 64, ...; its nearest and that point.  The loads are issued together.
+    static_assert(kMaxSite == 256, "four points per lane");
+    const global_f4 *site = (const global_f4 *)G.site;
+    float4 q[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t other = __shfl_xor(key, o, 64);
-        key = other < key ? other : key;
+    for (int c = 0; c < 4; c++) q[c] = as_float4(site[min(lane + 64 * c, G.n_site - 1)]);
+    uint32_t best = ~0u;
+    int near = 0;
+    float3 at = p;
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        const float dx = p.x - q[c].x, dy = p.y - q[c].y, dz = p.z - q[c].z;
+        const uint32_t d2 = __float_as_uint(fmaf(dz, dz, fmaf(dx, dx, dy * dy)));
+        if (lane + 64 * c < G.n_site && d2 < best) {
+            best = d2;
+            near = c;
+            at = f3(q[c]);
+        }
     }
-    const float d = sqrtf(__uint_as_float((uint32_t)(key >> 32)));
+    const uint32_t d2 = wave_min(best);
+    const float d2f = __uint_as_float(d2);
+    const float d = any_odd(d2f) ? sqrtf(d2f) : sqrt_normal(d2f);
     g = make_float3(0.f, 0.f, 0.f);
     if (d <= G.site_r) return 0.f;
-    const float4 q = G.site[(int)(key & 0xffffffffu)];
+    // outside every ball: the lowest index among the nearest
+    const uint32_t first = wave_min(best == d2 ? (uint32_t)(near * 64 + lane) : ~0u);
+    const int l = (int)(first & 63u);
     const float k = wall_slope / d;
-    g = make_float3(k * (px - q.x), k * (py - q.y), k * (pz - q.z));
+    g = make_float3(k * (p.x - read_lane(at.x, l)), k * (p.y - read_lane(at.y, l)), k * (p.z - read_lane(at.z, l)));
     return wall_slope * (d - G.site_r);
 }
+
+// What a lane keeps from an energy evaluation for its gradient: its atom's position
+// and total force (zero from n_atoms on), and the search space's gradient.
+struct LaneState {
+    float3 x, f, g_site;
+    float3 p;   // the root position
+};
 
 // Energy of `pose` (LDS, wave-uniform); every lane returns the same values.  The
 // gradient is left to eval_gradient (a line-search trial needs only the energy
@@ -659,14 +770,14 @@ __device__ inline float site_term(const GridView &G, const float *pose, float wa
 // barrier wave 0 alone gathers them and finishes; the other waves return zeros.
 // Every pair term and every sum is the one a single wave forms, so the result
 // does not depend on `parts`.  All `parts` waves must make the call.
-template <int PPL, int NBW>
-__device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL, NBW> &pr, const GridView &G,
-                              const float *pose, float wall_slope, int part = 0, int parts = 1,
+template <int PPL>
+__device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL> &pr, const GridView &G,
+                              const float *pose, const Root &root, float wall_slope, LaneState &keep, int part = 0, int parts = 1,
                               float4 *pf_shared = nullptr)
 {
     const int lane = lane_id();
 
-    frames(L, S, pr.anc, pose);
+    frames(L, S, pr.anc, pose, root);
 
     // (3) atom coordinates; issue the eight corner gathers of the inter-molecular
     //     term now and consume them after the intra-ligand pairs
@@ -726,10 +837,10 @@ __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL
         c000 = as_float4(m0[0]); c100 = as_float4(m0[1]); c010 = as_float4(m0[sy]); c110 = as_float4(m0[sy + 1]);
         c001 = as_float4(m0[sz]); c101 = as_float4(m0[sz + 1]);
         c011 = as_float4(m0[sz + sy]); c111 = as_float4(m0[sz + sy + 1]);
-        // atom lists: the corners are used at once, so that their registers are
-        // free for the intra-ligand loop (the launches that use this layout run
-        // several waves per SIMD, which hide the wait)
-        if constexpr (PPL == 0)
+        // atom lists and the pair stream: the corners are used at once, so that
+        // their registers are free for the intra-ligand loop (the launches that use
+        // these layouts run several waves per SIMD, which hide the wait)
+        if constexpr (PPL <= 0)
             trilinear(c000, c100, c010, c110, c001, c101, c011, c111, px, py, pz, clx, cly, clz, wg, w_atom, e_atom,
                       f);
     }
@@ -798,6 +909,98 @@ __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL
                 group(g, pw);
             }
         }
+    } else if constexpr (PPL == kStream) {
+        // pair stream: chunks of up to 127 pairs in the order of the lists, each
+        // stored as two slots (one in a short last chunk) of 64, then added from
+        // the lane's list of the chunk (words of four entries: chunk index | sign).
+        // The last index of a chunk's last slot is no pair: it stores zeros, which
+        // list padding adds.  Slots without class pairs skip the class terms.
+        // A chunk's words are loaded while the chunk before it is worked on, its two
+        // slots are evaluated together, and eight entries are in flight at a time.
+        const uint32_t *pairs = L.pair + lane, *list = L.slist + lane;
+        uint32_t cw0 = L.chunk_words[0], cw1 = L.chunk_words[1], plain = L.chunk_plain;
+        struct Words {
+            uint32_t pw[2], q[2];
+        };
+        // (what lies past a short chunk's words is read, inside the workgroup's LDS,
+        // and not used)
+        auto load_words = [&]() {
+            Words w;
+            w.pw[0] = pairs[0];
+            w.pw[1] = pairs[64];
+            w.q[0] = list[0];
+            w.q[1] = list[64];
+            return w;
+        };
+        auto slot = [&](uint32_t pw, const float4 &xi, const float4 &xj, auto plain_slot) {
+            const float dx = xi.x - xj.x, dy = xi.y - xj.y, dz = xi.z - xj.z;
+            const float r2 = pair_r2(dx, dy, dz);
+            const float2 es = pair_term<decltype(plain_slot)::value>(r2, xi.w + xj.w, pw >> 16);
+            const bool in = (int)pw >= 0 && r2 < kCutoff2;
+            const float ep = in ? es.x : 0.f, sp = in ? es.y : 0.f;
+            return make_float4(mul_rounded(sp, dx), mul_rounded(sp, dy), mul_rounded(sp, dz), ep);
+        };
+        auto gather = [&](const uint32_t (&q)[2], auto count) {
+            constexpr int N = decltype(count)::value;
+            float4 v[4 * N];
+#pragma unroll
+            for (int t = 0; t < 4 * N; t++) v[t] = S.pf[(q[t >> 2] >> (8 * (t & 3))) & 127u];
+#pragma unroll
+            for (int t = 0; t < 4 * N; t++) {
+                // +1 as the pair's first atom, -1 as its second (sg * v is exact, so
+                // the sum rounds once)
+                const float sg = __uint_as_float(((q[t >> 2] << (24 - 8 * (t & 3))) & 0x80000000u) | 0x3f800000u);
+                fnb.x = fmaf(sg, v[t].x, fnb.x);
+                fnb.y = fmaf(sg, v[t].y, fnb.y);
+                fnb.z = fmaf(sg, v[t].z, fnb.z);
+                e_lane = fmaf(__builtin_amdgcn_fmed3f(sg, 0.f, 1.f), v[t].w, e_lane);
+            }
+        };
+        Words w{};
+        if (L.n_chunks > 0) w = load_words();
+#pragma unroll 1
+        for (int c = 0; c < L.n_chunks; c++) {
+            const int slots = L.np - kStreamPairs * c > 63 ? 2 : 1, words = (int)(cw0 & 15u);
+            pairs += 64 * slots;
+            list += 64 * words;
+            Words next = w;
+            if (c + 1 < L.n_chunks) next = load_words();
+            const float4 xi = S.xyz[w.pw[0] & 255u], xj = S.xyz[(w.pw[0] >> 8) & 255u];
+            if (slots == 2) {
+                const float4 yi = S.xyz[w.pw[1] & 255u], yj = S.xyz[(w.pw[1] >> 8) & 255u];
+                const std::true_type P;
+                const std::false_type C;
+                float4 u, v;
+                if ((plain & 3u) == 2u) {
+                    u = slot(w.pw[0], xi, xj, P);
+                    v = slot(w.pw[1], yi, yj, P);
+                } else if ((plain & 3u) == 1u) {
+                    u = slot(w.pw[0], xi, xj, P);
+                    v = slot(w.pw[1], yi, yj, C);
+                } else {
+                    u = slot(w.pw[0], xi, xj, C);
+                    v = slot(w.pw[1], yi, yj, C);
+                }
+                S.pf[lane] = u;
+                S.pf[64 + lane] = v;
+            } else {
+                S.pf[lane] = slot(w.pw[0], xi, xj, std::false_type());
+            }
+            wave_sync();
+            if (words >= 2)
+                gather(w.q, std::integral_constant<int, 2>());
+            else if (words == 1)
+                gather(w.q, std::integral_constant<int, 1>());
+            for (int m = 2; m < words; m++) {
+                const uint32_t q[2] = {list[64 * (m - words)], 0u};
+                gather(q, std::integral_constant<int, 1>());
+            }
+            wave_sync();
+            w = next;
+            cw0 = (cw0 >> 4) | (cw1 << 28);
+            cw1 >>= 4;
+            plain >>= 2;
+        }
     } else {
         const int a = L.lanes_per_atom == 2 ? (lane & 31) : lane;
         if (a < L.na) {
@@ -849,16 +1052,6 @@ __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL
         if (lane < L.na && part == 0)
             trilinear(c000, c100, c010, c110, c001, c101, c011, c111, px, py, pz, clx, cly, clz, wg, w_atom, e_atom,
                       f);
-    }
-    float e_inter = wave_sum(e_atom);
-    float wall = wave_sum(w_atom);
-    // adaptive search space: outside every site ball the root position pays
-    // wall_slope per A of its distance to the nearest ball
-    if (G.n_site > 0) {
-        float3 g_site;
-        const float e = site_term(G, pose, wall_slope, g_site);
-        e_inter += e;
-        wall += e;
     }
     if (parts > 1) {
         __syncthreads();   // every part's pair terms are stored
@@ -915,8 +1108,21 @@ __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL
         fp.z += other_half(fp.z);
     }
     if (lane < L.na) f = f + fp;
+    float e_inter = wave_sum(e_atom);
     const float e_intra = wave_sum(e_lane);
-    S.af[lane] = make_float4(f.x, f.y, f.z, 0.f);
+    // most poses have no atom outside the box
+    float wall = __builtin_amdgcn_ballot_w64(w_atom != 0.f) != 0 ? wave_sum(w_atom) : 0.f;
+    // adaptive search space: outside every site ball the root position pays
+    // wall_slope per A of its distance to the nearest ball
+    keep.g_site = make_float3(0.f, 0.f, 0.f);
+    if (G.n_site > 0) {
+        const float e = site_term(G, root.p, wall_slope, keep.g_site);
+        e_inter += e;
+        wall += e;
+    }
+    keep.p = root.p;
+    keep.x = x;
+    keep.f = f;
     Energy out;
     out.inter = e_inter;
     out.intra = e_intra;
@@ -928,16 +1134,10 @@ __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL
 // Gradient in the tangent coordinates, written to grad[0..D) (LDS), of the pose
 // whose energy eval_energy last took on this wave (same `pose`; the wave's
 // scratch still holds that evaluation).
-template <int PPL, int NBW>
-__device__ void eval_gradient(const LigL &L, const WaveL &S, const IntraRegs<PPL, NBW> &pr, const GridView &G,
-                              const float *pose, float wall_slope, float *grad)
+__device__ inline void eval_gradient(const LigL &L, const WaveL &S, const LaneState &keep, float *grad)
 {
     const int lane = lane_id();
-    const float4 xl = S.xyz[lane < L.na ? lane : 0];
-    const float3 x = lane < L.na ? f3(xl) : make_float3(0.f, 0.f, 0.f);
-    const float3 f = f3(S.af[lane]);   // the atom's total force from the energy half
-    float3 g_site = make_float3(0.f, 0.f, 0.f);
-    if (G.n_site > 0) site_term(G, pose, wall_slope, g_site);
+    const float3 x = keep.x, f = keep.f, g_site = keep.g_site;
 
     // (7) gradient in the tangent coordinates.  With the root origin p, atom
     //     forces f_a and t_a = (x_a - p) x f_a, summed as lane prefix sums in
@@ -947,7 +1147,7 @@ __device__ void eval_gradient(const LigL &L, const WaveL &S, const IntraRegs<PPL
     //     about o_k is T_sub(k) - (o_k - p) x F_sub(k).
     //     dE/dp = F_sub(0), dE/dw = T_sub(0), dE/dtheta_k = u_k . torque about o_k.
     //     Fragment data are loaded first so that their latency hides under the scan.
-    const float3 o0 = make_float3(pose[0], pose[1], pose[2]);
+    const float3 o0 = keep.p;
     uint32_t range = 0u;
     float4 okv = make_float4(0.f, 0.f, 0.f, 0.f), uref = okv, rr0 = okv, rr1 = okv, rr2 = okv;
     if (lane < L.nf) {
@@ -994,30 +1194,36 @@ __device__ void eval_gradient(const LigL &L, const WaveL &S, const IntraRegs<PPL
 }
 
 // Energy and gradient of `pose`.
-template <int PPL, int NBW>
-__device__ Energy eval_pose(const LigL &L, const WaveL &S, const IntraRegs<PPL, NBW> &pr, const GridView &G,
+template <int PPL>
+__device__ Energy eval_pose(const LigL &L, const WaveL &S, const IntraRegs<PPL> &pr, const GridView &G,
                             const float *pose, float *grad, float wall_slope)
 {
-    const Energy e = eval_energy(L, S, pr, G, pose, wall_slope);
-    eval_gradient(L, S, pr, G, pose, wall_slope, grad);
+    LaneState keep;
+    const Energy e = eval_energy(L, S, pr, G, pose, root_of(pose, true), wall_slope, keep);
+    eval_gradient(L, S, keep, grad);
     return e;
 }
 
 // trial = x (+) alpha * dir   (p += a dp; q <- normalise(quat(a w) q); theta <- wrap(theta + a dtheta)).
 // Lane l writes coordinate l; the three kinds are selected per lane, no branch.
-__device__ inline void pose_step(const LigL &L, const float *x, float alpha, const float *dir, float *out)
+// The torsions are stored first, so that their trip through LDS passes under the
+// quaternion's arithmetic; position and quaternion are returned too.
+__device__ inline Root pose_step(const LigL &L, const float *x, float alpha, const float *dir, float *out, bool check)
 {
     const int lane = lane_id();
-    const float4 dq = quat_of_rotvec(alpha * dir[3], alpha * dir[4], alpha * dir[5]);
-    const float4 q = quat_normalize(quat_mul(dq, make_float4(x[3], x[4], x[5], x[6])));
     const bool tors = lane >= 7 && lane < L.nx;
     const int xi = lane < L.nx ? lane : 0, di = lane < 3 ? lane : (tors ? lane - 1 : 0);
-    const float lin = x[xi] + alpha * dir[di];
-    const float qc = lane == 3 ? q.x : (lane == 4 ? q.y : (lane == 5 ? q.z : q.w));
+    const float lin = fmaf(alpha, dir[di], x[xi]);
     const float th = wrap_angle(tors ? lin : 0.f);
-    const float v = lane < 3 ? lin : (lane < 7 ? qc : th);
-    if (lane < L.nx) out[lane] = v;
+    if (lane < 3 || tors) out[lane] = lane < 3 ? lin : th;
+    Root r;
+    r.p = make_float3(fmaf(alpha, dir[0], x[0]), fmaf(alpha, dir[1], x[1]), fmaf(alpha, dir[2], x[2]));
+    const float4 dq = quat_of_rotvec(alpha * dir[3], alpha * dir[4], alpha * dir[5]);
+    r.q = quat_normalize(quat_mul<false>(dq, make_float4(x[3], x[4], x[5], x[6])), check);
+    r.check = false;
+    if (lane >= 3 && lane < 7) out[lane] = lane == 3 ? r.q.x : (lane == 4 ? r.q.y : (lane == 5 ? r.q.z : r.q.w));
     wave_sync();
+    return r;
 }
 
 __device__ inline void copy_pose(const LigL &L, const float *src, float *dst)
@@ -1081,7 +1287,7 @@ __device__ inline float bfgs_step(const ChainL &C, int D, bool upd, float ys, fl
         if (lane < 4 * NQ) C.Hy[lane] = hy;
         const float yHy = wave_sum(yl * hy);
         wave_sync();
-        const float rho = 1.f / ys;
+        const float rho = any_odd(ys) ? 1.f / ys : rcp_normal(ys);
         const float aa = rho * (1.f + rho * yHy) * sl, bb = rho * sl, cc = rho * hy;
 #pragma unroll
         for (int q = 0; q < NQ; q++) {
@@ -1136,7 +1342,7 @@ __device__ inline float bfgs_step_any(const ChainL &C, int D, int nq, bool upd, 
         if (lane < 4 * nq) C.Hy[lane] = hy;
         const float yHy = wave_sum(yl * hy);
         wave_sync();
-        const float rho = 1.f / ys;
+        const float rho = any_odd(ys) ? 1.f / ys : rcp_normal(ys);
         const float aa = rho * (1.f + rho * yHy) * sl, bb = rho * sl, cc = rho * hy;
         if (own) {
             for (int q = 0; q < nq; q++) {
@@ -1169,6 +1375,17 @@ __device__ inline float bfgs_step_any(const ChainL &C, int D, int nq, bool upd, 
     return wave_sum(pl * gl);
 }
 
+// Several waves of a workgroup serve one chain, or (pair stream) each wave its
+// own: then there is nothing to wait for but the wave's own LDS traffic.
+template <bool SOLO>
+__device__ __forceinline__ void chain_sync()
+{
+    if constexpr (SOLO)
+        wave_sync();
+    else
+        __syncthreads();
+}
+
 // The Barzilai-Borwein gradient method (the paper's local optimiser, Section 2,
 // second modification) on the chain's pose x (LDS, in place), run by all W waves
 // of the workgroup: iters steps x <- x (+) a p with p = -g and a = s.s / s.y
@@ -1180,12 +1397,13 @@ __device__ inline float bfgs_step_any(const ChainL &C, int D, int nq, bool upd, 
 // (lane l: pose coordinate l, gradient component l), so a step costs no LDS
 // round trip besides the gradient's; the other waves form the same trial poses
 // from the gradient and step length wave 0 leaves in LDS at each round's end.
-template <int PPL, int NBW>
+template <int PPL>
 __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_base, const ChainL &C,
-                               const IntraRegs<PPL, NBW> &pr, const GridView &G, const SearchParams &P, float *x,
+                               const IntraRegs<PPL> &pr, const GridView &G, const SearchParams &P, float *x,
                                int &evals, int W)
 {
-    const int lane = lane_id(), w = wave_id(), D = L.D, nx = L.nx;
+    constexpr bool SOLO = PPL == kStream;
+    const int lane = lane_id(), w = SOLO ? 0 : wave_id(), D = L.D, nx = L.nx;
     const WaveL S = make_wave(wave_base + w * lay.wave_words, lay);
     const bool split = PPL > 0 && W > 1;
     float4 *const pf0 = make_wave(wave_base, lay).pf;
@@ -1197,6 +1415,7 @@ __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_bas
         Energy Eb;
         for (int it = 0; it <= P.bb_iters; it++) {
             float tr = xr;
+            Root root;
             if (it > 0) {
                 // trial = x (+) a p, p = -g: position and torsions lane by lane
                 // (torsion lane l takes gradient component l - 1), the rotation as
@@ -1205,25 +1424,33 @@ __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_bas
                 const float gsh = dpp<0x138>(gr);   // wave_shr:1, lane l gets lane l - 1
                 const float4 dq = quat_of_rotvec(a * -read_lane(gr, 3), a * -read_lane(gr, 4), a * -read_lane(gr, 5));
                 const float4 q = quat_normalize(
-                    quat_mul(dq, make_float4(read_lane(xr, 3), read_lane(xr, 4), read_lane(xr, 5), read_lane(xr, 6))));
+                    quat_mul<false>(dq, make_float4(read_lane(xr, 3), read_lane(xr, 4), read_lane(xr, 5), read_lane(xr, 6))),
+                    C.raw);
                 const bool tors = lane >= 7 && lane < nx;
                 const float lin = xr + a * -(lane < 3 ? gr : (tors ? gsh : 0.f));
                 const float qc = lane == 3 ? q.x : (lane == 4 ? q.y : (lane == 5 ? q.z : q.w));
                 const float th = wrap_angle(tors ? lin : 0.f);
                 tr = lane < 3 ? lin : (lane < 7 ? qc : th);
+                root.q = q;
+            } else {
+                root.q = make_float4(read_lane(xr, 3), read_lane(xr, 4), read_lane(xr, 5), read_lane(xr, 6));
             }
+            root.p = make_float3(read_lane(tr, 0), read_lane(tr, 1), read_lane(tr, 2));
+            root.check = C.raw && it == 0;
             if (lane < nx) S.trial[lane] = tr;
             wave_sync();
-            const Energy e = eval_energy(L, S, pr, G, S.trial, P.wall_slope, split ? w : 0, split ? W : 1, pf0);
+            LaneState keep;
+            const Energy e = eval_energy(L, S, pr, G, S.trial, root, P.wall_slope, keep, split ? w : 0, split ? W : 1, pf0);
             evals++;
             if (w == 0) {
-                eval_gradient(L, S, pr, G, S.trial, P.wall_slope, S.gt);
+                eval_gradient(L, S, keep, S.gt);
                 const float gn = lane < D ? S.gt[lane] : 0.f;
                 if (it > 0) {
                     // s = a p, y = g_new - g; the next length s.s / s.y when s.y > 0
                     const float sl = lane < D ? a * -gr : 0.f, yl = lane < D ? gn - gr : 0.f;
                     const float sy = wave_sum(sl * yl), ss = wave_sum(sl * sl);
-                    a = sy > 0.f ? fminf(ss / sy, P.bb_step_max) : P.bb_step0;
+                    const float bb = any_odd(ss) || any_odd(sy) ? ss / sy : div_normal(ss, sy);
+                    a = sy > 0.f ? fminf(bb, P.bb_step_max) : P.bb_step0;
                     if (e.total < Eb.total) {
                         Eb = e;
                         xbr = tr;
@@ -1243,7 +1470,7 @@ __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_bas
             }
             xr = tr;
             if (split && it < P.bb_iters) {
-                __syncthreads();   // wave 0's gradient and step length are stored
+                chain_sync<SOLO>();   // wave 0's gradient and step length are stored
                 if (w != 0) {
                     gr = lane < D ? C.g[(it & 1) * (C.s - C.g) + lane] : 0.f;
                     a = C.misc[kMiscBBa + (it & 1)];
@@ -1257,7 +1484,7 @@ __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_bas
     } else {
         evals += P.bb_iters + 1;   // the count wave 0 makes
     }
-    __syncthreads();
+    chain_sync<SOLO>();
     return get_energy(C.et);
 }
 
@@ -1271,85 +1498,87 @@ __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_bas
 // kept in LDS; wave 0 does this for the start point).  `evals` counts the
 // evaluations the one-at-a-time search makes (speculative trials past the
 // accepted one are not counted).  The final gradient is left in C.g.
-template <int PPL, int NBW>
+template <int PPL>
 __device__ Energy local_opt_group(const LigL &L, const Layout &lay, float *wave_base, const ChainL &C,
-                                  const IntraRegs<PPL, NBW> &pr, const GridView &G, const SearchParams &P, float *x,
+                                  const IntraRegs<PPL> &pr, const GridView &G, const SearchParams &P, float *x,
                                   int &evals, int W)
 {
-    if (P.optimizer == kOptBB) return local_opt_bb(L, lay, wave_base, C, pr, G, P, x, evals, W);
-    const int lane = lane_id(), w = wave_id(), D = L.D;
+    constexpr bool SOLO = PPL == kStream;
+    const int lane = lane_id(), w = SOLO ? 0 : wave_id(), D = L.D;
     const WaveL S = make_wave(wave_base + w * lay.wave_words, lay);
-    Energy Ex;
+    float Ex = 0.f;       // energy of the current iterate (its parts: C.misc + kMiscE)
     float gp = 0.f;
     int it = 0;           // iterations done
     int t0 = -1;          // first line-search trial of this round; -1: the start evaluation
-    float alpha0 = 1.f;   // alpha of the round's first trial
     const int Dp = lay.Dp;
     float s_l = 0.f, y_l = 0.f, g_l = 0.f, ys = 0.f;   // wave 0: this iteration's s, y, new g; s.y
+    // lane l: alpha of the round's trial l & 3 (shrink^t by repeated products)
+    const float sh = P.ls_shrink, sh2 = sh * sh;
+    const int v = lane & 3;
+    const float alpha_first = v == 0 ? 1.f : v == 1 ? sh : v == 2 ? sh2 : sh2 * sh;
+    float alpha = alpha_first;
     // Every evaluation of the local optimisation goes through the one energy call
     // and the one gradient call below (the start pose by wave 0, then one
     // line-search trial per wave per round), so the kernel holds a single copy
     // of the evaluation code.
     for (;;) {
         bool active;
+        LaneState keep;
+        Energy own;
+        Root root;
         if (t0 < 0) {
             active = w == 0;
-            if (active && lane < L.nx) S.trial[lane] = x[lane];
+            if (active) {
+                if (lane < L.nx) S.trial[lane] = x[lane];
+                root = root_of(x, C.raw);
+                wave_sync();
+            }
         } else {
             active = t0 + w < P.ls_trials;
-            if (active) {
-                float alpha = alpha0;
-                for (int q = 0; q < w; q++) alpha *= P.ls_shrink;
-                pose_step(L, x, alpha, C.p, S.trial);
-            }
+            if (active) root = pose_step(L, x, read_lane(alpha, w), C.p, S.trial, C.raw);
         }
         if (active) {
-            wave_sync();
-            put_energy(C.et + 4 * w, eval_energy(L, S, pr, G, S.trial, P.wall_slope));
+            own = eval_energy(L, S, pr, G, S.trial, root, P.wall_slope, keep);
+            if (lane == 0) C.et[w] = own.total;
         }
-        __syncthreads();
+        chain_sync<SOLO>();
         // the one evaluation of this round whose gradient is needed: wave 0's for
         // the start point; in a line search, the accepted trial's (decided alike
         // in every wave, so the barrier below is taken by all or none), and none
         // when every trial is rejected
-        int gw = 0, acc_slot = -1;
+        int gw = 0;
         float alpha_acc = 0.f;
+        const float total = C.et[v];   // lane l: the energy of trial l & 3
         if (t0 >= 0) {
-            float a = alpha0;
-            float4 et4[kMaxWaves];
-#pragma unroll
-            for (int q = 0; q < kMaxWaves; q++) et4[q] = reinterpret_cast<const float4 *>(C.et)[q];
             // Armijo test on the energy change, E(trial) - E(x) <= c1 a g.p, which
             // must also be a decrease of at least ls_min_decrease.  The float
             // difference of two nearby energies is exact, whereas forming
             // E(x) + c1 a g.p would round the tiny term away near convergence
-            // and accept trials that do not lower the energy at all.
-            int v = 0;
-#pragma unroll
-            for (; v < kMaxWaves; v++) {
-                if (v >= W || t0 + v >= P.ls_trials) break;
-                if (et4[v].x - Ex.total <= fminf(P.armijo_c1 * a * gp, -P.ls_min_decrease)) {
-                    acc_slot = v;
-                    alpha_acc = a;
-                    break;
-                }
-                a *= P.ls_shrink;
-            }
-            evals += acc_slot >= 0 ? acc_slot + 1 : v;
-            if (acc_slot < 0) {
+            // and accept trials that do not lower the energy at all.  Lane l tests
+            // trial l; the first that passes is taken.
+            const int n = min(W, P.ls_trials - t0);
+            const bool pass = lane < n && total - Ex <= fminf(P.armijo_c1 * alpha * gp, -P.ls_min_decrease);
+            const uint64_t passed = __builtin_amdgcn_ballot_w64(pass);
+            if (passed == 0) {
+                evals += n;
                 if (t0 + W >= P.ls_trials) break;   // every trial rejected: stop at x
-                alpha0 = a;
+                for (int q = 0; q < W; q++) alpha *= sh;
                 t0 += W;
-                __syncthreads();   // this round's energies are read before the next round writes
+                chain_sync<SOLO>();   // this round's energies are read before the next round writes
                 continue;
             }
-            gw = acc_slot;
+            gw = __builtin_ctzll(passed);
+            alpha_acc = read_lane(alpha, gw);
+            evals += gw + 1;
         }
         // that wave also takes the optimiser's step below, so no other wave waits
         // for the gradient
-        if (w == gw) eval_gradient(L, S, pr, G, S.trial, P.wall_slope, S.gt);
+        if (w == gw) {
+            eval_gradient(L, S, keep, S.gt);
+            put_energy(C.misc + kMiscE, own);
+        }
+        Ex = read_lane(total, gw);
         if (t0 < 0) {
-            Ex = get_energy(C.et);
             evals++;
             if (w == 0 && lane < Dp) {
                 g_l = lane < D ? S.gt[lane] : 0.f;
@@ -1364,8 +1593,7 @@ __device__ Energy local_opt_group(const LigL &L, const Layout &lay, float *wave_
                 }
             }
         } else {
-            const Energy Et = get_energy(C.et + 4 * acc_slot);
-            if (w == acc_slot) {
+            if (w == gw) {
                 // the accepted trial's wave: s = alpha p, y = g_new - g, x <- trial
                 s_l = 0.f;
                 y_l = 0.f;
@@ -1384,7 +1612,6 @@ __device__ Energy local_opt_group(const LigL &L, const Layout &lay, float *wave_
                 if (lane < L.nx) x[lane] = S.trial[lane];
                 ys = wave_sum(s_l * y_l);
             }
-            Ex = Et;
             it++;
         }
         if (it >= P.bfgs_iters) break;
@@ -1409,13 +1636,26 @@ __device__ Energy local_opt_group(const LigL &L, const Layout &lay, float *wave_
             }
             if (lane == 0) C.misc[kMiscGp] = g_p;
         }
-        __syncthreads();
+        chain_sync<SOLO>();
         gp = C.misc[kMiscGp];
         t0 = 0;
-        alpha0 = 1.f;
+        alpha = alpha_first;
     }
-    __syncthreads();
-    return Ex;
+    chain_sync<SOLO>();
+    return get_energy(C.misc + kMiscE);
+}
+
+// The kernels are compiled per optimiser: each then holds one evaluation's code
+// and only its own optimiser's registers.
+template <int PPL, bool BB>
+__device__ inline Energy local_opt(const LigL &L, const Layout &lay, float *wave_base, const ChainL &C,
+                                   const IntraRegs<PPL> &pr, const GridView &G, const SearchParams &P, float *x,
+                                   int &evals, int W)
+{
+    if constexpr (BB)
+        return local_opt_bb(L, lay, wave_base, C, pr, G, P, x, evals, W);
+    else
+        return local_opt_group(L, lay, wave_base, C, pr, G, P, x, evals, W);
 }
 
 // Stage the ligand blob into LDS (whole workgroup).
@@ -1428,7 +1668,7 @@ __device__ inline void stage_blob(const uint32_t *blob, int words, uint32_t *lds
 // ---------------------------------------------------------------- kernels
 
 // One pose per wave (independent waves).
-template <int PPL, int NBW>
+template <int PPL>
 __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ blob, int blob_words, GridView G, SearchParams P,
                                                    const float *poses, int n, float *energy, float *grad, float *xyz)
 {
@@ -1436,7 +1676,7 @@ __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ 
     uint32_t *lds = reinterpret_cast<uint32_t *>(lds4);
     stage_blob(blob, blob_words, lds);
     const LigL L = make_lig(lds, blob);
-    const Layout lay = make_layout(L.na, L.nf, PPL > 0 ? L.np : -1, L.D, L.nx);
+    const Layout lay = make_layout(L.na, L.nf, layout_pairs<PPL>(L.np), L.D, L.nx);
     const WaveL S = make_wave(reinterpret_cast<float *>(lds) + blob_words + wave_id() * lay.wave_words, lay);
     const int idx = blockIdx.x * (blockDim.x >> 6) + wave_id();
     if (idx >= n) return;
@@ -1446,7 +1686,7 @@ __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ 
     }
     if (lane < L.nx) S.trial[lane] = poses[(long)idx * L.nx + lane];
     wave_sync();
-    const IntraRegs<PPL, NBW> pr = load_intra<PPL, NBW>(L);
+    const IntraRegs<PPL> pr = load_intra<PPL>(L);
     const Energy E = eval_pose(L, S, pr, G, S.trial, S.gt, P.wall_slope);
     if (lane == 0) {
         energy[4 * idx + 0] = E.total;
@@ -1462,9 +1702,9 @@ __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ 
     }
 }
 
-// One pose per workgroup of W waves.
-template <int PPL, int NBW>
-__global__ __launch_bounds__(256) void local_opt_kernel(const uint32_t *blob, int blob_words, GridView G,
+// One pose per workgroup of W waves, or (pair stream) one per wave.
+template <int PPL, bool BB>
+__global__ __launch_bounds__(256, kMinWaves<PPL>) void local_opt_kernel(const uint32_t *blob, int blob_words, GridView G,
                                                         SearchParams P, const float *poses_in, int n,
                                                         float *poses_out, float *energy, int *evals_out)
 {
@@ -1472,22 +1712,25 @@ __global__ __launch_bounds__(256) void local_opt_kernel(const uint32_t *blob, in
     uint32_t *lds = reinterpret_cast<uint32_t *>(lds4);
     stage_blob(blob, blob_words, lds);
     const LigL L = make_lig(lds, blob);
-    const Layout lay = make_layout(L.na, L.nf, PPL > 0 ? L.np : -1, L.D, L.nx);
+    const Layout lay = make_layout(L.na, L.nf, layout_pairs<PPL>(L.np), L.D, L.nx);
+    constexpr bool SOLO = PPL == kStream;
     float *cbase = reinterpret_cast<float *>(lds) + blob_words;
-    const ChainL C = make_chain(cbase, lay);
+    if (SOLO) cbase += wave_id() * (lay.chain_words + lay.wave_words);
+    const ChainL C = make_chain(cbase, lay, true);
     float *wbase = cbase + lay.chain_words;
-    const int W = (int)(blockDim.x >> 6);
-    const int idx = blockIdx.x;
-    const int lane = lane_id(), w = wave_id();
+    const int W = SOLO ? 1 : (int)(blockDim.x >> 6);
+    const int idx = SOLO ? (int)(blockIdx.x * (blockDim.x >> 6)) + wave_id() : (int)blockIdx.x;
+    if (SOLO && idx >= n) return;
+    const int lane = lane_id(), w = SOLO ? 0 : wave_id();
     if (PPL > 0 && lane == 0) {
         const WaveL S0 = make_wave(wbase + w * lay.wave_words, lay);
         S0.pf[L.np] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if (w == 0 && lane < L.nx) C.cur[lane] = poses_in[(long)idx * L.nx + lane];
-    __syncthreads();
+    chain_sync<SOLO>();
     int evals = 0;
-    const IntraRegs<PPL, NBW> pr = load_intra<PPL, NBW>(L);
-    const Energy E = local_opt_group(L, lay, wbase, C, pr, G, P, C.cur, evals, W);
+    const IntraRegs<PPL> pr = load_intra<PPL>(L);
+    const Energy E = local_opt<PPL, BB>(L, lay, wbase, C, pr, G, P, C.cur, evals, W);
     if (w == 0) {
         if (lane < L.nx) poses_out[(long)idx * L.nx + lane] = C.cur[lane];
         if (lane == 0) {
@@ -1500,31 +1743,42 @@ __global__ __launch_bounds__(256) void local_opt_kernel(const uint32_t *blob, in
     }
 }
 
-// One Monte Carlo chain per workgroup of W waves, resumable: a task's chain
+// One Monte Carlo chain per workgroup of W waves, or (pair stream) one per wave of
+// a workgroup whose chains share a ligand, resumable: a task's chain
 // starts from its initial pose (position uniform in the box, Shoemake
 // orientation, uniform torsions) or from its saved state, runs up to tick_steps
 // steps of mutate -> BFGS -> Metropolis, keeping the lowest accepted energy, and
 // saves its state.  A chain that reaches its last step writes its record and the
 // coordinates of its best pose (for ranking).
-template <int PPL, int NBW>
-__global__ __launch_bounds__(256) void tick_kernel(const uint32_t *arena, const ChainTask *tasks, const GridView *grids,
+template <int PPL, bool BB>
+__global__ __launch_bounds__(256, kMinWaves<PPL>) void tick_kernel(const uint32_t *arena, const ChainTask *tasks, const GridView *grids,
                                                    SearchParams P, int tick_steps, int init, float *state,
                                                    float *records, float4 *best_xyz)
 {
-    const ChainTask t = tasks[blockIdx.x];
-    if (t.n_steps < 0) return;
+    constexpr bool SOLO = PPL == kStream;
+    int first = (int)blockIdx.x;
+    bool idle = false;
+    if constexpr (SOLO) {
+        const int count = tasks[blockIdx.x].wg_count;
+        first = tasks[blockIdx.x].wg_first + min(wave_id(), count - 1);
+        idle = wave_id() >= count;
+    }
+    const ChainTask t = tasks[first];
+    if (!SOLO && t.n_steps < 0) return;
     extern __shared__ float4 lds4[];
     uint32_t *lds = reinterpret_cast<uint32_t *>(lds4);
     stage_blob(arena + t.blob_off, (int)t.blob_words, lds);
+    if (SOLO && (idle || t.n_steps < 0)) return;   // after the workgroup's only barrier
     const GridView G = grids[t.grid];
     const LigL L = make_lig(lds, arena + t.blob_off);
-    const Layout lay = make_layout(L.na, L.nf, PPL > 0 ? L.np : -1, L.D, L.nx);
+    const Layout lay = make_layout(L.na, L.nf, layout_pairs<PPL>(L.np), L.D, L.nx);
     float *cbase = reinterpret_cast<float *>(lds) + t.blob_words;
-    const ChainL C = make_chain(cbase, lay);
+    if (SOLO) cbase += wave_id() * (lay.chain_words + lay.wave_words);
+    const ChainL C = make_chain(cbase, lay, false);
     float *wbase = cbase + lay.chain_words;
-    const int W = (int)(blockDim.x >> 6);
-    const IntraRegs<PPL, NBW> pr = load_intra<PPL, NBW>(L);
-    const int lane = lane_id(), w = wave_id();
+    const int W = SOLO ? 1 : (int)(blockDim.x >> 6);
+    const IntraRegs<PPL> pr = load_intra<PPL>(L);
+    const int lane = lane_id(), w = SOLO ? 0 : wave_id();
     const uint32_t c = t.chain;
     const uint64_t seed = (uint64_t)t.seed_lo | ((uint64_t)t.seed_hi << 32);
     float *st = state + (long)t.slot * kStWords;
@@ -1603,7 +1857,7 @@ __global__ __launch_bounds__(256) void tick_kernel(const uint32_t *arena, const 
         Eb = get_energy(st + kStEb);
         step = sti[kStStep]; evals = sti[kStEvals]; accepted = sti[kStAcc]; lopts = sti[kStLopt];
     }
-    __syncthreads();
+    chain_sync<SOLO>();
 
     const float rot_amp = L.rg > 0.f ? P.trans_amp / L.rg : 0.f;
     const int s_end = min(t.n_steps, step + tick_steps);
@@ -1620,14 +1874,15 @@ __global__ __launch_bounds__(256) void tick_kernel(const uint32_t *arena, const 
             } else if (which == 1) {
                 const float3 v = ball(u1, u2, u3);
                 const float4 dq = quat_of_rotvec(rot_amp * v.x, rot_amp * v.y, rot_amp * v.z);
-                const float4 q = quat_normalize(quat_mul(dq, make_float4(C.cur[3], C.cur[4], C.cur[5], C.cur[6])));
+                const float4 q =
+                    quat_normalize(quat_mul<true>(dq, make_float4(C.cur[3], C.cur[4], C.cur[5], C.cur[6])), false);
                 if (lane >= 3 && lane < 7) C.cand[lane] = lane == 3 ? q.x : (lane == 4 ? q.y : (lane == 5 ? q.z : q.w));
             } else {
                 if (lane == 7 + which - 2) C.cand[lane] = -kPi + 2 * kPi * u1;
             }
         }
-        __syncthreads();
-        const Energy Ec = local_opt_group(L, lay, wbase, C, pr, G, P, C.cand, evals, W);
+        chain_sync<SOLO>();
+        const Energy Ec = local_opt<PPL, BB>(L, lay, wbase, C, pr, G, P, C.cand, evals, W);
         lopts++;
         bool take = true;
         if (step > 0) {
@@ -1663,7 +1918,7 @@ __global__ __launch_bounds__(256) void tick_kernel(const uint32_t *arena, const 
     if (step < t.n_steps) return;
     // finished: record, and the coordinates of the best pose for RMSD clustering
     const WaveL S = make_wave(wbase, lay);
-    frames(L, S, pr.anc, C.best);
+    frames(L, S, pr.anc, C.best, root_of(C.best, false));
     float *rec = records + (long)t.slot * kRecWords;
     if (lane < L.nx) rec[kRecPose + lane] = C.best[lane];
     if (lane == 0) {
@@ -1756,28 +2011,34 @@ inline int pick_eval_waves(size_t blob_bytes, size_t wave_bytes)
 }  // namespace
 
 namespace {
-int pf_pairs(const LigHeader &h) { return h.intra_form == kFormAtoms ? -1 : h.n_pairs; }
+int pf_pairs(const LigHeader &h)
+{
+    return h.intra_form == kFormAtoms ? -1 : h.intra_form == kFormStream ? -2 : h.n_pairs;
+}
 }  // namespace
 
 size_t search_lds_bytes(const LigHeader &h, int waves)
 {
     const Layout c = make_layout(h.n_atoms, h.n_frags, pf_pairs(h), 6 + h.n_tors, 7 + h.n_tors);
-    return (size_t)h.total_words * 4 + (size_t)c.chain_words * 4 + (size_t)waves * c.wave_words * 4;
+    const size_t chains = h.intra_form == kFormStream ? (size_t)waves : 1;   // a chain per wave
+    return (size_t)h.total_words * 4 + chains * c.chain_words * 4 + (size_t)waves * c.wave_words * 4;
 }
 
 int search_class(const LigHeader &h)
 {
+    if (h.intra_form == kFormStream) return kStreamClass;
     if (h.intra_form == kFormAtoms) return 3;
     return h.n_pairs <= 512 ? 0 : (h.n_pairs <= 1024 ? 1 : 2);
 }
 
-// One switch over the six kernel variants: F(PPL, NBW).
+// One switch over the kernel variants by pair slots per lane (0: atom lists).
 #define DSDP_DISPATCH(cls, F)             \
     switch (cls) {                        \
-    case 0: F(8, 0); break;               \
-    case 1: F(16, 0); break;              \
-    case 2: F(32, 0); break;              \
-    case 3: F(0, 1); break;               \
+    case 0: F(8); break;                  \
+    case 1: F(16); break;                 \
+    case 2: F(32); break;                 \
+    case 3: F(kAtoms); break;             \
+    case 4: F(kStream); break;            \
     default: return hipErrorInvalidValue; \
     }
 
@@ -1791,8 +2052,8 @@ hipError_t launch_eval(const uint32_t *blob, int blob_words, const LigHeader &h,
     const int w = pick_eval_waves(bb, wb);
     const int blocks = (int)(((long)n + w - 1) / w);   // n may be close to INT_MAX
     const size_t lds = bb + w * wb;
-#define DSDP_EVAL(A, B) \
-    eval_kernel<A, B><<<blocks, 64 * w, lds, stream>>>(blob, blob_words, g, p, poses, n, energy, grad, xyz)
+#define DSDP_EVAL(A) \
+    eval_kernel<A><<<blocks, 64 * w, lds, stream>>>(blob, blob_words, g, p, poses, n, energy, grad, xyz)
     DSDP_DISPATCH(search_class(h), DSDP_EVAL)
 #undef DSDP_EVAL
     return hipGetLastError();
@@ -1805,26 +2066,39 @@ hipError_t launch_local_opt(const uint32_t *blob, int blob_words, const LigHeade
     if (n <= 0) return hipSuccess;
     if (waves < 1 || waves > kMaxWaves) return hipErrorInvalidValue;
     const size_t lds = search_lds_bytes(h, waves);
-#define DSDP_LOPT(A, B)                                                                                              \
-    local_opt_kernel<A, B><<<n, 64 * waves, lds, stream>>>(blob, blob_words, g, p, poses_in, n, poses_out, energy, \
-                                                           evals)
+    const int blocks = h.intra_form == kFormStream ? (int)(((long)n + waves - 1) / waves) : n;
+#define DSDP_LOPT_OF(A, BB)                                                                                        \
+    local_opt_kernel<A, BB><<<blocks, 64 * waves, lds, stream>>>(blob, blob_words, g, p, poses_in, n, poses_out, energy, \
+                                                            evals)
+#define DSDP_LOPT(A)             \
+    if (p.optimizer == kOptBB)   \
+        DSDP_LOPT_OF(A, true);   \
+    else                         \
+        DSDP_LOPT_OF(A, false)
     DSDP_DISPATCH(search_class(h), DSDP_LOPT)
 #undef DSDP_LOPT
+#undef DSDP_LOPT_OF
     return hipGetLastError();
 }
 
 hipError_t launch_tick(int cls, int waves, size_t lds_bytes, const uint32_t *arena, const ChainTask *tasks,
-                       int n_tasks, const GridView *grids, const SearchParams &p, int tick_steps, int init,
+                       int n_blocks, const GridView *grids, const SearchParams &p, int tick_steps, int init,
                        float *state, float *records, float4 *best_xyz, hipStream_t stream)
 {
-    if (n_tasks <= 0) return hipSuccess;
+    if (n_blocks <= 0) return hipSuccess;
     if (waves < 1 || waves > kMaxWaves) return hipErrorInvalidValue;
-    const dim3 grid(n_tasks), block(64 * waves);
-#define DSDP_TICK(A, B)                                                                                          \
-    tick_kernel<A, B><<<grid, block, lds_bytes, stream>>>(arena, tasks, grids, p, tick_steps, init, state, records, \
-                                                          best_xyz)
+    const dim3 grid(n_blocks), block(64 * waves);
+#define DSDP_TICK_OF(A, BB)                                                                                         \
+    tick_kernel<A, BB><<<grid, block, lds_bytes, stream>>>(arena, tasks, grids, p, tick_steps, init, state, records, \
+                                                           best_xyz)
+#define DSDP_TICK(A)             \
+    if (p.optimizer == kOptBB)   \
+        DSDP_TICK_OF(A, true);   \
+    else                         \
+        DSDP_TICK_OF(A, false)
     DSDP_DISPATCH(cls, DSDP_TICK)
 #undef DSDP_TICK
+#undef DSDP_TICK_OF
     return hipGetLastError();
 }
 #undef DSDP_DISPATCH
