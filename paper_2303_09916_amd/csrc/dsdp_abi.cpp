@@ -313,16 +313,13 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
         pairs.push_back((uint32_t)i | ((uint32_t)j << 8) | (pair_flags(xs[i], xs[j]) << 16));
     }
     const int np = (int)pairs.size();
-    // depth and subtree masks
+    // depths
     int max_depth = 0;
     std::vector<int> depth(nf, 0);
     for (int k = 1; k < nf; k++) {
         depth[k] = depth[lig->frag_parent[k]] + 1;
         max_depth = std::max(max_depth, depth[k]);
     }
-    std::vector<uint32_t> sub(nf, 0);
-    for (int m = 0; m < nf; m++)
-        for (int x = m; x >= 0; x = lig->frag_parent[x]) sub[x] |= 1u << m;
 
     LigHeader h;
     std::memset(&h, 0, sizeof h);
@@ -339,12 +336,10 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
         w += words;
         return o;
     };
+    take(8 * nf, 4);   // fragments, at kFragWords
     h.off_atom = take(4 * na, 4);
-    h.off_frag_u = take(4 * nf, 4);
-    h.off_frag_off = take(4 * nf, 4);
     h.off_atom_frag = take(na, 1);
     h.off_atom_ext = take(na, 1);
-    h.off_frag_range = take(nf, 1);
     h.off_frag_anc = take(nf, 1);
     const int lpa = na <= 32 ? 2 : 1;
     h.lanes_per_atom = lpa;
@@ -424,11 +419,8 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
         blob[(size_t)h.off_atom_ext + i] = (uint32_t)slot_atom[i];
     }
     for (int k = 0; k < nf; k++) {
-        if (k == 0) {
-            for (int a = 0; a < 3; a++) fput(h.off_frag_u + a, 0.f);
-            for (int a = 0; a < 3; a++) fput(h.off_frag_off + a, 0.f);
-            blob[(size_t)h.off_frag_u + 3] = 0u;   // no parent, depth 0
-        } else {
+        const int fu = kFragWords + 8 * k, fo = fu + 4;   // the root: zeros, no parent, depth 0
+        if (k > 0) {
             const int ia = atom_slot[lig->axis[2 * k]], ib = atom_slot[lig->axis[2 * k + 1]];
             double u[3], nrm = 0, op[3];
             for (int a = 0; a < 3; a++) {
@@ -438,15 +430,12 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
             nrm = std::sqrt(nrm);
             frag_origin(lig->frag_parent[k], op);
             for (int a = 0; a < 3; a++) {
-                fput(h.off_frag_u + 4 * k + a, (float)(u[a] / nrm));
-                fput(h.off_frag_off + 4 * k + a, (float)(ref[3 * ib + a] - op[a]));
+                fput(fu + a, (float)(u[a] / nrm));
+                fput(fo + a, (float)(ref[3 * ib + a] - op[a]));
             }
-            blob[(size_t)h.off_frag_u + 4 * k + 3] = (uint32_t)(lig->frag_parent[k] + 1) | ((uint32_t)depth[k] << 16);
+            blob[(size_t)fu + 3] = (uint32_t)(lig->frag_parent[k] + 1) | ((uint32_t)depth[k] << 16);
         }
-        blob[(size_t)h.off_frag_off + 4 * k + 3] = sub[k];
-    }
-    for (int k = 0; k < nf; k++) {
-        blob[(size_t)h.off_frag_range + k] = (uint32_t)fs[k] | ((uint32_t)fe[k] << 8) | ((uint32_t)se[k] << 16);
+        blob[(size_t)fo + 3] = (uint32_t)fs[k] | ((uint32_t)fe[k] << 8) | ((uint32_t)se[k] << 16);
         uint32_t anc = 0;
         int b = 0;
         for (int m = k > 0 ? lig->frag_parent[k] : 0; m > 0 && b < 4; m = lig->frag_parent[m], b++)

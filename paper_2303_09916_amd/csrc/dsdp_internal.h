@@ -77,11 +77,8 @@ struct LigHeader {
     // atoms in the caller's order), so that every fragment and every subtree
     // covers a contiguous range of atom slots.
     int32_t off_atom;        // float4[n_atoms]: local offset xyz from the fragment origin, w = map index bits
-    int32_t off_frag_u;      // float4[n_frags]: unit torsion axis, w = (parent + 1) | depth << 16
-    int32_t off_frag_off;    // float4[n_frags]: fragment origin in the parent frame, w = subtree mask bits
     int32_t off_atom_frag;   // int[n_atoms]
     int32_t off_atom_ext;    // int[n_atoms]: the caller's index of the atom in each slot
-    int32_t off_frag_range;  // uint32[n_frags]: first slot | end slot << 8 | subtree end slot << 16
     int32_t off_frag_anc;    // uint32[n_frags]: up to four ancestors below the root, nearest first, one
                              // byte each, 0 after the last
     int32_t off_pair;        // uint32[n_pairs]: i | j << 8 | flags << 16
@@ -117,6 +114,11 @@ constexpr int kStreamPairs = 127;   // pairs per chunk
 constexpr int kStreamChains = 4;    // chains per workgroup
 constexpr uint32_t kNbrNone = 0xFFu;   // empty partner byte (no pair is both hydrophobic and H-bonding)
 constexpr int kHeaderWords = (int)(sizeof(LigHeader) / 4 + 3) / 4 * 4;
+// The fragments follow the header, at an offset that kernels know: per fragment two
+// float4, the unit torsion axis in the parent frame (w = (parent + 1) | depth << 16)
+// and the fragment origin in the parent frame (w = first slot | end slot << 8 |
+// subtree end slot << 16).
+constexpr int kFragWords = kHeaderWords;
 
 // Per-chain result record in device memory (words).
 constexpr int kRecPose = 0;        // 40 floats: pose, stride 7 + n_tors used

@@ -27,7 +27,15 @@ namespace {
 
 constexpr float kPi = 3.14159265358979323846f;
 
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
+// Opaque to the optimiser: masks and addresses derived from it are formed where they
+// are used.  Hoisted out of the search's loops they took all scalar registers and
+// came back by lane reads from spills.
+__device__ __forceinline__ int lane_id()
+{
+    int l = (int)(threadIdx.x & 63u);
+    asm volatile("" : "+v"(l));
+    return l;
+}
 // uniform over the wave, and known to be: pointers and branches by wave stay scalar
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
@@ -355,12 +363,11 @@ struct LigL {
     int na, nf, nt, np, D, nx, maxdepth;
     float rg;
     const float4 *atom;      // local offset, w = map index
-    const float4 *fu;        // torsion axis in parent frame, w = (parent + 1) | depth << 16
-    const float4 *foff;      // origin in parent frame (w: subtree mask bits, not read here: subtrees
-                             // are slot ranges)
+    // per fragment: torsion axis in the parent frame, w = (parent + 1) | depth << 16; then
+    // origin in the parent frame, w = first slot | end slot << 8 | subtree end slot << 16
+    const float4 *frag;
     const int *atom_frag;
     const int *atom_ext;         // caller's index of the atom in each slot
-    const uint32_t *frag_range;  // first slot | end slot << 8 | subtree end slot << 16
     const uint32_t *frag_anc;    // up to four ancestors below the root, nearest first, a byte each
     const uint32_t *pair;
     const uint4 *plist;      // [n_chunks][64] gather lists (pair lists)
@@ -391,8 +398,8 @@ struct WaveL {
                            // (w); slot np stays 0.  Pair stream: [128], one chunk of pairs
     float4 *af, *at;       // [na]: prefix sums over atoms of force and of torque about the root origin
     float4 *R;       // [nf][4]: rows of R_k, then origin o_k
-    float *trial;    // [NXp]: this wave's trial pose
-    float *gt;       // [Dp]: gradient at the trial pose
+    float *trial;    // this wave's trial pose
+    float *gt;       // gradient at the trial pose
 };
 
 // State of one chain, shared by the waves that work on it.
@@ -401,7 +408,7 @@ struct ChainL {
     float *H;                    // [D][hs] inverse-Hessian estimate, row j owned by lane j; columns
                                  // D..hs-1 stay zero; hs is a multiple of 4 (float4 rows)
     int hs;
-    float *cur, *cand, *best;    // [NXp] poses
+    float *cur, *cand, *best;    // poses
     float *et;                   // [4 * kMaxWaves]: energies (total, inter, intra, wall) per trial slot
     float *misc;                 // [48]: initial draws and scalars
     bool raw;                    // the chain's start pose is a caller's (quaternion of any length)
@@ -415,16 +422,27 @@ constexpr int kOptBB = 1;        // SearchParams::optimizer value of Barzilai-Bo
 
 __host__ __device__ inline int rup4(int v) { return (v + 3) & ~3; }
 
+// Offsets in words.  What the optimiser touches every round lies at constant
+// offsets from the chain's and the wave's base, so that one address register
+// serves all of it (as pointers of their own they overflowed the scalar registers).
+namespace at {
+constexpr int kVec = 40, kPose = 44;   // strides of the tangent vectors and poses (at most 37, 38 used)
+constexpr int kG = 0, kP = kVec, kS = 2 * kVec, kY = 3 * kVec, kHy = 4 * kVec;
+constexpr int kCur = 5 * kVec, kCand = kCur + kPose, kBest = kCand + kPose;
+constexpr int kEt = kBest + kPose, kMisc = kEt + 16, kH = kMisc + 48;   // the chain's, H last
+constexpr int kTrial = 0, kGt = kPose, kR = kGt + kVec;                 // the wave's, R and the rest after
+static_assert(kMaxD <= kVec && kMaxD + 1 <= kPose && kH % 4 == 0 && kR % 4 == 0, "float4 alignment");
+}  // namespace at
+
 struct Layout {
-    int xyz, pf, af, at, R, trial, gt, wave_words;     // per-wave offsets
-    int vec, H, hs, pose, et, misc, chain_words, Dp, NXp;     // per-chain offsets
+    int xyz, pf, af, at, wave_words;   // per-wave offsets after R
+    int hs, chain_words, Dp;           // H's row stride
 };
 __host__ __device__ inline Layout make_layout(int na, int nf, int np, int D, int nx)
 {
     Layout c;
     c.Dp = rup4(D);
-    c.NXp = rup4(nx);
-    int w = 0;
+    int w = at::kR + 16 * nf;
     c.xyz = w; w += 4 * na;
     // np = -1: no pair-force scratch (atom lists); -2: one chunk (pair stream); else
     // the pairs, the zero slot np, and entries up to a whole group of two 64-pair slots
@@ -437,18 +455,9 @@ __host__ __device__ inline Layout make_layout(int na, int nf, int np, int D, int
         c.af = w; w += 4 * na;
         c.at = w; w += 4 * na;
     }
-    c.R = w; w += 16 * nf;
-    c.trial = w; w += c.NXp;
-    c.gt = w; w += c.Dp;
     c.wave_words = w;
-    w = 0;
-    c.vec = w; w += 5 * c.Dp;
     c.hs = c.Dp + 4;   // row stride off a multiple of the bank count
-    c.H = w; w += D * c.hs;
-    c.pose = w; w += 3 * c.NXp;
-    c.et = w; w += 4 * kMaxWaves;
-    c.misc = w; w += 48;
-    c.chain_words = w;
+    c.chain_words = at::kH + D * c.hs;
     return c;
 }
 
@@ -459,9 +468,9 @@ __device__ inline WaveL make_wave(float *base, const Layout &c)
     S.pf = reinterpret_cast<float4 *>(base + c.pf);
     S.af = reinterpret_cast<float4 *>(base + c.af);
     S.at = reinterpret_cast<float4 *>(base + c.at);
-    S.R = reinterpret_cast<float4 *>(base + c.R);
-    S.trial = base + c.trial;
-    S.gt = base + c.gt;
+    S.R = reinterpret_cast<float4 *>(base + at::kR);
+    S.trial = base + at::kTrial;
+    S.gt = base + at::kGt;
     return S;
 }
 
@@ -469,14 +478,12 @@ __device__ inline ChainL make_chain(float *base, const Layout &c, bool raw)
 {
     ChainL C;
     C.raw = raw;
-    float *v = base + c.vec;
-    C.g = v; C.p = v + c.Dp; C.s = v + 2 * c.Dp; C.y = v + 3 * c.Dp; C.Hy = v + 4 * c.Dp;
-    C.H = base + c.H;
+    C.g = base + at::kG; C.p = base + at::kP; C.s = base + at::kS; C.y = base + at::kY; C.Hy = base + at::kHy;
+    C.H = base + at::kH;
     C.hs = c.hs;
-    float *p = base + c.pose;
-    C.cur = p; C.cand = p + c.NXp; C.best = p + 2 * c.NXp;
-    C.et = base + c.et;
-    C.misc = base + c.misc;
+    C.cur = base + at::kCur; C.cand = base + at::kCand; C.best = base + at::kBest;
+    C.et = base + at::kEt;
+    C.misc = base + at::kMisc;
     return C;
 }
 
@@ -492,11 +499,9 @@ __device__ inline LigL make_lig(const uint32_t *blob, const uint32_t *hdr)
     L.maxdepth = h->max_depth;
     L.rg = h->rg;
     L.atom = reinterpret_cast<const float4 *>(blob + h->off_atom);
-    L.fu = reinterpret_cast<const float4 *>(blob + h->off_frag_u);
-    L.foff = reinterpret_cast<const float4 *>(blob + h->off_frag_off);
+    L.frag = reinterpret_cast<const float4 *>(blob + kFragWords);
     L.atom_frag = reinterpret_cast<const int *>(blob + h->off_atom_frag);
     L.atom_ext = reinterpret_cast<const int *>(blob + h->off_atom_ext);
-    L.frag_range = blob + h->off_frag_range;
     L.frag_anc = blob + h->off_frag_anc;
     L.pair = blob + h->off_pair;
     L.plist = reinterpret_cast<const uint4 *>(blob + h->off_plist);
@@ -612,8 +617,8 @@ __device__ inline void frames(const LigL &L, const WaveL &S, uint32_t anc, const
 #pragma unroll
         for (int j = 0; j < kAhead; j++) {
             const int m = mm[j] > 0 ? mm[j] : 1;   // an unused entry loads fragment 1's data
-            u[j] = L.fu[m];
-            off[j] = L.foff[m];
+            u[j] = L.frag[2 * m];
+            off[j] = L.frag[2 * m + 1];
             th[j] = pose[6 + m];
         }
         float4 qM = quat_axis(u[0], th[0]);
@@ -628,9 +633,9 @@ __device__ inline void frames(const LigL &L, const WaveL &S, uint32_t anc, const
         }
         int m = mm[kAhead - 1] > 0 ? (int)(__float_as_uint(u[kAhead - 1].w) & 0xffffu) - 1 : 0;
         while (m > 0) {
-            const float4 um = L.fu[m];
+            const float4 um = L.frag[2 * m];
             const float4 qm = quat_axis(um, pose[6 + m]);
-            v = f3(L.foff[m]) + quat_rotate(qm, v);
+            v = f3(L.frag[2 * m + 1]) + quat_rotate(qm, v);
             qM = quat_mul<false>(qm, qM);
             m = (int)(__float_as_uint(um.w) & 0xffffu) - 1;
         }
@@ -1151,8 +1156,8 @@ __device__ inline void eval_gradient(const LigL &L, const WaveL &S, const LaneSt
     uint32_t range = 0u;
     float4 okv = make_float4(0.f, 0.f, 0.f, 0.f), uref = okv, rr0 = okv, rr1 = okv, rr2 = okv;
     if (lane < L.nf) {
-        range = L.frag_range[lane];
-        uref = L.fu[lane];
+        range = __float_as_uint(L.frag[2 * lane + 1].w);
+        uref = L.frag[2 * lane];
         rr0 = S.R[4 * lane];
         rr1 = S.R[4 * lane + 1];
         rr2 = S.R[4 * lane + 2];
