@@ -139,19 +139,35 @@ dsdp_status validate_ligand(const dsdp_ligand *lig)
     return DSDP_OK;
 }
 
-// Layout of the intra-ligand term for a launch context (all give the same bits, so
-// this only moves speed).  A chain of one wave (the launch fills the device, or the
-// caller asks for one) takes the pair stream, which evaluates each pair once from
-// 2 KB of scratch: a 128-ligand batch of 128 chains each ran in STREAM_A ms with it and in
-// ATOMS_A ms with atom lists.  Chains of several waves take pair lists; launches that mix
-// ligands and do not fill the device take atom lists, whose smaller LDS footprint
-// lets more workgroups share a compute unit.
-int choose_intra_form(const IntraCtx &ctx)
+// Waves per chain by the chain count: what fills `per_cu` waves of every compute unit.
+int waves_for(long chains, long per_cu)
 {
-    const bool one_wave = ctx.waves == 1 || (ctx.waves == 0 && ctx.chains > 4L * device_cus());
+    return (int)std::max(1L, std::min(4L, per_cu * device_cus() / std::max(1L, chains)));
+}
+
+// Layout of the intra-ligand term for a launch context (all give the same bits, so
+// this only moves speed).  `lists` is the ligand's header with pair lists.
+//  - A chain of one wave takes the pair stream: 4096 chains of a 47-atom ligand with
+//    868 pairs ran 8 steps in 8.0 ms, with pair lists in 9.4, with atom lists in 10.1
+//    (20 atoms: 2.7, 2.9, 3.3).
+//  - Barzilai-Borwein chains of several waves share each evaluation's pairs: lists.
+//  - Other chains of several waves take pair lists, which have every pair in one go,
+//    while all workgroups are resident (47 atoms, 384 chains, 20 steps: 3.5 ms,
+//    stream 4.0), and the stream, which needs half the registers and a fraction of
+//    the LDS, when they would run in rounds (1024 chains: 4.8 ms at three waves,
+//    lists 6.5 at best; 60 atoms, 384 chains: 5.8, lists 6.5).
+//  - Launches that mix ligands and do not fill the device take atom lists, whose
+//    launches need not be split by pair count.
+int choose_intra_form(const IntraCtx &ctx, const LigHeader &lists)
+{
     if (ctx.form == DSDP_INTRA_ATOMS) return kFormAtoms;
-    if (one_wave) return kFormStream;
-    return ctx.form == DSDP_INTRA_AUTO && ctx.mixed ? kFormAtoms : kFormPairs;
+    const bool by_mix = ctx.form == DSDP_INTRA_AUTO && ctx.mixed;
+    const int waves = ctx.waves > 0 ? ctx.waves : waves_for(ctx.chains, ctx.bb || by_mix ? kListWaves : kStreamWaves);
+    if (waves == 1) return kFormStream;
+    if (by_mix) return kFormAtoms;
+    if (ctx.bb) return kFormPairs;
+    const long per_cu = std::min<long>(device_max_lds() / search_lds_bytes(lists, waves), kListWaves / waves);
+    return per_cu * device_cus() >= ctx.chains ? kFormPairs : kFormStream;
 }
 
 IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed)
@@ -161,6 +177,7 @@ IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed)
     c.waves = prm ? prm->waves_per_chain : 0;
     c.chains = chains;
     c.mixed = mixed;
+    c.bb = prm && prm->optimizer == DSDP_OPT_BB;
     return c;
 }
 
@@ -343,7 +360,6 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
     h.off_frag_anc = take(nf, 1);
     const int lpa = na <= 32 ? 2 : 1;
     h.lanes_per_atom = lpa;
-    h.intra_form = choose_intra_form(ctx);
 
     // per-lane lists of the chosen form.  Lane l serves atom l % 32 (every other
     // entry of the atom's list, from l / 32) when there are at most 32 atoms,
@@ -377,12 +393,17 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
         }
     }
     h.off_atom_rad = take(na, 1);
+    LigHeader lists = h;
+    lists.intra_form = kFormPairs;
+    lists.n_chunks = (int)((maxlen + 7) / 8);
+    lists.total_words = (w + np + 3 + lists.n_chunks * 256 + 3) / 4 * 4;
+    h.intra_form = choose_intra_form(ctx, lists);
     StreamChunks sc;
     if (h.intra_form == kFormStream) {
         // a workspace or pool is sized for the other layouts: a (small) ligand whose
         // stream would be larger than its pair lists takes those
         sc = stream_chunks(pairs, lane_list);
-        if (sc.n_chunks < 0 || (int)sc.words.size() + 64 * sc.list_words > np + (int)((maxlen + 7) / 8) * 256)
+        if (sc.n_chunks < 0 || (int)sc.words.size() + 64 * sc.list_words > np + lists.n_chunks * 256)
             h.intra_form = kFormPairs;
     }
     if (h.intra_form == kFormStream) {
@@ -394,7 +415,7 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
         h.off_slist = take(64 * sc.list_words, 1);
     } else if (h.intra_form == kFormPairs) {
         h.off_pair = take(np, 1);
-        h.n_chunks = (int)((maxlen + 7) / 8);
+        h.n_chunks = lists.n_chunks;
         h.off_plist = take(h.n_chunks * 64 * 4, 4);
     } else {
         h.nbr_words = (int)((maxlen + 3) / 4);
@@ -484,6 +505,7 @@ size_t max_blob_words(const dsdp_ligand *lig)
     IntraCtx pairs, atoms;
     pairs.form = DSDP_INTRA_PAIRS;
     pairs.waves = 2;
+    pairs.bb = true;
     atoms.form = DSDP_INTRA_ATOMS;
     if (prepare_ligand(lig, nullptr, a, pairs) || prepare_ligand(lig, nullptr, b, atoms)) return 0;
     return (size_t)std::max(a.h.total_words, b.h.total_words);
@@ -636,25 +658,18 @@ size_t device_max_lds()
     return bytes;
 }
 
-// Waves per chain: the caller's choice, else about 8 waves per compute unit
-// (measured on MI355X with a 32-atom ligand: 4 waves per chain at 384 chains,
-// 2 at 1024, 1 at 4096 chains); every choice gives the same results.  Reduced
+// Waves per chain: the caller's choice, else about 8 waves per compute unit (12
+// with the pair stream, whose registers leave room for them: 1024 chains of 47 atoms ran
+// in 4.8 ms at three waves, 5.5 at two); every choice gives the same results.  Reduced
 // until the workgroup's LDS fits the device's limit.
 dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains, int &waves)
 {
-    if (h.intra_form == kFormStream) {
-        waves = 1;
-        return DSDP_OK;
-    }
     int w = (prm && prm->waves_per_chain > 0) ? prm->waves_per_chain : 0;
     // Barzilai-Borwein evaluates one point per iteration: with atom lists one
     // wave does all of it (more would idle); pair lists spread its pairs over
     // the waves
     if (w == 0 && prm && prm->optimizer == DSDP_OPT_BB && h.intra_form != kFormPairs) w = 1;
-    if (w == 0) {
-        const long slots = 8L * device_cus();
-        w = (int)std::max(1L, std::min(4L, slots / std::max(1, n_chains)));
-    }
+    if (w == 0) w = waves_for(n_chains, h.intra_form == kFormStream ? kStreamWaves : kListWaves);
     const size_t cap = device_max_lds();
     while (w > 1 && search_lds_bytes(h, w) > cap) w--;
     if (search_lds_bytes(h, w) > cap)
@@ -666,13 +681,15 @@ dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains,
 // Waves per workgroup and its LDS for a launch of `chains` chains whose largest
 // member is h: the waves of a chain, or for the pair stream the chains that share
 // it: as many as leave four workgroups per compute unit and fit.
-dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds)
+dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds, int &cls)
 {
-    if (h.intra_form == kFormStream)
-        waves = (int)std::max(1L, std::min((long)kStreamChains, chains / (4L * device_cus())));
+    cls = search_class(h, waves);
+    const bool solo = cls == kStreamClass;
+    if (solo) waves = (int)std::max(1L, std::min((long)kStreamChains, chains / (4L * device_cus())));
     const size_t cap = device_max_lds();
-    while (waves > 1 && search_lds_bytes(h, waves) > cap) waves--;
-    lds = search_lds_bytes(h, waves);
+    while (waves > 1 && search_lds_bytes(h, waves, solo) > cap) waves--;
+    if (cls == kStreamClass + 1 && waves == 1) cls = kStreamClass;
+    lds = search_lds_bytes(h, waves, solo);
     if (lds > cap) return fail(DSDP_ERR_UNSUPPORTED, "ligand needs %zu bytes of LDS per chain", lds);
     return DSDP_OK;
 }
@@ -718,14 +735,14 @@ dsdp_status plan_groups(const dsdp_params *prm, const std::vector<const LigHeade
         lds1[i] = search_lds_bytes(*hdr[i], 1);
     }
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
-        const int ca = search_class(*hdr[a]), cb = search_class(*hdr[b]);
+        const int ca = search_class(*hdr[a], 1), cb = search_class(*hdr[b], 1);
         return ca != cb ? ca < cb : lds1[a] < lds1[b];
     });
     for (int k = 0; k < n;) {
         LaunchGroup g;
-        g.cls = search_class(*hdr[idx[k]]);
+        const int cls = search_class(*hdr[idx[k]], 1);
         int worst = idx[k];
-        while (k < n && search_class(*hdr[idx[k]]) == g.cls) {
+        while (k < n && search_class(*hdr[idx[k]], 1) == cls) {
             g.members.push_back(idx[k]);
             g.chains += chains[idx[k]];
             worst = idx[k];   // sorted by LDS: the last member needs the most
@@ -734,7 +751,7 @@ dsdp_status plan_groups(const dsdp_params *prm, const std::vector<const LigHeade
         // waves per chain from the group's chain count (groups are launched one
         // after another), then lowered until the largest member fits
         dsdp_status st = pick_waves(prm, *hdr[worst], (int)std::min<long>(g.chains, 1L << 30), g.waves);
-        if (!st) st = launch_shape(*hdr[worst], g.chains, g.waves, g.lds);
+        if (!st) st = launch_shape(*hdr[worst], g.chains, g.waves, g.lds, g.cls);
         if (st) return st;
         out.push_back(std::move(g));
     }
@@ -1117,12 +1134,13 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
     int waves = 1;
     size_t lds = 0;
     st = pick_waves(prm, pl.h, n_poses, waves);
-    if (!st) st = launch_shape(pl.h, n_poses, waves, lds);
+    int cls = 0;
+    if (!st) st = launch_shape(pl.h, n_poses, waves, lds, cls);
     if (st) return st;
     GridView view;
     st = device_view(g, ws, w, nullptr, s, view);
     if (st) return st;
-    HIP_TRY(launch_local_opt((const uint32_t *)(ws + w.arena), pl.h.total_words, pl.h, view, to_search(prm), waves,
+    HIP_TRY(launch_local_opt((const uint32_t *)(ws + w.arena), pl.h.total_words, pl.h, view, to_search(prm), cls, waves,
                              d_poses_in, n_poses, d_poses_out, d_energy, d_evals, s),
             "local-opt launch");
     return DSDP_OK;
@@ -1142,8 +1160,8 @@ constexpr int kTrialSteps = 4;   // timed MC steps of a tuner trial (every chain
 
 // The workspace's host-written part for one dock (blob, chain tasks from fresh
 // starts, grid view, ranking segment), uploaded on s.
-dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchWs &w, int waves, int n_chains,
-                        int n_steps, uint64_t seed, int top_k, char *ws, hipStream_t s, long &blocks)
+dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchWs &w, int cls, int waves,
+                        int n_chains, int n_steps, uint64_t seed, int top_k, char *ws, hipStream_t s, long &blocks)
 {
     HostImage img(w.host_end);
     std::memcpy(img.at<uint32_t>(w.arena), pl.blob.data(), pl.blob.size() * 4);
@@ -1161,7 +1179,7 @@ dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchW
         t.fresh = 1;
     }
     blocks = n_chains;
-    if (pl.h.intra_form == kFormStream) {
+    if (cls == kStreamClass) {
         blocks = 0;
         fill_stream_groups(tasks, blocks, 0, n_chains, waves);
     }
@@ -1195,16 +1213,16 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
     const int kind = prm->optimizer == DSDP_OPT_BB ? kTuneDockBb : kTuneDockBfgs;
     const TuneKey key = tune_key(dev, n_chains, {shape_bucket(pl.h.n_atoms, pl.h.n_pairs, 6 + pl.h.n_tors)}, kind);
     dsdp_status mst = DSDP_OK;
-    // the layout of a candidate (pair lists with one wave per chain: the pair stream)
+    // the layout of a candidate
     auto layout = [&](const DockCandidate &dc) -> const Prepared * {
-        const int want = dc.form == DSDP_INTRA_ATOMS ? kFormAtoms : dc.waves == 1 ? kFormStream : kFormPairs;
-        if (pl.h.intra_form == want) return &pl;
-        if (alt.blob.empty() || alt.h.intra_form != want) {
-            IntraCtx ctx;
-            ctx.form = dc.form;
-            ctx.waves = dc.waves;
-            if ((mst = prepare_ligand(lig, g->map_of_type, alt, ctx))) return nullptr;
-        }
+        if (pl.h.intra_form == kFormPairs && dc.form == DSDP_INTRA_PAIRS && dc.waves > 1) return &pl;
+        if (pl.h.intra_form == kFormStream && dc.form == DSDP_INTRA_PAIRS && dc.waves == 1) return &pl;
+        IntraCtx ctx;
+        ctx.form = dc.form;
+        ctx.waves = dc.waves;
+        ctx.chains = n_chains;
+        ctx.bb = prm->optimizer == DSDP_OPT_BB;
+        if ((mst = prepare_ligand(lig, g->map_of_type, alt, ctx))) return nullptr;
         return &alt;
     };
     int pick = -1;
@@ -1215,19 +1233,19 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
             const DockCandidate dc = dock_candidate(c);
             const Prepared *P = mst ? nullptr : layout(dc);
             if (!P) return -1.f;
-            int waves_wg = dc.waves;
-            size_t lds = search_lds_bytes(P->h, dc.waves);
-            if (P->h.intra_form == kFormStream && launch_shape(P->h, n_chains, waves_wg, lds)) return -1.f;
+            int waves_wg = dc.waves, cls = 0;
+            size_t lds = 0;
+            if (launch_shape(P->h, n_chains, waves_wg, lds, cls) || (cls != kStreamClass && waves_wg != dc.waves)) return -1.f;
             const SearchWs w = search_ws(P->h, n_chains);
-            if (lds > device_max_lds() || w.total > ws_bytes) return -1.f;
+            if (w.total > ws_bytes) return -1.f;
             long blocks = 0;
             // trial chains run 1 + kTrialSteps steps whatever the request's length,
             // so that requests of any length share the cached pick
-            if ((mst = upload_dock(g, *P, w, waves_wg, n_chains, 1 + kTrialSteps, seed, 0, ws, s, blocks))) return -1.f;
+            if ((mst = upload_dock(g, *P, w, cls, waves_wg, n_chains, 1 + kTrialSteps, seed, 0, ws, s, blocks))) return -1.f;
             Events ev;
             float ms = -1.f;
             auto tick = [&](int steps, int init) {
-                return launch_tick(search_class(P->h), waves_wg, lds, (const uint32_t *)(ws + w.arena),
+                return launch_tick(cls, waves_wg, lds, (const uint32_t *)(ws + w.arena),
                                    (const ChainTask *)(ws + w.tasks), (int)blocks, (const GridView *)(ws + w.grids), sp,
                                    steps, init, (float *)(ws + w.state), (float *)(ws + w.records),
                                    (float4 *)(ws + w.xyz), s);
@@ -1294,7 +1312,8 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
         if (st) return st;
     }
     size_t lds = 0;
-    st = launch_shape(pl.h, n_chains, waves, lds);
+    int cls = 0;
+    st = launch_shape(pl.h, n_chains, waves, lds, cls);
     if (st) return st;
     long blocks = 0;
     const SearchWs w = search_ws(pl.h, n_chains);
@@ -1307,7 +1326,7 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
     if (!d_ws || ws_bytes < w.total) return fail(DSDP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", w.total);
     if (!aligned256(d_ws)) return fail(DSDP_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
     char *ws = (char *)d_ws;
-    st = upload_dock(g, pl, w, waves, n_chains, n_steps, seed, top_k, ws, s, blocks);
+    st = upload_dock(g, pl, w, cls, waves, n_chains, n_steps, seed, top_k, ws, s, blocks);
     if (st) return st;
 
     Events ev;
@@ -1318,7 +1337,7 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
     float *rec = (float *)(ws + w.records);
     float4 *bxyz = (float4 *)(ws + w.xyz);
     int *sel = (int *)(ws + w.sel);
-    HIP_TRY(launch_tick(search_class(pl.h), waves, lds,
+    HIP_TRY(launch_tick(cls, waves, lds,
                         (const uint32_t *)(ws + w.arena), (const ChainTask *)(ws + w.tasks), (int)blocks,
                         (const GridView *)(ws + w.grids), sp, n_steps, 1, (float *)(ws + w.state), rec, bxyz, s),
             "search launch");
@@ -1403,30 +1422,28 @@ struct BatchPlan {
 // The plan of candidate `c`: each ligand's layout from its pair class, one
 // launch per (kernel variant, waves); waves lowered for a launch whose largest
 // member does not fit the LDS.  Returns false when a ligand cannot run.
-bool tuned_plan(int c, const std::vector<Prepared> &pp, const std::vector<Prepared> &pa,
-                const std::vector<Prepared> &ps, int n_chains, BatchPlan &out)
+bool tuned_plan(int c, const std::vector<Prepared> &ps, const std::vector<Prepared> &pa, int n_chains, BatchPlan &out)
 {
     const Plan pl = plan(c);
     out = BatchPlan();
-    const int n = (int)pp.size();
+    const int n = (int)ps.size();
     out.blob.resize((size_t)n);
     std::map<std::pair<int, int>, std::vector<int>> groups;
     for (int l = 0; l < n; l++) {
-        const bool lists = plan_form(pl, pp[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS;
-        const Prepared &pr = !lists ? pa[(size_t)l] : pl.waves == 1 ? ps[(size_t)l] : pp[(size_t)l];
+        const bool lists = plan_form(pl, ps[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS;
+        const Prepared &pr = lists ? ps[(size_t)l] : pa[(size_t)l];
         out.blob[(size_t)l] = &pr;
         // pair-stream launches by size, since a launch reserves its largest member's LDS
         const int size = pr.h.intra_form == kFormStream ? (pr.h.n_pairs > 512) + (pr.h.n_pairs > 1024) : 0;
-        groups[{search_class(pr.h) + 8 * size, pl.waves}].push_back(l);
+        groups[{search_class(pr.h, pl.waves) + 8 * size, pl.waves}].push_back(l);
     }
     for (auto &kv : groups) {
         BatchGroup b;
-        b.cls = kv.first.first % 8;
         b.waves = kv.first.second;
         int worst = kv.second[0];
         for (int l : kv.second)
             if (search_lds_bytes(out.blob[(size_t)l]->h, 1) > search_lds_bytes(out.blob[(size_t)worst]->h, 1)) worst = l;
-        if (launch_shape(out.blob[(size_t)worst]->h, (long)kv.second.size() * n_chains, b.waves, b.lds)) return false;
+        if (launch_shape(out.blob[(size_t)worst]->h, (long)kv.second.size() * n_chains, b.waves, b.lds, b.cls)) return false;
         // the largest ligands' chains first, so that the launch ends on short work
         std::vector<int> mem = kv.second;
         std::stable_sort(mem.begin(), mem.end(), [&](int a, int c) {
@@ -1610,17 +1627,15 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
     const bool tune = pp.tune == 1 && pp.optimizer == DSDP_OPT_BFGS && pp.waves_per_chain == 0 &&
                       pp.intra_form == DSDP_INTRA_AUTO && n_steps > 0;
     // every ligand prepared in the fixed rule's layout (unless the caller fixed one) or,
-    // when tuning, in all three
-    std::vector<Prepared> pls((size_t)n_ligs), atoms(tune ? (size_t)n_ligs : 0), streams(tune ? (size_t)n_ligs : 0);
+    // when tuning, in both
+    std::vector<Prepared> pls((size_t)n_ligs), atoms(tune ? (size_t)n_ligs : 0);
     size_t words = 0;
     for (int l = 0; l < n_ligs; l++) {
         if (tune) {
             IntraCtx ctx;
             ctx.form = DSDP_INTRA_PAIRS;
-            ctx.waves = 2;
-            st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], ctx);
             ctx.waves = 1;
-            if (!st) st = prepare_ligand(&ligs[l], g->map_of_type, streams[(size_t)l], ctx);
+            st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], ctx);
             ctx.form = DSDP_INTRA_ATOMS;
             if (!st) st = prepare_ligand(&ligs[l], g->map_of_type, atoms[(size_t)l], ctx);
         } else {
@@ -1631,8 +1646,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
             snprintf(msg, sizeof msg, "ligand %d: %s", l, g_error.c_str());
             return fail(st, "%s", msg);
         }
-        words += tune ? (size_t)std::max(pls[(size_t)l].h.total_words, atoms[(size_t)l].h.total_words)
-                      : max_blob_words(&ligs[l]);
+        words += max_blob_words(&ligs[l]);
     }
     const long n_slots = (long)n_ligs * n_chains;
     const SearchWs w = search_ws(words, n_slots, 1, n_ligs);
@@ -1664,7 +1678,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
         // starts afresh)
         auto measure = [&](int c) -> float {
             BatchPlan tp;
-            if (mst || !tuned_plan(c, pls, atoms, streams, n_chains, tp)) return -1.f;
+            if (mst || !tuned_plan(c, pls, atoms, n_chains, tp)) return -1.f;
             // 1 + kTrialSteps steps whatever the batch's length, so that batches of
             // any length share the cached pick
             if ((mst = upload_plan(tp, g, seeds, n_chains, 1 + kTrialSteps, top_k, w, ws, cs))) return -1.f;
@@ -1685,7 +1699,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
         int pick = 0;
         const bool found = tuner().pick(key, measure, pick, n_slots, kTrialSteps);
         if (mst) return mst;
-        if (!found || !tuned_plan(pick, pls, atoms, streams, n_chains, bp))
+        if (!found || !tuned_plan(pick, pls, atoms, n_chains, bp))
             return fail(DSDP_ERR_UNSUPPORTED, "no launch plan fits the batch");
     } else {
         std::vector<const LigHeader *> hdr((size_t)n_ligs);

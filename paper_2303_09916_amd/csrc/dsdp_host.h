@@ -47,9 +47,13 @@ struct IntraCtx {
     int waves = 0;
     long chains = 1;
     bool mixed = false;
+    bool bb = false;   // Barzilai-Borwein: a chain's waves share each evaluation's pairs
 };
 IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed);
-int choose_intra_form(const IntraCtx &ctx);   // kForm*
+// Waves per compute unit that the search's launches aim at: pair and atom lists,
+// pair stream (what their registers let a unit hold).
+constexpr long kListWaves = 8, kStreamWaves = 12;
+int choose_intra_form(const IntraCtx &ctx, const LigHeader &lists);   // kForm*
 dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepared &out, const IntraCtx &ctx);
 // blob words of the larger of the two forms (workspace sizing without params); 0 on invalid input
 size_t max_blob_words(const dsdp_ligand *lig);
@@ -59,7 +63,7 @@ SearchParams to_search(const dsdp_params *p);
 int device_cus();
 size_t device_max_lds();
 dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains, int &waves);
-dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds);
+dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds, int &cls);
 void fill_stream_groups(ChainTask *launch_tasks, long &blocks, long first, long n, int waves);
 // One launch per kernel variant over the ligands that use it; each launch
 // reserves its largest member's LDS for every workgroup.

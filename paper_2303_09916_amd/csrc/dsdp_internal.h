@@ -180,7 +180,8 @@ struct SearchParams {
 hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const int *cn, const float *clo,
                              float cell, const GridView &g, const int *map_types_host, float4 *maps,
                              hipStream_t stream);
-size_t search_lds_bytes(const LigHeader &h, int waves);
+// LDS of a workgroup of `waves` waves that serve one chain, or (solo) one each.
+size_t search_lds_bytes(const LigHeader &h, int waves, bool solo = false);
 // Gather-throughput probe: blocks x 256 threads, rounds of 8-corner gathers each;
 // sink: blocks * 256 floats.
 hipError_t launch_valu_probe(int blocks, int iters, float seed, float *sink, hipStream_t stream);
@@ -190,7 +191,7 @@ hipError_t launch_eval(const uint32_t *blob, int blob_words, const LigHeader &h,
                        const SearchParams &p, const float *poses, int n, float *energy, float *grad, float *xyz,
                        hipStream_t stream);
 hipError_t launch_local_opt(const uint32_t *blob, int blob_words, const LigHeader &h, const GridView &g,
-                            const SearchParams &p, int waves, const float *poses_in, int n, float *poses_out,
+                            const SearchParams &p, int cls, int waves, const float *poses_in, int n, float *poses_out,
                             float *energy, int *evals, hipStream_t stream);
 // Advance every task by up to tick_steps MC steps (init = start chains afresh).
 // cls: search_class of every task's ligand; lds_bytes: per-workgroup LDS.
@@ -200,10 +201,11 @@ hipError_t launch_tick(int cls, int waves, size_t lds_bytes, const uint32_t *are
                        float *state, float *records, float4 *best_xyz, hipStream_t stream);
 hipError_t launch_rank(const float *records, const float4 *best_xyz, const RankSeg *segs, int n_segs,
                        int max_chains, float rmsd_cut, int *sel, hipStream_t stream);
-// Kernel variant of a prepared ligand: 0..2 pair lists with 8, 16, 32 pair
-// slots per lane; 3 atom lists; 4 pair stream.
+// Kernel variant of a prepared ligand at `waves` waves per chain: 0..2 pair lists
+// with 8, 16, 32 pair slots per lane; 3 atom lists; 4 pair stream, a chain per
+// wave; 5 pair stream, several waves per chain.
 constexpr int kStreamClass = 4;
-int search_class(const LigHeader &h);
+int search_class(const LigHeader &h, int waves);
 // Size of the per-device static scratch array behind dsdp_dock_static, and its
 // device address on the current device (looked up on first use per device).
 constexpr size_t kStaticScratchBytes = DSDP_STATIC_SCRATCH_BYTES;

@@ -480,7 +480,7 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
         std::vector<long> ch;
         long total = 0;
         for (Request *q : s->running) total += q->n_chains;
-        one_wave = total > 4L * device_cus();
+        one_wave = total > kListWaves * device_cus() / 2;
         for (Request *q : s->running) {
             hdr.push_back(one_wave && q->has_stream ? &q->stream.h : &q->pl.h);
             ch.push_back(q->n_chains);
@@ -494,7 +494,7 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
         blocks.push_back(g.chains);
         for (int m : g.members) {
             const Request *q = s->running[(size_t)m];
-            const bool stream = g.cls == kStreamClass && q->has_stream;
+            const bool stream = one_wave && q->has_stream;
             const Prepared &pl = stream ? q->stream : q->pl;
             const size_t off = q->arena_off + (stream ? align256(q->pl.blob.size() * 4) : 0);
             for (int c = 0; c < q->n_chains; c++) {

@@ -1402,12 +1402,11 @@ __device__ __forceinline__ void chain_sync()
 // (lane l: pose coordinate l, gradient component l), so a step costs no LDS
 // round trip besides the gradient's; the other waves form the same trial poses
 // from the gradient and step length wave 0 leaves in LDS at each round's end.
-template <int PPL>
+template <int PPL, bool SOLO>
 __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_base, const ChainL &C,
                                const IntraRegs<PPL> &pr, const GridView &G, const SearchParams &P, float *x,
                                int &evals, int W)
 {
-    constexpr bool SOLO = PPL == kStream;
     const int lane = lane_id(), w = SOLO ? 0 : wave_id(), D = L.D, nx = L.nx;
     const WaveL S = make_wave(wave_base + w * lay.wave_words, lay);
     const bool split = PPL > 0 && W > 1;
@@ -1503,12 +1502,11 @@ __device__ Energy local_opt_bb(const LigL &L, const Layout &lay, float *wave_bas
 // kept in LDS; wave 0 does this for the start point).  `evals` counts the
 // evaluations the one-at-a-time search makes (speculative trials past the
 // accepted one are not counted).  The final gradient is left in C.g.
-template <int PPL>
+template <int PPL, bool SOLO>
 __device__ Energy local_opt_group(const LigL &L, const Layout &lay, float *wave_base, const ChainL &C,
                                   const IntraRegs<PPL> &pr, const GridView &G, const SearchParams &P, float *x,
                                   int &evals, int W)
 {
-    constexpr bool SOLO = PPL == kStream;
     const int lane = lane_id(), w = SOLO ? 0 : wave_id(), D = L.D;
     const WaveL S = make_wave(wave_base + w * lay.wave_words, lay);
     float Ex = 0.f;       // energy of the current iterate (its parts: C.misc + kMiscE)
@@ -1652,15 +1650,15 @@ __device__ Energy local_opt_group(const LigL &L, const Layout &lay, float *wave_
 
 // The kernels are compiled per optimiser: each then holds one evaluation's code
 // and only its own optimiser's registers.
-template <int PPL, bool BB>
+template <int PPL, bool BB, bool SOLO>
 __device__ inline Energy local_opt(const LigL &L, const Layout &lay, float *wave_base, const ChainL &C,
                                    const IntraRegs<PPL> &pr, const GridView &G, const SearchParams &P, float *x,
                                    int &evals, int W)
 {
     if constexpr (BB)
-        return local_opt_bb(L, lay, wave_base, C, pr, G, P, x, evals, W);
+        return local_opt_bb<PPL, SOLO>(L, lay, wave_base, C, pr, G, P, x, evals, W);
     else
-        return local_opt_group(L, lay, wave_base, C, pr, G, P, x, evals, W);
+        return local_opt_group<PPL, SOLO>(L, lay, wave_base, C, pr, G, P, x, evals, W);
 }
 
 // Stage the ligand blob into LDS (whole workgroup).
@@ -1708,7 +1706,7 @@ __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ 
 }
 
 // One pose per workgroup of W waves, or (pair stream) one per wave.
-template <int PPL, bool BB>
+template <int PPL, bool BB, bool SOLO>
 __global__ __launch_bounds__(256, kMinWaves<PPL>) void local_opt_kernel(const uint32_t *blob, int blob_words, GridView G,
                                                         SearchParams P, const float *poses_in, int n,
                                                         float *poses_out, float *energy, int *evals_out)
@@ -1718,7 +1716,6 @@ __global__ __launch_bounds__(256, kMinWaves<PPL>) void local_opt_kernel(const ui
     stage_blob(blob, blob_words, lds);
     const LigL L = make_lig(lds, blob);
     const Layout lay = make_layout(L.na, L.nf, layout_pairs<PPL>(L.np), L.D, L.nx);
-    constexpr bool SOLO = PPL == kStream;
     float *cbase = reinterpret_cast<float *>(lds) + blob_words;
     if (SOLO) cbase += wave_id() * (lay.chain_words + lay.wave_words);
     const ChainL C = make_chain(cbase, lay, true);
@@ -1735,7 +1732,7 @@ __global__ __launch_bounds__(256, kMinWaves<PPL>) void local_opt_kernel(const ui
     chain_sync<SOLO>();
     int evals = 0;
     const IntraRegs<PPL> pr = load_intra<PPL>(L);
-    const Energy E = local_opt<PPL, BB>(L, lay, wbase, C, pr, G, P, C.cur, evals, W);
+    const Energy E = local_opt<PPL, BB, SOLO>(L, lay, wbase, C, pr, G, P, C.cur, evals, W);
     if (w == 0) {
         if (lane < L.nx) poses_out[(long)idx * L.nx + lane] = C.cur[lane];
         if (lane == 0) {
@@ -1755,12 +1752,11 @@ __global__ __launch_bounds__(256, kMinWaves<PPL>) void local_opt_kernel(const ui
 // steps of mutate -> BFGS -> Metropolis, keeping the lowest accepted energy, and
 // saves its state.  A chain that reaches its last step writes its record and the
 // coordinates of its best pose (for ranking).
-template <int PPL, bool BB>
+template <int PPL, bool BB, bool SOLO>
 __global__ __launch_bounds__(256, kMinWaves<PPL>) void tick_kernel(const uint32_t *arena, const ChainTask *tasks, const GridView *grids,
                                                    SearchParams P, int tick_steps, int init, float *state,
                                                    float *records, float4 *best_xyz)
 {
-    constexpr bool SOLO = PPL == kStream;
     int first = (int)blockIdx.x;
     bool idle = false;
     if constexpr (SOLO) {
@@ -1887,7 +1883,7 @@ __global__ __launch_bounds__(256, kMinWaves<PPL>) void tick_kernel(const uint32_
             }
         }
         chain_sync<SOLO>();
-        const Energy Ec = local_opt<PPL, BB>(L, lay, wbase, C, pr, G, P, C.cand, evals, W);
+        const Energy Ec = local_opt<PPL, BB, SOLO>(L, lay, wbase, C, pr, G, P, C.cand, evals, W);
         lopts++;
         bool take = true;
         if (step > 0) {
@@ -2022,28 +2018,30 @@ int pf_pairs(const LigHeader &h)
 }
 }  // namespace
 
-size_t search_lds_bytes(const LigHeader &h, int waves)
+size_t search_lds_bytes(const LigHeader &h, int waves, bool solo)
 {
     const Layout c = make_layout(h.n_atoms, h.n_frags, pf_pairs(h), 6 + h.n_tors, 7 + h.n_tors);
-    const size_t chains = h.intra_form == kFormStream ? (size_t)waves : 1;   // a chain per wave
+    const size_t chains = solo ? (size_t)waves : 1;
     return (size_t)h.total_words * 4 + chains * c.chain_words * 4 + (size_t)waves * c.wave_words * 4;
 }
 
-int search_class(const LigHeader &h)
+int search_class(const LigHeader &h, int waves)
 {
-    if (h.intra_form == kFormStream) return kStreamClass;
+    if (h.intra_form == kFormStream) return waves == 1 ? kStreamClass : kStreamClass + 1;
     if (h.intra_form == kFormAtoms) return 3;
     return h.n_pairs <= 512 ? 0 : (h.n_pairs <= 1024 ? 1 : 2);
 }
 
-// One switch over the kernel variants by pair slots per lane (0: atom lists).
+// One switch over the kernel variants: pair slots per lane (or kAtoms, kStream),
+// a chain per wave.
 #define DSDP_DISPATCH(cls, F)             \
     switch (cls) {                        \
-    case 0: F(8); break;                  \
-    case 1: F(16); break;                 \
-    case 2: F(32); break;                 \
-    case 3: F(kAtoms); break;             \
-    case 4: F(kStream); break;            \
+    case 0: F(8, false); break;           \
+    case 1: F(16, false); break;          \
+    case 2: F(32, false); break;          \
+    case 3: F(kAtoms, false); break;      \
+    case 4: F(kStream, true); break;      \
+    case 5: F(kStream, false); break;     \
     default: return hipErrorInvalidValue; \
     }
 
@@ -2057,30 +2055,31 @@ hipError_t launch_eval(const uint32_t *blob, int blob_words, const LigHeader &h,
     const int w = pick_eval_waves(bb, wb);
     const int blocks = (int)(((long)n + w - 1) / w);   // n may be close to INT_MAX
     const size_t lds = bb + w * wb;
-#define DSDP_EVAL(A) \
+#define DSDP_EVAL(A, SOLO) \
     eval_kernel<A><<<blocks, 64 * w, lds, stream>>>(blob, blob_words, g, p, poses, n, energy, grad, xyz)
-    DSDP_DISPATCH(search_class(h), DSDP_EVAL)
+    DSDP_DISPATCH(search_class(h, 1), DSDP_EVAL)
 #undef DSDP_EVAL
     return hipGetLastError();
 }
 
 hipError_t launch_local_opt(const uint32_t *blob, int blob_words, const LigHeader &h, const GridView &g,
-                            const SearchParams &p, int waves, const float *poses_in, int n, float *poses_out,
+                            const SearchParams &p, int cls, int waves, const float *poses_in, int n, float *poses_out,
                             float *energy, int *evals, hipStream_t stream)
 {
     if (n <= 0) return hipSuccess;
     if (waves < 1 || waves > kMaxWaves) return hipErrorInvalidValue;
-    const size_t lds = search_lds_bytes(h, waves);
-    const int blocks = h.intra_form == kFormStream ? (int)(((long)n + waves - 1) / waves) : n;
-#define DSDP_LOPT_OF(A, BB)                                                                                        \
-    local_opt_kernel<A, BB><<<blocks, 64 * waves, lds, stream>>>(blob, blob_words, g, p, poses_in, n, poses_out, energy, \
+    const bool solo = cls == kStreamClass;
+    const size_t lds = search_lds_bytes(h, waves, solo);
+    const int blocks = solo ? (int)(((long)n + waves - 1) / waves) : n;
+#define DSDP_LOPT_OF(A, BB, SOLO)                                                                                        \
+    local_opt_kernel<A, BB, SOLO><<<blocks, 64 * waves, lds, stream>>>(blob, blob_words, g, p, poses_in, n, poses_out, energy, \
                                                             evals)
-#define DSDP_LOPT(A)             \
-    if (p.optimizer == kOptBB)   \
-        DSDP_LOPT_OF(A, true);   \
-    else                         \
-        DSDP_LOPT_OF(A, false)
-    DSDP_DISPATCH(search_class(h), DSDP_LOPT)
+#define DSDP_LOPT(A, SOLO)             \
+    if (p.optimizer == kOptBB)         \
+        DSDP_LOPT_OF(A, true, SOLO);   \
+    else                               \
+        DSDP_LOPT_OF(A, false, SOLO)
+    DSDP_DISPATCH(cls, DSDP_LOPT)
 #undef DSDP_LOPT
 #undef DSDP_LOPT_OF
     return hipGetLastError();
@@ -2093,14 +2092,14 @@ hipError_t launch_tick(int cls, int waves, size_t lds_bytes, const uint32_t *are
     if (n_blocks <= 0) return hipSuccess;
     if (waves < 1 || waves > kMaxWaves) return hipErrorInvalidValue;
     const dim3 grid(n_blocks), block(64 * waves);
-#define DSDP_TICK_OF(A, BB)                                                                                         \
-    tick_kernel<A, BB><<<grid, block, lds_bytes, stream>>>(arena, tasks, grids, p, tick_steps, init, state, records, \
+#define DSDP_TICK_OF(A, BB, SOLO)                                                                                         \
+    tick_kernel<A, BB, SOLO><<<grid, block, lds_bytes, stream>>>(arena, tasks, grids, p, tick_steps, init, state, records, \
                                                            best_xyz)
-#define DSDP_TICK(A)             \
-    if (p.optimizer == kOptBB)   \
-        DSDP_TICK_OF(A, true);   \
-    else                         \
-        DSDP_TICK_OF(A, false)
+#define DSDP_TICK(A, SOLO)             \
+    if (p.optimizer == kOptBB)         \
+        DSDP_TICK_OF(A, true, SOLO);   \
+    else                               \
+        DSDP_TICK_OF(A, false, SOLO)
     DSDP_DISPATCH(cls, DSDP_TICK)
 #undef DSDP_TICK
 #undef DSDP_TICK_OF
