@@ -409,7 +409,7 @@ size_t dsdp_dock_batch_workspace_bytes(const dsdp_ligand *ligs, int32_t n_ligs, 
  * uneven size share the launches: chains are grouped by the ligand's pair-list
  * size class, each group launched with the wave count the library's tuner picks
  * for the group's chain count; the MC steps run in ticks of steps_per_tick steps
- * (0 = about eight ticks) that continue from saved chain state, and the ticks
+ * (0 = about eight ticks, of at least 250 steps) that continue from saved chain state, and the ticks
  * and the ranking are captured once into a HIP graph and launched as one unit.
  *   ligs, seeds  host [n_ligs];
  *   out          host [n_ligs][top_k];  n_out host [n_ligs];

@@ -396,7 +396,7 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
     LigHeader lists = h;
     lists.intra_form = kFormPairs;
     lists.n_chunks = (int)((maxlen + 7) / 8);
-    lists.total_words = (w + np + 3 + lists.n_chunks * 256 + 3) / 4 * 4;
+    lists.total_words = (w + np + 3) / 4 * 4 + lists.n_chunks * 256;
     h.intra_form = choose_intra_form(ctx, lists);
     StreamChunks sc;
     if (h.intra_form == kFormStream) {
@@ -494,6 +494,7 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
     }
     for (int i = 0; i < na; i++) fput(h.off_atom_rad + i, xs_radius(xs[i]));
     out.h = h;
+    out.list_words = lists.total_words;
     out.blob.swap(blob);
     return DSDP_OK;
 }
@@ -736,16 +737,15 @@ dsdp_status plan_groups(const dsdp_params *prm, const std::vector<const LigHeade
     }
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
         const int ca = search_class(*hdr[a], 1), cb = search_class(*hdr[b], 1);
-        return ca != cb ? ca < cb : lds1[a] < lds1[b];
+        return ca != cb ? ca < cb : lds1[a] > lds1[b];
     });
     for (int k = 0; k < n;) {
         LaunchGroup g;
         const int cls = search_class(*hdr[idx[k]], 1);
-        int worst = idx[k];
+        const int worst = idx[k];   // sorted by LDS: the first member needs the most
         while (k < n && search_class(*hdr[idx[k]], 1) == cls) {
             g.members.push_back(idx[k]);
             g.chains += chains[idx[k]];
-            worst = idx[k];   // sorted by LDS: the last member needs the most
             k++;
         }
         // waves per chain from the group's chain count (groups are launched one
@@ -1433,9 +1433,7 @@ bool tuned_plan(int c, const std::vector<Prepared> &ps, const std::vector<Prepar
         const bool lists = plan_form(pl, ps[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS;
         const Prepared &pr = lists ? ps[(size_t)l] : pa[(size_t)l];
         out.blob[(size_t)l] = &pr;
-        // pair-stream launches by size, since a launch reserves its largest member's LDS
-        const int size = pr.h.intra_form == kFormStream ? (pr.h.n_pairs > 512) + (pr.h.n_pairs > 1024) : 0;
-        groups[{search_class(pr.h, pl.waves) + 8 * size, pl.waves}].push_back(l);
+        groups[{search_class(pr.h, pl.waves), pl.waves}].push_back(l);
     }
     for (auto &kv : groups) {
         BatchGroup b;
@@ -1646,7 +1644,8 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
             snprintf(msg, sizeof msg, "ligand %d: %s", l, g_error.c_str());
             return fail(st, "%s", msg);
         }
-        words += max_blob_words(&ligs[l]);
+        words += tune ? (size_t)std::max(pls[(size_t)l].list_words, atoms[(size_t)l].h.total_words)
+                      : max_blob_words(&ligs[l]);
     }
     const long n_slots = (long)n_ligs * n_chains;
     const SearchWs w = search_ws(words, n_slots, 1, n_ligs);
@@ -1724,9 +1723,11 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
     st = upload_plan(bp, g, seeds, n_chains, n_steps, top_k, w, ws, s);
     if (st) return st;
 
-    // ticks of steps_per_tick MC steps (0: about eight ticks), captured once as a
+    // ticks of steps_per_tick MC steps (0: about eight ticks, of at least 250 steps,
+    // since every tick ends on its slowest chains: 128 ligands x 128 chains x 200 steps
+    // took 324 ms in one tick, 350 in eight), captured once as a
     // graph: each group's ticks on its own branch, then the ranking
-    const int spt = steps_per_tick > 0 ? steps_per_tick : std::max(1, (n_steps + 7) / 8);
+    const int spt = steps_per_tick > 0 ? steps_per_tick : std::max(250, (n_steps + 7) / 8);
     const int n_ticks = n_steps > 0 ? (n_steps + spt - 1) / spt : 1;
     float *rec = (float *)(ws + w.records);
     float4 *bxyz = (float4 *)(ws + w.xyz);

@@ -38,6 +38,7 @@ struct Prepared {
     LigHeader h;
     std::vector<uint32_t> blob;
     std::vector<int> map_index;   // per atom
+    int list_words = 0;           // blob words with pair lists, whatever the layout
 };
 // Where a prepared ligand will run: the caller's layout request
 // (DSDP_INTRA_*) and waves per chain (0: by the chain count), the chains of the

@@ -389,7 +389,7 @@ constexpr int kAtoms = 0, kStream = -1;
 // others: three, which the atom lists and the pair stream reach without spills to
 // speak of (four spill the stream's loop invariants).
 template <int PPL>
-constexpr int kMinWaves = PPL == 8 || PPL == 16 ? 2 : 3;
+constexpr int kMinWaves = PPL == 8 || PPL == 16 ? 2 : PPL == kStream ? 4 : 3;
 
 // Scratch of one pose evaluation (one per wave).
 struct WaveL {

@@ -1,0 +1,101 @@
+"""GPU: the layouts of the intra-ligand term and the waves per chain move speed only.
+Docks, refinements and scores are equal bit for bit between the pair stream (one
+chain or pose per wave, one to four to a workgroup, or several waves), the pair
+lists and the atom lists, at pair counts around the stream's chunks of 127 pairs and
+chain counts that leave a workgroup partly filled."""
+import numpy as np
+import pytest
+
+import paper_2303_09916_amd as D
+from synth import make_ligand, make_receptor, make_box, PALETTE_T9
+from helpers import box32
+
+pytestmark = pytest.mark.gpu
+
+PAIRS, ATOMS = 1, 2
+
+
+@pytest.fixture(scope="module")
+def grid():
+    import gpu_common as gc
+    rec = make_receptor(300, radius=12.0, seed=4)
+    return gc.GpuGrid(rec.xyz, rec.types, box32(make_box(rec.pocket, 14.0, spacing=0.5)), PALETTE_T9)
+
+
+def params(form, waves, **over):
+    return D.dsdp_params_default(intra_form=form, waves_per_chain=waves, tune=0, **over)
+
+
+def chain_bits(grid, lig, n_chains, steps, p):
+    import gpu_common as gc
+    poses, xyz, chains, st = gc.gpu_dock(grid, lig, n_chains, steps, 11, 5, p)
+    rec = np.array([list(c.pos) + list(c.quat) + list(c.tors) + [c.e_total, c.e_inter, c.e_intra, c.e_wall]
+                    for c in chains], np.float32)
+    return rec, np.array([p_.chain for p_ in poses]), xyz, st.pose_evals, st.accepted
+
+
+def same(a, b):
+    return all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+# atoms, torsions: no pairs; a handful; around one chunk; around two; several; the largest
+SHAPES = [(5, 0), (8, 2), (19, 4), (20, 5), (26, 6), (33, 8), (47, 9), (64, 31)]
+
+
+@pytest.mark.parametrize("atoms,tors", SHAPES)
+def test_layouts_give_the_same_bits(grid, atoms, tors):
+    lig = make_ligand(atoms, tors, seed=atoms, palette=PALETTE_T9)
+    for over in ({}, {"optimizer": D.DSDP_OPT_BB, "bb_iters": 12}):
+        ref = chain_bits(grid, lig, 9, 3, params(ATOMS, 1, **over))
+        for form, waves in ((PAIRS, 1), (PAIRS, 2), (PAIRS, 4), (ATOMS, 3)):
+            assert same(chain_bits(grid, lig, 9, 3, params(form, waves, **over)), ref), (over, form, waves)
+
+
+@pytest.mark.parametrize("n_chains", [1027, 2051, 4099])
+def test_chains_that_share_a_workgroup(grid, n_chains):
+    """1027: several waves, in rounds; 2051 and 4099: two and four chains a workgroup,
+    the last one partly filled."""
+    lig = make_ligand(30, 6, seed=3, palette=PALETTE_T9)
+    ref = chain_bits(grid, lig, n_chains, 1, params(ATOMS, 1))
+    for waves in (1, 2, 3):
+        assert same(chain_bits(grid, lig, n_chains, 1, params(PAIRS, waves)), ref), waves
+    assert same(chain_bits(grid, lig, n_chains, 1, params(0, 0)), ref)
+
+
+@pytest.mark.parametrize("n", [1, 1030, 4101])
+def test_refine_and_score(grid, n):
+    import gpu_common as gc
+    lig = make_ligand(41, 7, seed=8, palette=PALETTE_T9)
+    L = D.Ligand.from_synth(lig)
+    rng = np.random.default_rng(n)
+    poses = np.zeros((n, L.nx), np.float32)
+    poses[:, :3] = rng.uniform(np.asarray(grid.origin), np.asarray(grid.origin) + (np.asarray(grid.n) - 1) * 0.5, (n, 3))
+    q = rng.normal(size=(n, 4))
+    poses[:, 3:7] = q * rng.uniform(0.2, 3.0, (n, 1))      # quaternions of any length
+    poses[:, 7:] = rng.uniform(-np.pi, np.pi, (n, L.n_tors))
+    poses[0, 3:7] = (1e-21, 0.0, 2e-21, 0.0)               # whose squared length is denormal
+    ref = gc.gpu_local_opt(grid, lig, poses, params(ATOMS, 1))
+    assert np.isfinite(ref[1]).all()
+    for form, waves in ((PAIRS, 1), (PAIRS, 2), (PAIRS, 4), (0, 0)):
+        assert same(gc.gpu_local_opt(grid, lig, poses, params(form, waves)), ref), (form, waves)
+    ref = gc.gpu_eval(grid, lig, poses, params(ATOMS, 1))
+    for form, waves in ((PAIRS, 1), (PAIRS, 2), (0, 0)):
+        assert same(gc.gpu_eval(grid, lig, poses, params(form, waves)), ref), (form, waves)
+
+
+def test_batch_of_mixed_sizes(grid):
+    """A batch that shares launches between ligands of every size equals its docks alone,
+    with chains that do not divide into workgroups."""
+    import gpu_common as gc
+    torch = grid.torch
+    ligs = [make_ligand(a, t, seed=a, palette=PALETTE_T9) for a, t in SHAPES]
+    Ls = [D.Ligand.from_synth(l) for l in ligs]
+    n_chains = 519
+    ws = gc.dev_bytes(torch, D.dsdp_dock_batch_workspace_bytes(Ls, n_chains))
+    seeds = list(range(100, 100 + len(Ls)))
+    for p in (params(PAIRS, 1), params(0, 0), None):
+        res, _ = D.dsdp_dock_batch(grid.handle, Ls, n_chains, 2, seeds, 3, ws, p)
+        for lig, L, seed, got in zip(ligs, Ls, seeds, res):
+            w1 = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n_chains))
+            want, _, _, _ = D.dsdp_dock(grid.handle, L, n_chains, 2, seed, 3, w1, params(ATOMS, 1))
+            assert [(x.chain, x.e_total, list(x.pos)) for x in got] == [(x.chain, x.e_total, list(x.pos)) for x in want]
