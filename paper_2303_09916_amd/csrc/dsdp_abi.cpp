@@ -679,20 +679,28 @@ dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains,
     return DSDP_OK;
 }
 
-// Waves per workgroup and its LDS for a launch of `chains` chains whose largest
-// member is h: the waves of a chain, or for the pair stream the chains that share
-// it: as many as leave four workgroups per compute unit and fit.
-dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds, int &cls)
+// Kernel variant, waves per workgroup and LDS of a launch over ligands of one layout:
+// the waves of a chain, or for the pair stream the chains that share it, as many as
+// leave four workgroups per compute unit and fit.  The LDS is every member's
+// maximum at that shape: the member that needs most for one chain need not be the one
+// that needs most for four.
+dsdp_status launch_shape(const std::vector<const LigHeader *> &members, long chains, int &waves, size_t &lds, int &cls)
 {
-    cls = search_class(h, waves);
-    const bool solo = cls == kStreamClass;
-    if (solo) waves = (int)std::max(1L, std::min((long)kStreamChains, chains / (4L * device_cus())));
-    const size_t cap = device_max_lds();
-    while (waves > 1 && search_lds_bytes(h, waves, solo) > cap) waves--;
-    if (cls == kStreamClass + 1 && waves == 1) cls = kStreamClass;
-    lds = search_lds_bytes(h, waves, solo);
-    if (lds > cap) return fail(DSDP_ERR_UNSUPPORTED, "ligand needs %zu bytes of LDS per chain", lds);
-    return DSDP_OK;
+    const LigHeader &any = *members[0];
+    if (any.intra_form == kFormStream && waves == 1) {
+        cls = kStreamClass;
+        waves = (int)std::max(1L, std::min((long)kStreamChains, chains / (4L * device_cus())));
+    } else {
+        cls = search_class(any, waves);
+    }
+    for (;; waves--) {
+        if (cls == kStreamClass + 1 && waves == 1) cls = kStreamClass;
+        lds = 0;
+        for (const LigHeader *h : members) lds = std::max(lds, search_lds_bytes(*h, waves, cls == kStreamClass));
+        if (lds <= device_max_lds()) return DSDP_OK;
+        if (waves == 1) break;
+    }
+    return fail(DSDP_ERR_UNSUPPORTED, "ligand needs %zu bytes of LDS per chain", lds);
 }
 
 // The workgroups of n tasks of one ligand (task `first` of the launch onwards) in a
@@ -751,7 +759,9 @@ dsdp_status plan_groups(const dsdp_params *prm, const std::vector<const LigHeade
         // waves per chain from the group's chain count (groups are launched one
         // after another), then lowered until the largest member fits
         dsdp_status st = pick_waves(prm, *hdr[worst], (int)std::min<long>(g.chains, 1L << 30), g.waves);
-        if (!st) st = launch_shape(*hdr[worst], g.chains, g.waves, g.lds, g.cls);
+        std::vector<const LigHeader *> members;
+        for (int m : g.members) members.push_back(hdr[m]);
+        if (!st) st = launch_shape(members, g.chains, g.waves, g.lds, g.cls);
         if (st) return st;
         out.push_back(std::move(g));
     }
@@ -1135,7 +1145,7 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
     size_t lds = 0;
     st = pick_waves(prm, pl.h, n_poses, waves);
     int cls = 0;
-    if (!st) st = launch_shape(pl.h, n_poses, waves, lds, cls);
+    if (!st) st = launch_shape({&pl.h}, n_poses, waves, lds, cls);
     if (st) return st;
     GridView view;
     st = device_view(g, ws, w, nullptr, s, view);
@@ -1235,7 +1245,7 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
             if (!P) return -1.f;
             int waves_wg = dc.waves, cls = 0;
             size_t lds = 0;
-            if (launch_shape(P->h, n_chains, waves_wg, lds, cls) || (cls != kStreamClass && waves_wg != dc.waves)) return -1.f;
+            if (launch_shape({&P->h}, n_chains, waves_wg, lds, cls) || (cls != kStreamClass && waves_wg != dc.waves)) return -1.f;
             const SearchWs w = search_ws(P->h, n_chains);
             if (w.total > ws_bytes) return -1.f;
             long blocks = 0;
@@ -1313,7 +1323,7 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
     }
     size_t lds = 0;
     int cls = 0;
-    st = launch_shape(pl.h, n_chains, waves, lds, cls);
+    st = launch_shape({&pl.h}, n_chains, waves, lds, cls);
     if (st) return st;
     long blocks = 0;
     const SearchWs w = search_ws(pl.h, n_chains);
@@ -1438,10 +1448,9 @@ bool tuned_plan(int c, const std::vector<Prepared> &ps, const std::vector<Prepar
     for (auto &kv : groups) {
         BatchGroup b;
         b.waves = kv.first.second;
-        int worst = kv.second[0];
-        for (int l : kv.second)
-            if (search_lds_bytes(out.blob[(size_t)l]->h, 1) > search_lds_bytes(out.blob[(size_t)worst]->h, 1)) worst = l;
-        if (launch_shape(out.blob[(size_t)worst]->h, (long)kv.second.size() * n_chains, b.waves, b.lds, b.cls)) return false;
+        std::vector<const LigHeader *> members;
+        for (int l : kv.second) members.push_back(&out.blob[(size_t)l]->h);
+        if (launch_shape(members, (long)kv.second.size() * n_chains, b.waves, b.lds, b.cls)) return false;
         // the largest ligands' chains first, so that the launch ends on short work
         std::vector<int> mem = kv.second;
         std::stable_sort(mem.begin(), mem.end(), [&](int a, int c) {

@@ -64,7 +64,7 @@ SearchParams to_search(const dsdp_params *p);
 int device_cus();
 size_t device_max_lds();
 dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains, int &waves);
-dsdp_status launch_shape(const LigHeader &h, long chains, int &waves, size_t &lds, int &cls);
+dsdp_status launch_shape(const std::vector<const LigHeader *> &members, long chains, int &waves, size_t &lds, int &cls);
 void fill_stream_groups(ChainTask *launch_tasks, long &blocks, long first, long n, int waves);
 // One launch per kernel variant over the ligands that use it; each launch
 // reserves its largest member's LDS for every workgroup.

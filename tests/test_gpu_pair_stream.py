@@ -99,3 +99,41 @@ def test_batch_of_mixed_sizes(grid):
             w1 = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n_chains))
             want, _, _, _ = D.dsdp_dock(grid.handle, L, n_chains, 2, seed, 3, w1, params(ATOMS, 1))
             assert [(x.chain, x.e_total, list(x.pos)) for x in got] == [(x.chain, x.e_total, list(x.pos)) for x in want]
+
+
+def test_members_that_need_most_lds_differ(grid):
+    """A launch's LDS covers every member at its shape: of a ligand with many pairs and few
+    torsions (large lists) and one with few atoms and many torsions (large chain state) the
+    first needs more for one chain and the second for four; also through the scheduler."""
+    import gpu_common as gc
+    torch = grid.torch
+    ligs = [make_ligand(46, 3, seed=5, palette=PALETTE_T9), make_ligand(36, 20, seed=6, palette=PALETTE_T9)]
+    ligs += [make_ligand(60, 12, seed=7, palette=PALETTE_T9), make_ligand(44, 28, seed=9, palette=PALETTE_T9)]
+    Ls = [D.Ligand.from_synth(l) for l in ligs]
+    n_chains, steps = 1100, 2
+    want = []
+    for k, L in enumerate(Ls):
+        w1 = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n_chains))
+        want.append(D.dsdp_dock(grid.handle, L, n_chains, steps, 40 + k, 3, w1, params(ATOMS, 1))[0])
+
+    def key(poses):
+        return [(x.chain, x.e_total, list(x.pos), list(x.tors)) for x in poses]
+
+    for lo, hi in ((0, 2), (2, 4), (0, 4)):
+        ws = gc.dev_bytes(torch, D.dsdp_dock_batch_workspace_bytes(Ls[lo:hi], n_chains))
+        for p in (params(PAIRS, 1), params(PAIRS, 2), params(ATOMS, 2), None):
+            res, _ = D.dsdp_dock_batch(grid.handle, Ls[lo:hi], n_chains, steps, list(range(40 + lo, 40 + hi)), 3, ws, p)
+            assert [key(r) for r in res] == [key(w) for w in want[lo:hi]], (lo, hi)
+    rec = make_receptor(300, radius=12.0, seed=4)
+    box = box32(make_box(rec.pocket, 14.0, spacing=0.5))
+    pool = gc.dev_bytes(torch, D.dsdp_sched_fixed_bytes(8192) + (64 << 20))
+    h = D.dsdp_sched_create(pool, 8192, 1)
+    try:
+        rid = D.dsdp_sched_add_receptor(h, rec.xyz, rec.types, box, list(PALETTE_T9))
+        t = [D.dsdp_sched_submit(h, rid, L, n_chains, steps, 40 + k, 3) for k, L in enumerate(Ls)]
+        for _ in range(8):
+            D.dsdp_sched_tick(h)
+        for k, ticket in enumerate(t):
+            assert key(D.dsdp_sched_poll(h, ticket, 3)[1]) == key(want[k]), k
+    finally:
+        D.dsdp_sched_destroy(h)
