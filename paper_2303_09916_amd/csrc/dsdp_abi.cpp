@@ -946,6 +946,8 @@ dsdp_status dsdp_build_grids(const dsdp_atom *rec, int32_t n_rec, const dsdp_box
     g->view.site = nullptr;
     g->view.n_site = 0;
     g->view.site_r = 0.f;
+    g->view.quads = nullptr;
+    g->view.qz = 0;
     for (int t = 0; t < kNXS; t++) g->map_of_type[t] = -1;
     for (int t = 0; t < n_types; t++) {
         g->map_of_type[tl[t]] = t;
@@ -1114,6 +1116,21 @@ dsdp_status dsdp_eval_poses(dsdp_grids g, const dsdp_ligand *lig, const float *d
     GridView view;
     st = device_view(g, ws, w, nullptr, s, view);
     if (st) return st;
+    // A large set of poses gathers from a copy of the maps whose cells are contiguous
+    // (launch_quads), kept in the part of the workspace that only the searches use:
+    // maps of 32 MB or more (below, L2 keeps enough of them: 53^3 x 8, 10^6 poses of 32
+    // atoms 1474 us without the copy, 1446 with it), ligands of 24 atoms or more (12
+    // atoms leave the launch bound elsewhere: 920 and 931 us on 81^3 x 8) and at least four
+    // atoms to gather per node, which repay the copy (on 81^3 x 8, 32 atoms: 3 x 10^5
+    // poses, 2.3 a node, 621 and 608 us; 10^6 poses, 7.5 a node, 1941 and 1552; 65^3 x 8,
+    // 55 atoms, 3.5 a node, 581 and 599).
+    const size_t nodes = (size_t)view.T * view.n[0] * view.n[1] * view.n[2];
+    if (pl.h.intra_form == kFormStream && nodes * 16 >= ((size_t)32 << 20) && pl.h.n_atoms >= 24 &&
+        (double)n_poses * pl.h.n_atoms >= 4.0 * (double)nodes && quads_bytes(view) <= w.total - w.state) {
+        view.quads = (const float4 *)(ws + w.state);
+        view.qz = (view.n[2] + 1) / 2 * 2;
+        HIP_TRY(launch_quads(view, (float4 *)(ws + w.state), s), "map copy launch");
+    }
     HIP_TRY(launch_eval((const uint32_t *)(ws + w.arena), pl.h.total_words, pl.h, view, to_search(prm), d_poses,
                         n_poses, d_energy, d_grad, d_xyz, s),
             "eval launch");

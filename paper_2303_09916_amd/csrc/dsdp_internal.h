@@ -60,7 +60,17 @@ struct GridView {
     const float4 *site;
     int n_site;
     float site_r;
+    // copy of the maps for scoring many poses (launch_quads): [T][ny][nx][qz] of four nodes
+    const float4 *quads;
+    int qz;
 };
+// The maps with each node's (x, y) to (x + 1, y + 1) quad stored together and z
+// innermost (padded to even), so that a cell's eight corners are 128 contiguous bytes.
+inline size_t quads_bytes(const GridView &g)
+{
+    return (size_t)g.T * g.n[1] * g.n[0] * ((g.n[2] + 1) / 2 * 2) * 64;
+}
+hipError_t launch_quads(const GridView &g, float4 *quads, hipStream_t stream);
 constexpr int kMaxSite = 256;
 constexpr int kMaxSitePoints = 1024;   // points one site extraction can return
 constexpr uint32_t kTagSite = 3;       // Philox stream of the initial positions in the search space

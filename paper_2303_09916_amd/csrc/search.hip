@@ -386,8 +386,10 @@ constexpr int kAtoms = 0, kStream = -1;
 // Waves per SIMD the search kernels' registers must allow.  Register-held pair lists:
 // two, so that two workgroups of four waves share a compute unit (384 chains take
 // 1.5 a unit; with one a launch of 384 took 0.95 ms where it takes 0.61).  The
-// others: three, which the atom lists and the pair stream reach without spills to
-// speak of (four spill the stream's loop invariants).
+// lists read from LDS and the atom lists: three, which they reach without spills
+// (four and five waves spill: a 128-ligand library 132 and 142 ms instead of 126).  The
+// pair stream: four, for 40 bytes of spilled invariants (4096 one-wave chains of 47
+// atoms 7.9 ms at three, 6.9 at four).
 template <int PPL>
 constexpr int kMinWaves = PPL == 8 || PPL == 16 ? 2 : PPL == kStream ? 4 : 3;
 
@@ -775,7 +777,7 @@ struct LaneState {
 // barrier wave 0 alone gathers them and finishes; the other waves return zeros.
 // Every pair term and every sum is the one a single wave forms, so the result
 // does not depend on `parts`.  All `parts` waves must make the call.
-template <int PPL>
+template <int PPL, bool QUADS = false>
 __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL> &pr, const GridView &G,
                               const float *pose, const Root &root, float wall_slope, LaneState &keep, int part = 0, int parts = 1,
                               float4 *pf_shared = nullptr)
@@ -837,11 +839,18 @@ __device__ Energy eval_energy(const LigL &L, const WaveL &S, const IntraRegs<PPL
         // results below does not also wait for these loads; node offsets are
         // 32-bit (a map holds fewer than 2^31 nodes)
         const int t = __float_as_int(loc.w);
-        const int sy = G.n[0], sz = G.n[0] * G.n[1];
-        const global_f4 *m0 = (const global_f4 *)(G.maps + (long)t * sz * G.n[2]) + (ci[2] * sz + ci[1] * sy + ci[0]);
-        c000 = as_float4(m0[0]); c100 = as_float4(m0[1]); c010 = as_float4(m0[sy]); c110 = as_float4(m0[sy + 1]);
-        c001 = as_float4(m0[sz]); c101 = as_float4(m0[sz + 1]);
-        c011 = as_float4(m0[sz + sy]); c111 = as_float4(m0[sz + sy + 1]);
+        if constexpr (QUADS) {
+            const global_f4 *m =
+                (const global_f4 *)G.quads + ((((long)t * G.n[1] + ci[1]) * G.n[0] + ci[0]) * G.qz + ci[2]) * 4;
+            c000 = as_float4(m[0]); c100 = as_float4(m[1]); c010 = as_float4(m[2]); c110 = as_float4(m[3]);
+            c001 = as_float4(m[4]); c101 = as_float4(m[5]); c011 = as_float4(m[6]); c111 = as_float4(m[7]);
+        } else {
+            const int sy = G.n[0], sz = G.n[0] * G.n[1];
+            const global_f4 *m0 = (const global_f4 *)(G.maps + (long)t * sz * G.n[2]) + (ci[2] * sz + ci[1] * sy + ci[0]);
+            c000 = as_float4(m0[0]); c100 = as_float4(m0[1]); c010 = as_float4(m0[sy]); c110 = as_float4(m0[sy + 1]);
+            c001 = as_float4(m0[sz]); c101 = as_float4(m0[sz + 1]);
+            c011 = as_float4(m0[sz + sy]); c111 = as_float4(m0[sz + sy + 1]);
+        }
         // atom lists and the pair stream: the corners are used at once, so that
         // their registers are free for the intra-ligand loop (the launches that use
         // these layouts run several waves per SIMD, which hide the wait)
@@ -1199,12 +1208,12 @@ __device__ inline void eval_gradient(const LigL &L, const WaveL &S, const LaneSt
 }
 
 // Energy and gradient of `pose`.
-template <int PPL>
+template <int PPL, bool QUADS>
 __device__ Energy eval_pose(const LigL &L, const WaveL &S, const IntraRegs<PPL> &pr, const GridView &G,
                             const float *pose, float *grad, float wall_slope)
 {
     LaneState keep;
-    const Energy e = eval_energy(L, S, pr, G, pose, root_of(pose, true), wall_slope, keep);
+    const Energy e = eval_energy<PPL, QUADS>(L, S, pr, G, pose, root_of(pose, true), wall_slope, keep);
     eval_gradient(L, S, keep, grad);
     return e;
 }
@@ -1670,8 +1679,12 @@ __device__ inline void stage_blob(const uint32_t *blob, int words, uint32_t *lds
 
 // ---------------------------------------------------------------- kernels
 
-// One pose per wave (independent waves).
-template <int PPL>
+// One pose per wave (independent waves).  Poses spread over the box share few cache
+// lines, so a large set is bound by the lines below L2: 4.5 an atom from the maps (a
+// pair of nodes on each of four rows), 1.5 from the quads: 2^20 poses of 32 atoms on
+// 81^3 x 8 maps took 2026 us from the maps and take 1604 from the quads, their copy
+// included.  When they are used: dsdp_eval_poses.
+template <int PPL, bool QUADS>
 __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ blob, int blob_words, GridView G, SearchParams P,
                                                    const float *poses, int n, float *energy, float *grad, float *xyz)
 {
@@ -1690,7 +1703,7 @@ __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ 
     if (lane < L.nx) S.trial[lane] = poses[(long)idx * L.nx + lane];
     wave_sync();
     const IntraRegs<PPL> pr = load_intra<PPL>(L);
-    const Energy E = eval_pose(L, S, pr, G, S.trial, S.gt, P.wall_slope);
+    const Energy E = eval_pose<PPL, QUADS>(L, S, pr, G, S.trial, S.gt, P.wall_slope);
     if (lane == 0) {
         energy[4 * idx + 0] = E.total;
         energy[4 * idx + 1] = E.inter;
@@ -1703,6 +1716,25 @@ __global__ __launch_bounds__(256) void eval_kernel(const uint32_t *__restrict__ 
         float *o = xyz + ((long)idx * L.na + L.atom_ext[lane]) * 3;
         o[0] = v.x; o[1] = v.y; o[2] = v.z;
     }
+}
+
+// The quads of every node: 8 nodes in x and 8 in z to a workgroup, so that both the
+// reads (x innermost) and the writes (z innermost) are of whole 128-byte lines.  At the
+// upper faces the node itself stands for its missing neighbour (no cell starts there).
+__global__ __launch_bounds__(64) void quads_kernel(GridView G, float4 *quads)
+{
+    const int lane = (int)threadIdx.x;
+    const int zb = (G.n[2] + 7) / 8, t = (int)blockIdx.z / zb;
+    const int x = (int)blockIdx.x * 8 + (lane & 7), y = (int)blockIdx.y, z = ((int)blockIdx.z % zb) * 8 + (lane >> 3);
+    if (x >= G.n[0] || z >= G.n[2]) return;
+    const int dx = x + 1 < G.n[0] ? 1 : 0, dy = y + 1 < G.n[1] ? G.n[0] : 0;
+    const float4 *m = G.maps + (((long)t * G.n[2] + z) * G.n[1] + y) * G.n[0] + x;
+    float4 *q = quads + ((((long)t * G.n[1] + y) * G.n[0] + x) * G.qz + z) * 4;
+    const float4 a = m[0], b = m[dx], c = m[dy], d = m[dx + dy];
+    q[0] = a;
+    q[1] = b;
+    q[2] = c;
+    q[3] = d;
 }
 
 // One pose per workgroup of W waves, or (pair stream) one per wave.
@@ -2055,10 +2087,25 @@ hipError_t launch_eval(const uint32_t *blob, int blob_words, const LigHeader &h,
     const int w = pick_eval_waves(bb, wb);
     const int blocks = (int)(((long)n + w - 1) / w);   // n may be close to INT_MAX
     const size_t lds = bb + w * wb;
-#define DSDP_EVAL(A, SOLO) \
-    eval_kernel<A><<<blocks, 64 * w, lds, stream>>>(blob, blob_words, g, p, poses, n, energy, grad, xyz)
-    DSDP_DISPATCH(search_class(h, 1), DSDP_EVAL)
+#define DSDP_EVAL_OF(A, QUADS) \
+    eval_kernel<A, QUADS><<<blocks, 64 * w, lds, stream>>>(blob, blob_words, g, p, poses, n, energy, grad, xyz)
+#define DSDP_EVAL(A, SOLO) DSDP_EVAL_OF(A, false)
+    if (g.quads && search_class(h, 1) == kStreamClass)
+        DSDP_EVAL_OF(kStream, true);
+    else
+        DSDP_DISPATCH(search_class(h, 1), DSDP_EVAL)
 #undef DSDP_EVAL
+#undef DSDP_EVAL_OF
+    return hipGetLastError();
+}
+
+hipError_t launch_quads(const GridView &g, float4 *quads, hipStream_t stream)
+{
+    GridView v = g;
+    v.qz = (g.n[2] + 1) / 2 * 2;
+    // at most 256 x 2048 x (17 x 256) blocks
+    const dim3 grid((g.n[0] + 7) / 8, g.n[1], (unsigned)(g.T * ((g.n[2] + 7) / 8)));
+    quads_kernel<<<grid, 64, 0, stream>>>(v, quads);
     return hipGetLastError();
 }
 

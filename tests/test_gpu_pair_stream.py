@@ -137,3 +137,34 @@ def test_members_that_need_most_lds_differ(grid):
             assert key(D.dsdp_sched_poll(h, ticket, 3)[1]) == key(want[k]), k
     finally:
         D.dsdp_sched_destroy(h)
+
+
+def test_scoring_from_the_contiguous_copy():
+    """Enough poses on large enough maps are scored from a copy of the maps with contiguous
+    cells; the results are those of the same poses scored in small sets, which are not.
+    Odd node counts, poses at and beyond every face."""
+    import gpu_common as gc
+    rec = make_receptor(300, radius=12.0, seed=4)
+    g = gc.GpuGrid(rec.xyz, rec.types, box32(make_box(rec.pocket, (12.4, 13.3, 11.6), spacing=0.15)), PALETTE_T9)
+    torch = g.torch
+    nodes = int(np.prod(g.n)) * len(PALETTE_T9)
+    assert nodes * 16 >= 32 << 20 and min(g.n) % 2 + max(g.n) % 2 >= 1
+    lig = make_ligand(30, 5, seed=2, palette=PALETTE_T9)
+    L = D.Ligand.from_synth(lig)
+    n = 4 * nodes // L.n_atoms + 777
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    P = torch.rand((n, L.nx), generator=gen, device="cuda")
+    lo = torch.tensor(np.asarray(g.origin, np.float32), device="cuda")
+    ext = torch.tensor([(a - 1) * 0.15 for a in g.n], device="cuda", dtype=torch.float32)
+    P[:, :3] = lo - 2.0 + P[:, :3] * (ext + 4.0)
+    P[:, 3:] = P[:, 3:] * 2 - 1
+    P[:, 7:] *= np.pi
+    E = torch.empty((n, 4), device="cuda")
+    G = torch.empty((n, L.D), device="cuda")
+    ws = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n))
+    D.dsdp_eval_poses(g.handle, L, P, n, E, G, None, ws)
+    small = n // 9
+    for k in list(range(0, n - small, small))[:9]:
+        e, gr = torch.empty((small, 4), device="cuda"), torch.empty((small, L.D), device="cuda")
+        D.dsdp_eval_poses(g.handle, L, P[k:k + small].contiguous(), small, e, gr, None, ws)
+        assert torch.equal(e, E[k:k + small]) and torch.equal(gr, G[k:k + small])
