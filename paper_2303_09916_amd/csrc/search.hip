@@ -19,6 +19,7 @@
 // does not depend on which wave, workgroup or launch runs it.
 #include "dsdp_internal.h"
 
+#include <cstring>
 #include <mutex>
 #include <type_traits>
 
@@ -2097,6 +2098,31 @@ hipError_t launch_eval(const uint32_t *blob, int blob_words, const LigHeader &h,
 #undef DSDP_EVAL
 #undef DSDP_EVAL_OF
     return hipGetLastError();
+}
+
+namespace {
+struct PutWords {
+    uint32_t w[1000];
+};
+__global__ __launch_bounds__(256) void put_kernel(const PutWords words, int n, uint32_t *dst)
+{
+    for (int i = (int)threadIdx.x; i < n; i += 256) dst[i] = words.w[i];
+}
+}  // namespace
+
+hipError_t launch_put(const void *src, size_t bytes, void *dst, hipStream_t stream)
+{
+    if (bytes > kPutBytes || bytes % 4 != 0) return hipErrorInvalidValue;
+    for (size_t done = 0; done < bytes;) {
+        PutWords a;
+        const size_t n = bytes - done < sizeof a.w ? bytes - done : sizeof a.w;
+        std::memcpy(a.w, (const char *)src + done, n);
+        put_kernel<<<1, 256, 0, stream>>>(a, (int)(n / 4), (uint32_t *)((char *)dst + done));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        done += n;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_quads(const GridView &g, float4 *quads, hipStream_t stream)

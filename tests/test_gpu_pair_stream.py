@@ -168,3 +168,34 @@ def test_scoring_from_the_contiguous_copy():
         e, gr = torch.empty((small, 4), device="cuda"), torch.empty((small, L.D), device="cuda")
         D.dsdp_eval_poses(g.handle, L, P[k:k + small].contiguous(), small, e, gr, None, ws)
         assert torch.equal(e, E[k:k + small]) and torch.equal(gr, G[k:k + small])
+
+
+@pytest.mark.parametrize("atoms,tors", SHAPES)
+def test_calls_in_a_row_with_ligands_of_every_size(grid, atoms, tors):
+    """A ligand reaches the device as kernel arguments or as a copy, by its size: two
+    ligands scored one after the other on one workspace, without a wait between, do not
+    disturb each other, in either layout."""
+    torch = grid.torch
+    Ls = [D.Ligand.from_synth(make_ligand(a, t, seed=a, palette=PALETTE_T9)) for a, t in ((atoms, tors), (33, 8))]
+    n = 40
+    ws = torch.empty(max(D.dsdp_dock_workspace_bytes(L, n) for L in Ls), dtype=torch.uint8, device="cuda")
+    lo = torch.tensor(np.asarray(grid.origin, np.float32), device="cuda")
+    P = [torch.rand((n, L.nx), device="cuda") for L in Ls]
+    for p in P:
+        p[:, :3] = p[:, :3] * 13.0 + lo
+
+    def score(k, form):
+        e = torch.empty((n, 4), device="cuda")
+        g = torch.empty((n, Ls[k].D), device="cuda")
+        D.dsdp_eval_poses(grid.handle, Ls[k], P[k], n, e, g, None, ws, params(form, 0))
+        return e, g
+
+    alone = []
+    for k in (0, 1):
+        alone.append(score(k, ATOMS))
+        torch.cuda.synchronize()
+    got = [score(k, f) for _ in range(3) for k in (0, 1) for f in (PAIRS, ATOMS)]
+    torch.cuda.synchronize()
+    for i, (e, g) in enumerate(got):
+        k = (i // 2) % 2
+        assert torch.equal(e, alone[k][0]) and torch.equal(g, alone[k][1])
