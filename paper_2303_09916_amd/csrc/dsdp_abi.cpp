@@ -613,13 +613,16 @@ dsdp_status device_view(const dsdp_grids_s *g, char *ws, const SearchWs &w, unsi
 // Host data of the call to the device, ready on the stream.  What fits goes as kernel
 // arguments: a pageable copy has to be waited for before the host data is freed,
 // and the wait was a third of a small call (scoring 96 poses of a 20-atom ligand
-// took 29 us, takes 20; the maps of 300 atoms in a 43^3 box 45 and 31).  A stream
+// took 29 us, takes 20; the maps of 300 atoms in a 43^3 box 45 and 31).  `most` is where
+// the launches cost more than the wait: two of them where the device's part is short
+// (a 42-atom ligand's 12 KB in three: 55 us, copied 51), four for maps (800 atoms in
+// a 20 A box: 65 us, copied 74).  A stream
 // under capture takes the copy, whose wait fails there: the ligand of a recorded
 // call must not be repeated by its replays.
-dsdp_status upload(const void *src, size_t bytes, void *dst, hipStream_t stream)
+dsdp_status upload(const void *src, size_t bytes, void *dst, hipStream_t stream, size_t most = kPutBytes / 2)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (bytes <= kPutBytes && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
+    if (bytes <= most && hipStreamIsCapturing(stream, &capture) == hipSuccess &&
         capture == hipStreamCaptureStatusNone) {
         HIP_TRY(launch_put(src, bytes, dst, stream), "upload launch");
         return DSDP_OK;
@@ -941,8 +944,8 @@ dsdp_status dsdp_build_grids(const dsdp_atom *rec, int32_t n_rec, const dsdp_box
     int *d_start = (int *)(ws + align256((size_t)std::max(n_rec, 1) * 16));
     const size_t atom_bytes = keep.size() * sizeof(float4), start_bytes = start.size() * sizeof(int);
     if (atom_bytes + start_bytes <= kPutBytes) {
-        st = upload(sorted.data(), atom_bytes, d_atoms, s);
-        if (!st) st = upload(start.data(), start_bytes, d_start, s);
+        st = upload(sorted.data(), atom_bytes, d_atoms, s, kPutBytes);
+        if (!st) st = upload(start.data(), start_bytes, d_start, s, kPutBytes);
         if (st) return st;
     } else {
         HIP_TRY(hipMemcpyAsync(d_atoms, sorted.data(), atom_bytes, hipMemcpyHostToDevice, s), "receptor upload");

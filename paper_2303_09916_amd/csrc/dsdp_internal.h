@@ -189,7 +189,7 @@ struct SearchParams {
 // Launchers (defined in the .hip files).
 // Small host data (whole words, at most kPutBytes) to device memory as kernel
 // arguments: the caller's copy is free on return and nothing waits.
-constexpr size_t kPutBytes = 2 * 4000;
+constexpr size_t kPutBytes = 4 * 4000;
 hipError_t launch_put(const void *src, size_t bytes, void *dst, hipStream_t stream);
 hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const int *cn, const float *clo,
                              float cell, const GridView &g, const int *map_types_host, float4 *maps,
