@@ -388,7 +388,7 @@ typedef struct {
     int32_t intra_form_large;  /* pick: the same for more pairs (docks: the layout) */
     int32_t waves_per_chain;   /* pick */
     int32_t trial_steps;       /* timed MC steps of each trial (every chain of the request) */
-    float trial_ms[DSDP_TUNE_CANDIDATES];   /* each candidate's trial time (< 0: could not run;
+    float trial_ms[DSDP_TUNE_CANDIDATES];   /* each candidate's trial time (< 0: not run;
                                                0 past the kind's candidates) */
 } dsdp_tune_entry;
 

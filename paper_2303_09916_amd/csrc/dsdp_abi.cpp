@@ -1246,6 +1246,27 @@ dsdp_status upload_dock(const dsdp_grids_s *g, const Prepared &pl, const SearchW
     return DSDP_OK;
 }
 
+// Candidates that a trial of a few steps rates too well: its launch ends on its slowest
+// chain, a share that more waves per chain shorten and that long searches hardly have.
+// Left out, each for the other that the same searches ran faster with:
+//  - several waves without pair lists where a chain per wave fills the device (32 atoms,
+//    100 steps: 8192 chains 59 ms at one wave, 70 at two, where the trials say 3.94 and
+//    3.65; 60 atoms, 3072 chains: 68 and, with atom lists at two, 97, the trials 5.29 and
+//    5.25);
+//  - three and four waves without pair lists while two-wave workgroups with lists of up to
+//    sixteen pairs a lane are all resident and four-wave ones are not (200 steps, 640
+//    chains: 47 atoms 35.3 ms with these lists, 38.3 with the stream at four waves, where
+//    the trials say 1.70 and 1.55; 20 atoms 19.1 and, with atom lists, 24.4, the trials
+//    0.63 and 0.64; 32 atoms, 1024 chains, 400 steps: 51 and 59, the trials 1.19 and 1.16).
+// `two_wave_lists`: the two-wave candidate takes pair lists, resident all at once.
+bool beyond_trial(const Prepared &p, int waves, long chains, bool two_wave_lists)
+{
+    const long cus = device_cus();
+    if (p.h.intra_form == kFormPairs || waves == 1) return false;
+    if (chains >= kStreamWaves * cus) return true;
+    return waves > 2 && two_wave_lists && p.h.n_pairs <= 16 * 64 && chains > kListWaves / 4 * cus;
+}
+
 // The tuned layout and waves of a dock: the cached pick for the request's
 // make-up (optimiser, ligand shape, chains), else each candidate timed on a
 // trial of the request itself (every chain, one untimed step from fresh starts
@@ -1277,10 +1298,15 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
     if (lookup_only) {
         if (!tuner().find(key, pick)) return DSDP_OK;
     } else {
+        bool two_wave_lists = false;
         auto measure = [&](int c) -> float {
+            if (c == 0 && kind == kTuneDockBfgs) {
+                const Prepared *two = layout({DSDP_INTRA_PAIRS, 2});
+                two_wave_lists = two && two->h.intra_form == kFormPairs;
+            }
             const DockCandidate dc = dock_candidate(c);
             const Prepared *P = mst ? nullptr : layout(dc);
-            if (!P) return -1.f;
+            if (!P || beyond_trial(*P, dc.waves, n_chains, two_wave_lists)) return -1.f;
             int waves_wg = dc.waves, cls = 0;
             size_t lds = 0;
             if (launch_shape({&P->h}, n_chains, waves_wg, lds, cls) || (cls != kStreamClass && waves_wg != dc.waves)) return -1.f;
@@ -1353,6 +1379,24 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
         st = tune_dock(g, lig, prm, pl0, alt, n_chains, seed, sp, (char *)d_ws,
                        static_ws ? kStaticScratchBytes : ws_bytes, s, static_ws, use, waves);
         if (st) return st;
+    }
+    // The fixed rule rates waves as short launches do (see beyond_trial); whole searches of
+    // ligands with up to sixteen pairs a lane run faster with two waves per chain where
+    // resident pair lists serve those (32 atoms, 1024 chains, 200 steps: 26.2 ms, the stream
+    // at three waves 28.9) and where the rule leaves one wave to chains that would not fill
+    // the device (2048 chains: 38.9 ms, one wave 45.4).
+    const long cus = device_cus();
+    if (waves == 0 && prm->waves_per_chain == 0 && prm->intra_form == DSDP_INTRA_AUTO && prm->optimizer != DSDP_OPT_BB &&
+        pl0.h.n_pairs <= 16 * 64 && n_chains > kListWaves / 4 * cus && n_chains <= kListWaves * cus) {
+        IntraCtx two;
+        two.form = DSDP_INTRA_PAIRS;
+        two.waves = 2;
+        two.chains = n_chains;
+        if ((st = prepare_ligand(lig, g->map_of_type, alt, two))) return st;
+        if (alt.h.intra_form == kFormPairs || n_chains > kStreamWaves / 2 * cus) {
+            use = &alt;
+            waves = 2;
+        }
     }
     const Prepared &pl = *use;
     if (waves == 0) {

@@ -62,6 +62,17 @@ def test_chains_that_share_a_workgroup(grid, n_chains):
     assert same(chain_bits(grid, lig, n_chains, 1, params(0, 0)), ref)
 
 
+@pytest.mark.parametrize("n_chains", [513, 1024, 1537, 2049, 3072])
+@pytest.mark.parametrize("atoms,tors", [(20, 5), (47, 9), (60, 12)])
+def test_automatic_choices_around_their_limits(grid, n_chains, atoms, tors):
+    """The tuner's pick and the fixed rule, on both sides of the chain counts at which
+    candidates are left out."""
+    lig = make_ligand(atoms, tors, seed=atoms, palette=PALETTE_T9)
+    ref = chain_bits(grid, lig, n_chains, 1, params(ATOMS, 1))
+    assert same(chain_bits(grid, lig, n_chains, 1, params(0, 0)), ref)
+    assert same(chain_bits(grid, lig, n_chains, 1, D.dsdp_params_default(tune=1)), ref)
+
+
 @pytest.mark.parametrize("n", [1, 1030, 4101])
 def test_refine_and_score(grid, n):
     import gpu_common as gc
