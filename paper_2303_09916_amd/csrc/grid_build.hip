@@ -26,8 +26,8 @@
 //  - the root and the reciprocal are the shortest sequences that still round
 //    correctly (both checked against sqrtf and 1/x over every input in range).
 // Measured on MI355X, kernel alone, before and after: 81^3 nodes, 8 types, 4000
-// atoms 270 -> 120 us; 107^3, 9 types, 12000 atoms 540 -> 243 us; 43^3, 4 types, 300
-// atoms 60 -> 26 us (37 us without the split into runs of maps, see kFillWaves).
+// atoms 275 -> 120 us; 107^3, 9 types, 12000 atoms 610 -> 243 us; 43^3, 4 types, 300
+// atoms 72 -> 26 us (37 us without the split into runs of maps, see kFillWaves).
 #include "dsdp_internal.h"
 
 #include <algorithm>

@@ -7,8 +7,9 @@
 // modification) and the parallelisation paragraph (many short, independent
 // Monte Carlo copies; results post-processed into ranked poses).
 //
-// Execution model: one workgroup of 1-4 wavefronts per chain (one wavefront per
-// pose for plain evaluations).  Lanes map to ligand atoms for kinematics and
+// Execution model: one workgroup of 1-4 wavefronts per chain, or, where chains fill
+// the device, a wavefront per chain and up to four chains of one ligand per workgroup
+// (one wavefront per pose for plain evaluations).  Lanes map to ligand atoms for kinematics and
 // grid gathers, to atom pairs (strided) for the intra-ligand terms, to fragments
 // for the torque tree and to tangent coordinates for the BFGS vectors; a chain's
 // extra waves evaluate concurrent line-search trials (BFGS) or share one
@@ -683,7 +684,7 @@ __device__ __forceinline__ uint32_t pl_entry(const uint4 (&pl)[N], int t)
 // Trilinear energy and force of one atom from its eight gathered corners (eq. 2
 // and eq. 4); the map gradient along a clamped axis is dropped, the wall added.
 // Written with explicit fused multiply-adds and no others formed, so that every
-// place it is inlined rounds alike (the two intra-ligand layouts use it at
+// place it is inlined rounds alike (the intra-ligand layouts use it at
 // different points of the evaluation).
 __device__ __forceinline__ float corner_sum(const float (&w)[8], float v0, float v1, float v2, float v3, float v4,
                                             float v5, float v6, float v7)

@@ -92,7 +92,8 @@ inline TuneKey tune_key(int device, int chains, const std::vector<ShapeBucket> &
 }
 
 // The candidate plans: for each, the layout of a ligand's intra-ligand term as
-// a function of its pair class (1 pair lists, 2 atom lists) and the waves per
+// a function of its pair class (1 each pair once: pair lists or the pair stream, by
+// the rule of choose_intra_form; 2 atom lists) and the waves per
 // chain.  Plan 0 is the library's fixed rule for batches that fill the device.
 struct Plan {
     int form_small;   // layout of ligands with at most 512 pairs
@@ -114,7 +115,7 @@ inline Plan plan(int i)
 }
 inline int plan_form(const Plan &p, int n_pairs) { return n_pairs <= 512 ? p.form_small : p.form_large; }
 
-// The candidates of a single ligand's dock: both layouts (1 pair lists, 2 atom
+// The candidates of a single ligand's dock: both forms (1 each pair once, 2 atom
 // lists) at 4, 3, 2 and 1 waves per chain.
 struct DockCandidate {
     int form;
