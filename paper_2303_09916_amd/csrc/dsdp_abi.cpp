@@ -181,63 +181,6 @@ IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed)
     return c;
 }
 
-// One chunk of the pair stream, in the order its pairs are stored: those without a
-// class first (each part in list order).  Pair p of the list is entry `at[p]` of
-// chunk p / kStreamPairs.
-struct StreamChunks {
-    std::vector<int> at;
-    std::vector<uint32_t> words;              // stored pair words, whole slots
-    std::vector<std::vector<uint8_t>> list;   // per chunk: [entry][lane]
-    uint32_t chunk_words[2] = {0, 0}, plain = 0;
-    int n_chunks = 0, list_words = 0;
-};
-StreamChunks stream_chunks(const std::vector<uint32_t> &pairs, const std::vector<std::vector<uint16_t>> &lane_list)
-{
-    StreamChunks sc;
-    const int np = (int)pairs.size();
-    sc.n_chunks = (np + kStreamPairs - 1) / kStreamPairs;
-    sc.at.assign((size_t)np, 0);
-    for (int c = 0; c < sc.n_chunks; c++) {
-        const int p0 = c * kStreamPairs, p1 = std::min(np, p0 + kStreamPairs), n = p1 - p0;
-        const int slots = n > 63 ? 2 : 1, zero = 64 * slots - 1;
-        int k = 0;
-        std::vector<uint32_t> w((size_t)64 * slots, 0x80000000u);   // no pair
-        for (int pass = 0; pass < 2; pass++) {
-            for (int p = p0; p < p1; p++)
-                if (((pairs[(size_t)p] >> 16) != 0) == (pass == 1)) {
-                    sc.at[(size_t)p] = k;
-                    w[(size_t)k++] = pairs[(size_t)p];
-                }
-            // slots of class-free pairs only (a short last slot without a class pair counts)
-            if (pass == 0) sc.plain |= (uint32_t)(k == n ? slots : k / 64) << (2 * c);
-        }
-        sc.words.insert(sc.words.end(), w.begin(), w.end());
-        size_t longest = 0;
-        std::vector<std::vector<uint8_t>> lanes(64);
-        for (int l = 0; l < 64; l++) {
-            for (uint16_t e : lane_list[(size_t)l]) {
-                const int p = e & 0x7fff;
-                if (p >= p0 && p < p1) lanes[(size_t)l].push_back((uint8_t)(sc.at[(size_t)p] | ((e & 0x8000) ? 128 : 0)));
-            }
-            longest = std::max(longest, lanes[(size_t)l].size());
-        }
-        const int words = (int)((longest + 3) / 4);
-        for (auto &v : lanes) v.resize((size_t)4 * words, (uint8_t)zero);
-        std::vector<uint8_t> flat;
-        for (int m = 0; m < words; m++)
-            for (int l = 0; l < 64; l++)
-                for (int b = 0; b < 4; b++) flat.push_back(lanes[(size_t)l][(size_t)4 * m + b]);
-        sc.list.push_back(std::move(flat));
-        if (words > 15) {
-            sc.n_chunks = -1;   // does not fit the format: the caller takes another layout
-            return sc;
-        }
-        sc.chunk_words[c / 8] |= (uint32_t)words << (4 * (c % 8));
-        sc.list_words += words;
-    }
-    return sc;
-}
-
 // map_of_type == nullptr: map indices are left 0 (used only for sizing).
 dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepared &out, const IntraCtx &ctx)
 {
@@ -465,11 +408,7 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
     }
     if (h.intra_form == kFormStream) {
         std::copy(sc.words.begin(), sc.words.end(), blob.begin() + h.off_pair);
-        size_t o = (size_t)h.off_slist;
-        for (const std::vector<uint8_t> &v : sc.list) {
-            if (!v.empty()) std::memcpy(&blob[o], v.data(), v.size());
-            o += v.size() / 4;
-        }
+        if (!sc.list.empty()) std::memcpy(&blob[(size_t)h.off_slist], sc.list.data(), sc.list.size());
     } else if (h.intra_form == kFormPairs) {
         for (int p = 0; p < np; p++) blob[(size_t)h.off_pair + p] = pairs[p];
         for (int c = 0; c < h.n_chunks; c++)

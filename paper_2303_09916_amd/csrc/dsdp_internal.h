@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include "dsdp.h"
+#include "pair_stream.h"
 #include <stdint.h>
 
 namespace dsdp {
@@ -120,7 +121,6 @@ struct LigHeader {
 constexpr int kFormPairs = 0;
 constexpr int kFormAtoms = 1;
 constexpr int kFormStream = 2;
-constexpr int kStreamPairs = 127;   // pairs per chunk
 constexpr int kStreamChains = 4;    // chains per workgroup
 constexpr uint32_t kNbrNone = 0xFFu;   // empty partner byte (no pair is both hydrophobic and H-bonding)
 constexpr int kHeaderWords = (int)(sizeof(LigHeader) / 4 + 3) / 4 * 4;
