@@ -139,35 +139,12 @@ dsdp_status validate_ligand(const dsdp_ligand *lig)
     return DSDP_OK;
 }
 
-// Waves per chain by the chain count: what fills `per_cu` waves of every compute unit.
-int waves_for(long chains, long per_cu)
-{
-    return (int)std::max(1L, std::min(4L, per_cu * device_cus() / std::max(1L, chains)));
-}
+Device this_device() { return {device_cus(), device_max_lds()}; }
 
-// Layout of the intra-ligand term for a launch context (all give the same bits, so
-// this only moves speed).  `lists` is the ligand's header with pair lists.
-//  - A chain of one wave takes the pair stream: 4096 chains of a 47-atom ligand with
-//    868 pairs ran 8 steps in 8.0 ms, with pair lists in 9.4, with atom lists in 10.1
-//    (20 atoms: 2.7, 2.9, 3.3).
-//  - Barzilai-Borwein chains of several waves share each evaluation's pairs: lists.
-//  - Other chains of several waves take pair lists, which have every pair in one go,
-//    while all workgroups are resident (47 atoms, 384 chains, 20 steps: 3.5 ms,
-//    stream 4.0), and the stream, which needs half the registers and a fraction of
-//    the LDS, when they would run in rounds (1024 chains: 4.8 ms at three waves,
-//    lists 6.5 at best; 60 atoms, 384 chains: 5.8, lists 6.5).
-//  - Launches that mix ligands and do not fill the device take atom lists, whose
-//    launches need not be split by pair count.
+// choose_layout for a ligand whose header with pair lists is `lists`.
 int choose_intra_form(const IntraCtx &ctx, const LigHeader &lists)
 {
-    if (ctx.form == DSDP_INTRA_ATOMS) return kFormAtoms;
-    const bool by_mix = ctx.form == DSDP_INTRA_AUTO && ctx.mixed;
-    const int waves = ctx.waves > 0 ? ctx.waves : waves_for(ctx.chains, ctx.bb || by_mix ? kListWaves : kStreamWaves);
-    if (waves == 1) return kFormStream;
-    if (by_mix) return kFormAtoms;
-    if (ctx.bb) return kFormPairs;
-    const long per_cu = std::min<long>(device_max_lds() / search_lds_bytes(lists, waves), kListWaves / waves);
-    return per_cu * device_cus() >= ctx.chains ? kFormPairs : kFormStream;
+    return choose_layout(ctx, lists.n_pairs, this_device(), [&](int waves) { return search_lds_bytes(lists, waves); });
 }
 
 IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed)
@@ -433,7 +410,7 @@ dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepa
     }
     for (int i = 0; i < na; i++) fput(h.off_atom_rad + i, xs_radius(xs[i]));
     out.h = h;
-    out.list_words = lists.total_words;
+    out.lists = lists;
     out.blob.swap(blob);
     return DSDP_OK;
 }
@@ -443,10 +420,8 @@ size_t max_blob_words(const dsdp_ligand *lig)
     Prepared a, b;
     // (a pair stream is never larger than the pair lists)
     IntraCtx pairs, atoms;
-    pairs.form = DSDP_INTRA_PAIRS;
-    pairs.waves = 2;
-    pairs.bb = true;
-    atoms.form = DSDP_INTRA_ATOMS;
+    pairs.layout = kFormPairs;
+    atoms.layout = kFormAtoms;
     if (prepare_ligand(lig, nullptr, a, pairs) || prepare_ligand(lig, nullptr, b, atoms)) return 0;
     return (size_t)std::max(a.h.total_words, b.h.total_words);
 }
@@ -623,7 +598,7 @@ dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains,
     // wave does all of it (more would idle); pair lists spread its pairs over
     // the waves
     if (w == 0 && prm && prm->optimizer == DSDP_OPT_BB && h.intra_form != kFormPairs) w = 1;
-    if (w == 0) w = waves_for(n_chains, h.intra_form == kFormStream ? kStreamWaves : kListWaves);
+    if (w == 0) w = waves_for(n_chains, h.intra_form == kFormStream ? kStreamWaves : kListWaves, device_cus());
     const size_t cap = device_max_lds();
     while (w > 1 && search_lds_bytes(h, w) > cap) w--;
     if (search_lds_bytes(h, w) > cap)
@@ -1223,13 +1198,12 @@ dsdp_status tune_dock(const dsdp_grids_s *g, const dsdp_ligand *lig, const dsdp_
     dsdp_status mst = DSDP_OK;
     // the layout of a candidate
     auto layout = [&](const DockCandidate &dc) -> const Prepared * {
-        if (pl.h.intra_form == kFormPairs && dc.form == DSDP_INTRA_PAIRS && dc.waves > 1) return &pl;
-        if (pl.h.intra_form == kFormStream && dc.form == DSDP_INTRA_PAIRS && dc.waves == 1) return &pl;
         IntraCtx ctx;
         ctx.form = dc.form;
         ctx.waves = dc.waves;
         ctx.chains = n_chains;
         ctx.bb = prm->optimizer == DSDP_OPT_BB;
+        if (choose_intra_form(ctx, pl.lists) == pl.h.intra_form) return &pl;
         if ((mst = prepare_ligand(lig, g->map_of_type, alt, ctx))) return nullptr;
         return &alt;
     };
@@ -1661,10 +1635,9 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
     for (int l = 0; l < n_ligs; l++) {
         if (tune) {
             IntraCtx ctx;
-            ctx.form = DSDP_INTRA_PAIRS;
-            ctx.waves = 1;
+            ctx.layout = kFormStream;
             st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], ctx);
-            ctx.form = DSDP_INTRA_ATOMS;
+            ctx.layout = kFormAtoms;
             if (!st) st = prepare_ligand(&ligs[l], g->map_of_type, atoms[(size_t)l], ctx);
         } else {
             st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], intra_ctx(prm, (long)n_ligs * n_chains, true));
@@ -1674,7 +1647,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
             snprintf(msg, sizeof msg, "ligand %d: %s", l, g_error.c_str());
             return fail(st, "%s", msg);
         }
-        words += tune ? (size_t)std::max(pls[(size_t)l].list_words, atoms[(size_t)l].h.total_words)
+        words += tune ? (size_t)std::max(pls[(size_t)l].lists.total_words, atoms[(size_t)l].h.total_words)
                       : max_blob_words(&ligs[l]);
     }
     const long n_slots = (long)n_ligs * n_chains;

@@ -4,6 +4,7 @@
 
 #include "../../include/dsdp.h"
 #include "dsdp_internal.h"
+#include "layout.h"
 
 #include <string>
 #include <vector>
@@ -38,22 +39,9 @@ struct Prepared {
     LigHeader h;
     std::vector<uint32_t> blob;
     std::vector<int> map_index;   // per atom
-    int list_words = 0;           // blob words with pair lists, whatever the layout
-};
-// Where a prepared ligand will run: the caller's layout request
-// (DSDP_INTRA_*) and waves per chain (0: by the chain count), the chains of the
-// launch and whether the launch mixes ligands.
-struct IntraCtx {
-    int form = DSDP_INTRA_AUTO;
-    int waves = 0;
-    long chains = 1;
-    bool mixed = false;
-    bool bb = false;   // Barzilai-Borwein: a chain's waves share each evaluation's pairs
+    LigHeader lists;              // the header it has with pair lists, whatever the layout
 };
 IntraCtx intra_ctx(const dsdp_params *prm, long chains, bool mixed);
-// Waves per compute unit that the search's launches aim at: pair and atom lists,
-// pair stream (what their registers let a unit hold).
-constexpr long kListWaves = 8, kStreamWaves = 12;
 int choose_intra_form(const IntraCtx &ctx, const LigHeader &lists);   // kForm*
 dsdp_status prepare_ligand(const dsdp_ligand *lig, const int *map_of_type, Prepared &out, const IntraCtx &ctx);
 // blob words of the larger of the two forms (workspace sizing without params); 0 on invalid input

@@ -4,7 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include "dsdp.h"
-#include "pair_stream.h"
+#include "layout.h"
 #include <stdint.h>
 
 namespace dsdp {
@@ -96,7 +96,7 @@ struct LigHeader {
     int32_t off_plist;       // uint4[n_chunks][64]: per gather lane, 8 u16 entries (pair | sign << 15) per chunk
     int32_t n_chunks;        // chunks of 8 entries per gather lane
     int32_t lanes_per_atom;  // 2 when n_atoms <= 32 (lanes a and a + 32 split atom a's list), else 1
-    int32_t intra_form;      // kFormPairs or kFormAtoms (how the intra-ligand term is laid out)
+    int32_t intra_form;      // kForm*: how the intra-ligand term is laid out
     int32_t nbr_words;       // atom lists: words of packed partner bytes per lane
     int32_t off_nbr;         // atom lists: uint32[nbr_words][64], byte = partner | hydrophobic << 6 | hbond << 7
     int32_t off_atom_rad;    // float[n_atoms] XS radius (every layout)
@@ -108,20 +108,6 @@ struct LigHeader {
     int32_t total_words;     // multiple of 4
 };
 
-// Layouts of the intra-ligand term.  Pair lists: lane l evaluates pairs
-// l + 64 k once and stores each pair's force in LDS; every atom then gathers the
-// forces of its pairs.  Atom lists: a lane owns an atom (or half of its partners
-// when there are at most 32 atoms) and evaluates each of the atom's pairs from
-// its own side, so every pair is evaluated twice but nothing per pair is kept
-// in LDS.  The second trades arithmetic for LDS and registers; which one a ligand
-// uses depends on its shape only (choose_intra_form).
-// The pair stream is the pair lists' arithmetic for chains of one wave each: the
-// pairs come in chunks whose forces fit 2 KB, and several chains of a workgroup
-// share the ligand, so that LDS holds enough chains to fill the chip.
-constexpr int kFormPairs = 0;
-constexpr int kFormAtoms = 1;
-constexpr int kFormStream = 2;
-constexpr int kStreamChains = 4;    // chains per workgroup
 constexpr uint32_t kNbrNone = 0xFFu;   // empty partner byte (no pair is both hydrophobic and H-bonding)
 constexpr int kHeaderWords = (int)(sizeof(LigHeader) / 4 + 3) / 4 * 4;
 // The fragments follow the header, at an offset that kernels know: per fragment two

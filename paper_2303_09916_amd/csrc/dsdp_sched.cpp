@@ -414,11 +414,11 @@ dsdp_status dsdp_sched_submit(dsdp_sched s, int32_t receptor_id, const dsdp_liga
     const bool choose = s->prm.intra_form == DSDP_INTRA_AUTO && s->prm.waves_per_chain == 0;
     IntraCtx ctx = intra_ctx(&s->prm, s->capacity, true);
     if (choose) {
-        ctx.waves = 1;
+        ctx.layout = kFormStream;
         st = prepare_ligand(lig, s->receptors[(size_t)receptor_id].map_of_type, q->stream, ctx);
         if (st) return st;
         if (q->stream.h.intra_form != kFormStream) q->stream = Prepared();
-        ctx.form = DSDP_INTRA_ATOMS;
+        ctx.layout = kFormAtoms;
     }
     st = prepare_ligand(lig, s->receptors[(size_t)receptor_id].map_of_type, q->pl, ctx);
     if (st) return st;

@@ -1,0 +1,92 @@
+// Rules for the layout of a ligand's intra-ligand term and the waves of its chains:
+// plain C++, no device code, so they can be unit-tested on the host.  Every choice
+// gives the same bits, so the rules only move speed.  Private to the library.
+#pragma once
+
+#include "../../include/dsdp.h"
+#include "pair_stream.h"
+
+#include <algorithm>
+#include <cstddef>
+
+namespace dsdp {
+
+// Layouts of the intra-ligand term.  Pair lists: lane l evaluates pairs
+// l + 64 k once and stores each pair's force in LDS; every atom then gathers the
+// forces of its pairs.  Atom lists: a lane owns an atom (or half of its partners
+// when there are at most 32 atoms) and evaluates each of the atom's pairs from
+// its own side, so every pair is evaluated twice but nothing per pair is kept
+// in LDS.  Pair stream: the pair lists' arithmetic in chunks of kStreamPairs pairs,
+// whose forces fit 2 KB, so that a compute unit holds more chains; chains of one wave
+// share the ligand among up to kStreamChains of a workgroup.
+constexpr int kFormPairs = 0;
+constexpr int kFormAtoms = 1;
+constexpr int kFormStream = 2;
+constexpr int kStreamChains = 4;    // chains per workgroup
+
+namespace host {
+
+// Where a prepared ligand will run: the caller's layout request
+// (DSDP_INTRA_*) and waves per chain (0: by the chain count), the chains of the
+// launch and whether the launch mixes ligands.
+struct IntraCtx {
+    int form = DSDP_INTRA_AUTO;
+    int waves = 0;
+    long chains = 1;
+    bool mixed = false;
+    bool bb = false;   // Barzilai-Borwein: a chain's waves share each evaluation's pairs
+    int layout = -1;   // kForm*: this layout, whatever the rule
+};
+// Waves per compute unit that the search's launches aim at: pair and atom lists,
+// pair stream (what their registers let a unit hold).
+constexpr long kListWaves = 8, kStreamWaves = 12;
+
+// Compute units and the LDS a workgroup may use.
+struct Device {
+    long cus;
+    size_t max_lds;
+};
+
+// Waves per chain by the chain count: what fills `per_cu` waves of every compute unit.
+inline int waves_for(long chains, long per_cu, long cus)
+{
+    return (int)std::max(1L, std::min(4L, per_cu * cus / std::max(1L, chains)));
+}
+
+// Chains with pair lists that the device holds at once, of `waves` waves and `lds`
+// bytes each.
+inline long resident_lists(size_t lds, int waves, const Device &dev)
+{
+    return std::min<long>((long)(dev.max_lds / lds), kListWaves / waves) * dev.cus;
+}
+
+// Layout of the intra-ligand term for a launch context; lists_lds(waves): the LDS of a
+// workgroup of the ligand with pair lists.
+//  - Pair lists have every pair in one go, the stream has chunks one after the other and
+//    needs half the registers and a fraction of the LDS: lists while all workgroups are
+//    resident, the stream when they would run in rounds.  Several waves per chain (BFGS, 47
+//    atoms): 384 chains, 20 steps 3.5 and 4.0 ms; 1024 chains 6.5 and 4.8 at three waves.
+//    One wave (Barzilai-Borwein, 10 steps): 47 atoms, 1024 chains 6.7 and 8.2 ms, 1300
+//    chains (in rounds) 13.2 and 9.4; 33 atoms, 2048 chains 5.5 and 6.0, 2500 chains 9.2
+//    and 7.5.
+//  - One wave and a single chunk of pairs: the stream, which is one go too (12 atoms, 384
+//    to 2048 chains: 2.8 to 3.2 ms, lists 3.0 to 3.6).
+//  - Barzilai-Borwein chains of several waves share each evaluation's pairs: lists.
+//  - Launches that mix ligands take the stream from one wave per chain on (by
+//    kListWaves), else atom lists, whose launches need not be split by pair count.
+template <typename ListsLds>
+int choose_layout(const IntraCtx &ctx, int n_pairs, const Device &dev, ListsLds lists_lds)
+{
+    if (ctx.layout >= 0) return ctx.layout;
+    if (ctx.form == DSDP_INTRA_ATOMS) return kFormAtoms;
+    const bool by_mix = ctx.form == DSDP_INTRA_AUTO && ctx.mixed;
+    const int waves = ctx.waves > 0 ? ctx.waves
+                                    : waves_for(ctx.chains, ctx.bb || by_mix ? kListWaves : kStreamWaves, dev.cus);
+    if (by_mix) return waves == 1 ? kFormStream : kFormAtoms;
+    if (waves == 1 && n_pairs <= kStreamPairs) return kFormStream;
+    if (waves > 1 && ctx.bb) return kFormPairs;
+    return ctx.chains <= resident_lists(lists_lds(waves), waves, dev) ? kFormPairs : kFormStream;
+}
+
+}  // namespace host
+}  // namespace dsdp

@@ -1,0 +1,71 @@
+// Host unit check of the layout rules on a device of 256 compute units with 160 KB of
+// LDS each.  Built and run by tests/test_layout.py.
+#include "layout.h"
+
+#include <cstdio>
+
+using namespace dsdp;
+using namespace dsdp::host;
+
+static int failures = 0;
+#define CHECK(c)                                                                       \
+    do {                                                                               \
+        if (!(c)) {                                                                    \
+            std::fprintf(stderr, "layout check failed: %s (line %d)\n", #c, __LINE__); \
+            failures++;                                                                \
+        }                                                                              \
+    } while (0)
+
+static const Device kDev{256, 160 << 10};
+
+static IntraCtx ctx(int form, int waves, long chains, bool mixed = false, bool bb = false)
+{
+    IntraCtx c;
+    c.form = form;
+    c.waves = waves;
+    c.chains = chains;
+    c.mixed = mixed;
+    c.bb = bb;
+    return c;
+}
+
+int main()
+{
+    const int AUTO = DSDP_INTRA_AUTO, PAIRS = DSDP_INTRA_PAIRS, ATOMS = DSDP_INTRA_ATOMS;
+    // a ligand whose pair lists leave four one-wave and two four-wave workgroups on a unit
+    auto lds = [](int waves) { return (size_t)25000 + 13000 * (size_t)waves; };
+    auto pick = [&](const IntraCtx &c, int n_pairs = 868) { return choose_layout(c, n_pairs, kDev, lds); };
+
+    CHECK(waves_for(1, 8, 256) == 4 && waves_for(683, 8, 256) == 2 && waves_for(1025, 8, 256) == 1);
+    CHECK(waves_for(1024, 12, 256) == 3 && waves_for(1536, 12, 256) == 2 && waves_for(1537, 12, 256) == 1);
+    CHECK(resident_lists(lds(1), 1, kDev) == 1024 && resident_lists(lds(4), 4, kDev) == 512);
+    CHECK(resident_lists(4000, 1, kDev) == 2048 && resident_lists(4000, 3, kDev) == 512);
+
+    // one wave per chain: lists while all workgroups are resident, then the stream
+    for (bool bb : {false, true})
+        for (int form : {AUTO, PAIRS}) {
+            CHECK(pick(ctx(form, 1, 9, false, bb)) == kFormPairs);
+            CHECK(pick(ctx(form, 1, 1024, false, bb)) == kFormPairs);
+            CHECK(pick(ctx(form, 1, 1025, false, bb)) == kFormStream);
+            CHECK(pick(ctx(form, 1, 1 << 20, false, bb)) == kFormStream);
+        }
+    // a single chunk of pairs: the stream at once
+    CHECK(pick(ctx(AUTO, 1, 9), kStreamPairs) == kFormStream && pick(ctx(AUTO, 1, 9), kStreamPairs + 1) == kFormPairs);
+    // several waves: the same rule for BFGS; lists for Barzilai-Borwein
+    CHECK(pick(ctx(AUTO, 0, 512)) == kFormPairs && pick(ctx(AUTO, 0, 513)) == kFormStream);
+    CHECK(pick(ctx(PAIRS, 4, 512)) == kFormPairs && pick(ctx(PAIRS, 4, 4096)) == kFormStream);
+    CHECK(pick(ctx(AUTO, 4, 4096, false, true)) == kFormPairs && pick(ctx(PAIRS, 2, 4096, false, true)) == kFormPairs);
+    // several ligands: atom lists until a wave per chain fills the device
+    CHECK(pick(ctx(AUTO, 0, 1024, true)) == kFormAtoms && pick(ctx(AUTO, 0, 1025, true)) == kFormStream);
+    CHECK(pick(ctx(AUTO, 1, 9, true)) == kFormStream && pick(ctx(AUTO, 2, 9000, true)) == kFormAtoms);
+    // what is asked for
+    CHECK(pick(ctx(ATOMS, 1, 9)) == kFormAtoms && pick(ctx(ATOMS, 0, 9000, true)) == kFormAtoms);
+    for (int f : {kFormPairs, kFormAtoms, kFormStream}) {
+        IntraCtx c = ctx(ATOMS, 1, 4096, true, true);
+        c.layout = f;
+        CHECK(pick(c) == f);
+    }
+    if (failures) return 1;
+    std::printf("the rules are as specified\n");
+    return 0;
+}

@@ -1,0 +1,48 @@
+"""GPU: launches on both sides of the layout rules' limits give the same bits."""
+import numpy as np
+import pytest
+
+import paper_2303_09916_amd as D
+from synth import make_ligand, make_receptor, make_box, PALETTE_T9
+from helpers import box32
+
+pytestmark = pytest.mark.gpu
+
+PAIRS, ATOMS = 1, 2
+
+
+@pytest.fixture(scope="module")
+def grid():
+    import gpu_common as gc
+    rec = make_receptor(300, radius=12.0, seed=4)
+    return gc.GpuGrid(rec.xyz, rec.types, box32(make_box(rec.pocket, 14.0, spacing=0.5)), PALETTE_T9)
+
+
+def params(form, waves, **over):
+    return D.dsdp_params_default(intra_form=form, waves_per_chain=waves, tune=0, **over)
+
+
+def chain_bits(grid, lig, n_chains, steps, p):
+    import gpu_common as gc
+    poses, xyz, chains, st = gc.gpu_dock(grid, lig, n_chains, steps, 11, 5, p)
+    rec = np.array([list(c.pos) + list(c.quat) + list(c.tors) + [c.e_total, c.e_inter, c.e_intra, c.e_wall]
+                    for c in chains], np.float32)
+    return rec, np.array([p_.chain for p_ in poses]), xyz, st.pose_evals, st.accepted
+
+
+def same(a, b):
+    return all(np.array_equal(x, y, equal_nan=x.dtype.kind == "f") for x, y in zip(map(np.asarray, a), map(np.asarray, b)))
+
+
+@pytest.mark.parametrize("atoms,tors", [(5, 0), (8, 2), (19, 4), (20, 5), (26, 6), (33, 8), (47, 9), (64, 31)])
+def test_one_wave_lists_and_stream(grid, atoms, tors):
+    """One wave per chain: pair lists for few chains, the pair stream for more than are
+    resident with lists, both optimisers; the first chains of the large launch are
+    those of the small one."""
+    lig = make_ligand(atoms, tors, seed=atoms, palette=PALETTE_T9)
+    for over in ({}, {"optimizer": D.DSDP_OPT_BB, "bb_iters": 12}):
+        few = chain_bits(grid, lig, 9, 1, params(PAIRS, 1, **over))
+        many = chain_bits(grid, lig, 2100, 1, params(PAIRS, 1, **over))
+        assert same(few, chain_bits(grid, lig, 9, 1, params(ATOMS, 1, **over)))
+        assert same(many, chain_bits(grid, lig, 2100, 1, params(ATOMS, 1, **over)))
+        assert np.array_equal(few[0], many[0][:9])

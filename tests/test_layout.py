@@ -1,0 +1,22 @@
+"""The rules that choose the layout of the intra-ligand term, on the host: pair lists
+while all workgroups are resident, the pair stream beyond, atom lists where asked for
+or where small launches mix ligands."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_layout_rules(tmp_path):
+    exe = str(tmp_path / "layout_check")
+    env = {k: v for k, v in os.environ.items() if k != "LD_PRELOAD"}
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-I", os.path.join(ROOT, "paper_2303_09916_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "layout_check.cpp"), "-o", exe], check=True, env=env)
+    r = subprocess.run([exe], capture_output=True, text=True, env=env)
+    assert r.returncode == 0, r.stderr
+    assert "as specified" in r.stdout
