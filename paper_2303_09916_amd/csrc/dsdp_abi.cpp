@@ -1038,7 +1038,9 @@ dsdp_status dsdp_eval_poses(dsdp_grids g, const dsdp_ligand *lig, const float *d
     dsdp_status st = check_params(prm);
     if (st) return st;
     Prepared pl;
-    st = prepare_ligand(lig, g->map_of_type, pl, intra_ctx(prm, n_poses, false));
+    IntraCtx ctx = intra_ctx(prm, n_poses, false);
+    ctx.score = true;
+    st = prepare_ligand(lig, g->map_of_type, pl, ctx);
     if (st) return st;
     const SearchWs w = search_ws(pl.h, std::max(n_poses, 1));
     if (!d_ws || ws_bytes < w.total) return fail(DSDP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", w.total);

@@ -35,6 +35,7 @@ struct IntraCtx {
     long chains = 1;
     bool mixed = false;
     bool bb = false;   // Barzilai-Borwein: a chain's waves share each evaluation's pairs
+    bool score = false;   // poses scored once each, a wave per pose whatever `waves` says
     int layout = -1;   // kForm*: this layout, whatever the rule
 };
 // Waves per compute unit that the search's launches aim at: pair and atom lists,
@@ -72,6 +73,11 @@ inline long resident_lists(size_t lds, int waves, const Device &dev)
 //  - One wave and a single chunk of pairs: the stream, which is one go too (12 atoms, 384
 //    to 2048 chains: 2.8 to 3.2 ms, lists 3.0 to 3.6).
 //  - Barzilai-Borwein chains of several waves share each evaluation's pairs: lists.
+//  - Scoring prepares the ligand in every call and is bound by that up to some 20 poses a
+//    unit: pair lists while resident, then atom lists, the smaller sections (5000 poses a
+//    call: 33 atoms 35.5 us, lists 39.8, stream 41.8; 60 atoms 82, 144 and 85), and
+//    the stream where the kernel is what counts (20000 poses: 33 atoms 60 us, lists 64, atoms
+//    76; 60 atoms 125, 471 and 126).
 //  - Launches that mix ligands take the stream from one wave per chain on (by
 //    kListWaves), else atom lists, whose launches need not be split by pair count.
 template <typename ListsLds>
@@ -79,6 +85,11 @@ int choose_layout(const IntraCtx &ctx, int n_pairs, const Device &dev, ListsLds 
 {
     if (ctx.layout >= 0) return ctx.layout;
     if (ctx.form == DSDP_INTRA_ATOMS) return kFormAtoms;
+    if (ctx.score) {
+        if (ctx.chains > 20 * dev.cus) return kFormStream;
+        if (ctx.chains <= resident_lists(lists_lds(1), 1, dev)) return kFormPairs;
+        return ctx.form == DSDP_INTRA_AUTO ? kFormAtoms : kFormStream;
+    }
     const bool by_mix = ctx.form == DSDP_INTRA_AUTO && ctx.mixed;
     const int waves = ctx.waves > 0 ? ctx.waves
                                     : waves_for(ctx.chains, ctx.bb || by_mix ? kListWaves : kStreamWaves, dev.cus);

@@ -58,6 +58,18 @@ int main()
     // several ligands: atom lists until a wave per chain fills the device
     CHECK(pick(ctx(AUTO, 0, 1024, true)) == kFormAtoms && pick(ctx(AUTO, 0, 1025, true)) == kFormStream);
     CHECK(pick(ctx(AUTO, 1, 9, true)) == kFormStream && pick(ctx(AUTO, 2, 9000, true)) == kFormAtoms);
+    // scoring: lists while resident, then atom lists (unless pairs are asked for), then the
+    // stream; the waves asked for play no part
+    for (int waves = 0; waves <= 4; waves++) {
+        auto score = [&](int form, long poses) {
+            IntraCtx c = ctx(form, waves, poses);
+            c.score = true;
+            return pick(c);
+        };
+        CHECK(score(AUTO, 1) == kFormPairs && score(AUTO, 1024) == kFormPairs && score(PAIRS, 1024) == kFormPairs);
+        CHECK(score(AUTO, 1025) == kFormAtoms && score(AUTO, 5120) == kFormAtoms && score(PAIRS, 5120) == kFormStream);
+        CHECK(score(AUTO, 5121) == kFormStream && score(PAIRS, 5121) == kFormStream && score(ATOMS, 1 << 20) == kFormAtoms);
+    }
     // what is asked for
     CHECK(pick(ctx(ATOMS, 1, 9)) == kFormAtoms && pick(ctx(ATOMS, 0, 9000, true)) == kFormAtoms);
     for (int f : {kFormPairs, kFormAtoms, kFormStream}) {

@@ -46,3 +46,33 @@ def test_one_wave_lists_and_stream(grid, atoms, tors):
         assert same(few, chain_bits(grid, lig, 9, 1, params(ATOMS, 1, **over)))
         assert same(many, chain_bits(grid, lig, 2100, 1, params(ATOMS, 1, **over)))
         assert np.array_equal(few[0], many[0][:9])
+
+
+@pytest.mark.parametrize("n", [1, 1000, 2049, 5120, 5121])
+@pytest.mark.parametrize("atoms,tors", [(20, 5), (47, 9)])
+def test_scoring_layout(grid, atoms, tors, n):
+    """Scoring takes its layout from the poses alone (pair lists, then atom lists, then the
+    stream), not from the waves asked for, which it does not use; the same bits each
+    time.  The layout is read from the ligand's header at the start of the workspace."""
+    import gpu_common as gc
+    torch = grid.torch
+    L = D.Ligand.from_synth(make_ligand(atoms, tors, seed=atoms, palette=PALETTE_T9))
+    P = torch.rand((n, L.nx), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    P[:, :3] = P[:, :3] * 13.0 + torch.tensor(np.asarray(grid.origin, np.float32), device="cuda")
+    ws = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n))
+
+    def score(form, waves):
+        e, g = torch.empty((n, 4), device="cuda"), torch.empty((n, L.D), device="cuda")
+        D.dsdp_eval_poses(grid.handle, L, P, n, e, g, None, ws, params(form, waves))
+        return e.cpu().numpy(), g.cpu().numpy(), int(ws[:60].view(torch.int32)[14])
+
+    ref = score(ATOMS, 1)
+    assert ref[2] == 1
+    auto = [score(0, waves) for waves in (0, 1, 2, 4)]
+    assert len({a[2] for a in auto}) == 1
+    if n in (1, 1000):
+        assert auto[0][2] == 0
+    if n == 5121:
+        assert auto[0][2] == 2
+    for got in auto + [score(PAIRS, 1), score(PAIRS, 3)]:
+        assert same(got[:2], ref[:2])
