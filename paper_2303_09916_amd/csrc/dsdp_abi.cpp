@@ -1084,8 +1084,15 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
         return fail(DSDP_ERR_INVALID_ARG, "device array is NULL");
     dsdp_status st = check_params(prm);
     if (st) return st;
+    dsdp_params p;
+    if (prm)
+        p = *prm;
+    else
+        dsdp_params_default(&p);
+    if (p.waves_per_chain == 0 && p.intra_form == DSDP_INTRA_AUTO && p.optimizer == DSDP_OPT_BFGS)
+        p.waves_per_chain = refine_waves(n_poses, device_cus());
     Prepared pl;
-    st = prepare_ligand(lig, g->map_of_type, pl, intra_ctx(prm, n_poses, false));
+    st = prepare_ligand(lig, g->map_of_type, pl, intra_ctx(&p, n_poses, false));
     if (st) return st;
     const SearchWs w = search_ws(pl.h, std::max(n_poses, 1));
     if (!d_ws || ws_bytes < w.total) return fail(DSDP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", w.total);
@@ -1097,14 +1104,14 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
     if (st) return st;
     int waves = 1;
     size_t lds = 0;
-    st = pick_waves(prm, pl.h, n_poses, waves);
+    st = pick_waves(&p, pl.h, n_poses, waves);
     int cls = 0;
     if (!st) st = launch_shape({&pl.h}, n_poses, waves, lds, cls);
     if (st) return st;
     GridView view;
     st = device_view(g, ws, w, nullptr, s, view);
     if (st) return st;
-    HIP_TRY(launch_local_opt((const uint32_t *)(ws + w.arena), pl.h.total_words, pl.h, view, to_search(prm), cls, waves,
+    HIP_TRY(launch_local_opt((const uint32_t *)(ws + w.arena), pl.h.total_words, pl.h, view, to_search(&p), cls, waves,
                              d_poses_in, n_poses, d_poses_out, d_energy, d_evals, s),
             "local-opt launch");
     return DSDP_OK;

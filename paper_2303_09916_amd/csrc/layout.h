@@ -61,6 +61,16 @@ inline long resident_lists(size_t lds, int waves, const Device &dev)
     return std::min<long>((long)(dev.max_lds / lds), kListWaves / waves) * dev.cus;
 }
 
+// Waves per pose of a BFGS refinement whose waves are left to the library (0: by the
+// rule of the searches).  Poses take 2 to some 100 evaluations and the launch ends on the
+// slowest, which two waves shorten; one wave from where the extra waves cost more (2500 poses:
+// 33 atoms 0.90 ms, one wave 1.10, 60 atoms 1.34 and 2.11; 4000 poses: 0.80 and 0.86, 1.86
+// and 1.97; 6000 poses: 1.04 and 1.09, 2.57 and 2.55, 54 atoms 2.14 and 2.02).
+inline int refine_waves(long poses, long cus)
+{
+    return poses > kStreamWaves / 2 * cus && poses <= 16 * cus ? 2 : 0;
+}
+
 // Layout of the intra-ligand term for a launch context; lists_lds(waves): the LDS of a
 // workgroup of the ligand with pair lists.
 //  - Pair lists have every pair in one go, the stream has chunks one after the other and

@@ -70,6 +70,9 @@ int main()
         CHECK(score(AUTO, 1025) == kFormAtoms && score(AUTO, 5120) == kFormAtoms && score(PAIRS, 5120) == kFormStream);
         CHECK(score(AUTO, 5121) == kFormStream && score(PAIRS, 5121) == kFormStream && score(ATOMS, 1 << 20) == kFormAtoms);
     }
+    // refinements: two waves where a search's chains would take one, up to 16 poses a unit
+    CHECK(refine_waves(1536, 256) == 0 && refine_waves(1537, 256) == 2 && refine_waves(4096, 256) == 2 &&
+          refine_waves(4097, 256) == 0 && refine_waves(0, 256) == 0);
     // what is asked for
     CHECK(pick(ctx(ATOMS, 1, 9)) == kFormAtoms && pick(ctx(ATOMS, 0, 9000, true)) == kFormAtoms);
     for (int f : {kFormPairs, kFormAtoms, kFormStream}) {

@@ -76,3 +76,19 @@ def test_scoring_layout(grid, atoms, tors, n):
         assert auto[0][2] == 2
     for got in auto + [score(PAIRS, 1), score(PAIRS, 3)]:
         assert same(got[:2], ref[:2])
+
+
+@pytest.mark.parametrize("n", [1536, 1537, 4096, 4097])
+@pytest.mark.parametrize("atoms,tors", [(12, 2), (60, 12)])
+def test_refinement_waves(grid, atoms, tors, n):
+    """The waves that the library picks for a refinement, on both sides of its limits."""
+    import gpu_common as gc
+    lig = make_ligand(atoms, tors, seed=atoms, palette=PALETTE_T9)
+    L = D.Ligand.from_synth(lig)
+    rng = np.random.default_rng(n)
+    P = np.zeros((n, L.nx), np.float32)
+    P[:, :3] = np.asarray(grid.origin) + rng.uniform(0, 13.0, (n, 3))
+    P[:, 3:7] = rng.normal(size=(n, 4))
+    P[:, 7:] = rng.uniform(-np.pi, np.pi, (n, L.n_tors))
+    ref = gc.gpu_local_opt(grid, lig, P, params(ATOMS, 1, bfgs_iters=3))
+    assert same(gc.gpu_local_opt(grid, lig, P, params(0, 0, bfgs_iters=3)), ref)
