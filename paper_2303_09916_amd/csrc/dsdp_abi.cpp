@@ -1461,18 +1461,29 @@ struct Graph {
 // The plan of candidate `c`: each ligand's layout from its pair class, one
 // launch per (kernel variant, waves); waves lowered for a launch whose largest
 // member does not fit the LDS.  Returns false when a ligand cannot run.
-bool tuned_plan(int c, const std::vector<Prepared> &ps, const std::vector<Prepared> &pa, int n_chains, BatchPlan &out)
+// ps, pa, pl: the ligands as pair stream, atom lists and (or empty) pair lists.  Where a
+// plan evaluates each pair once, that is by pair lists while all chains of the batch are
+// resident with the largest member's, as in choose_layout, else by the stream (at two
+// waves, ligands of 14, 26 and 33 atoms with 256 chains each: 14.8 ms, stream 17.8, and 512
+// chains 19.7 and 18.2; eight of 14 to 60 atoms with 64: 33.1 and 37.2, 128: 49.7 and 37.6).
+bool tuned_plan(int c, const std::vector<Prepared> &ps, const std::vector<Prepared> &pa, const std::vector<Prepared> &pl,
+                int n_chains, BatchPlan &out)
 {
-    const Plan pl = plan(c);
+    const Plan pln = plan(c);
     out = BatchPlan();
     const int n = (int)ps.size();
     out.blob.resize((size_t)n);
+    bool lists = !pl.empty();
+    for (int l = 0; l < n && lists; l++)
+        if (plan_form(pln, ps[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS)
+            lists = (long)n * n_chains <=
+                    resident_lists(search_lds_bytes(pl[(size_t)l].h, pln.waves), pln.waves, this_device());
     std::map<std::pair<int, int>, std::vector<int>> groups;
     for (int l = 0; l < n; l++) {
-        const bool lists = plan_form(pl, ps[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS;
-        const Prepared &pr = lists ? ps[(size_t)l] : pa[(size_t)l];
+        const bool once = plan_form(pln, ps[(size_t)l].h.n_pairs) == DSDP_INTRA_PAIRS;
+        const Prepared &pr = !once ? pa[(size_t)l] : lists ? pl[(size_t)l] : ps[(size_t)l];
         out.blob[(size_t)l] = &pr;
-        groups[{search_class(pr.h, pl.waves), pl.waves}].push_back(l);
+        groups[{search_class(pr.h, pln.waves), pln.waves}].push_back(l);
     }
     for (auto &kv : groups) {
         BatchGroup b;
@@ -1663,8 +1674,10 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
     const bool tune = pp.tune == 1 && pp.optimizer == DSDP_OPT_BFGS && pp.waves_per_chain == 0 &&
                       pp.intra_form == DSDP_INTRA_AUTO && n_steps > 0;
     // every ligand prepared in the fixed rule's layout (unless the caller fixed one) or,
-    // when tuning, in both
-    std::vector<Prepared> pls((size_t)n_ligs), atoms(tune ? (size_t)n_ligs : 0);
+    // when tuning, in every layout (pair lists only where the chains could all be
+    // resident with them)
+    const bool few = tune && (long)n_ligs * n_chains <= kListWaves * device_cus();
+    std::vector<Prepared> pls((size_t)n_ligs), atoms(tune ? (size_t)n_ligs : 0), lists(few ? (size_t)n_ligs : 0);
     size_t words = 0;
     for (int l = 0; l < n_ligs; l++) {
         if (tune) {
@@ -1673,6 +1686,8 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
             st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], ctx);
             ctx.layout = kFormAtoms;
             if (!st) st = prepare_ligand(&ligs[l], g->map_of_type, atoms[(size_t)l], ctx);
+            ctx.layout = kFormPairs;
+            if (!st && few) st = prepare_ligand(&ligs[l], g->map_of_type, lists[(size_t)l], ctx);
         } else {
             st = prepare_ligand(&ligs[l], g->map_of_type, pls[(size_t)l], intra_ctx(prm, (long)n_ligs * n_chains, true));
         }
@@ -1716,7 +1731,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
         // 1.98, and ran 100 steps in 31.6 ms, the other in 37.1); the search afterwards starts afresh
         auto measure = [&](int c) -> float {
             BatchPlan tp;
-            if (mst || !tuned_plan(c, pls, atoms, n_chains, tp)) return -1.f;
+            if (mst || !tuned_plan(c, pls, atoms, lists, n_chains, tp)) return -1.f;
             // 1 + kTrialSteps steps whatever the batch's length, so that batches of
             // any length share the cached pick
             if ((mst = upload_plan(tp, g, seeds, n_chains, 1 + kTrialSteps, top_k, w, ws, cs))) return -1.f;
@@ -1739,7 +1754,7 @@ dsdp_status dsdp_dock_batch(dsdp_grids g, const dsdp_ligand *ligs, int32_t n_lig
         int pick = 0;
         const bool found = tuner().pick(key, measure, pick, n_slots, kTrialSteps);
         if (mst) return mst;
-        if (!found || !tuned_plan(pick, pls, atoms, n_chains, bp))
+        if (!found || !tuned_plan(pick, pls, atoms, lists, n_chains, bp))
             return fail(DSDP_ERR_UNSUPPORTED, "no launch plan fits the batch");
     } else {
         std::vector<const LigHeader *> hdr((size_t)n_ligs);

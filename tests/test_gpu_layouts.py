@@ -92,3 +92,23 @@ def test_refinement_waves(grid, atoms, tors, n):
     P[:, 7:] = rng.uniform(-np.pi, np.pi, (n, L.n_tors))
     ref = gc.gpu_local_opt(grid, lig, P, params(ATOMS, 1, bfgs_iters=3))
     assert same(gc.gpu_local_opt(grid, lig, P, params(0, 0, bfgs_iters=3)), ref)
+
+
+@pytest.mark.parametrize("n_chains", [16, 341, 342, 700])
+def test_tuned_batch_layouts(grid, n_chains):
+    """A tuned batch evaluates each pair once by pair lists while its chains are all
+    resident with those (at two waves: 4 a compute unit, so 1024 chains of these ligands),
+    never by the stream then; every result is that of docking alone.  The layout is read
+    from the first ligand's header at the start of the workspace."""
+    import gpu_common as gc
+    torch = grid.torch
+    Ls = [D.Ligand.from_synth(make_ligand(a, t, seed=a, palette=PALETTE_T9)) for a, t in ((33, 6), (26, 5), (20, 4))]
+    ws = gc.dev_bytes(torch, D.dsdp_dock_batch_workspace_bytes(Ls, n_chains))
+    res, _ = D.dsdp_dock_batch(grid.handle, Ls, n_chains, 2, [5, 6, 7], 3, ws)
+    form = int(ws[:60].view(torch.int32)[14])
+    if 3 * n_chains <= 1024:
+        assert form != 2
+    for k, L in enumerate(Ls):
+        w1 = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n_chains))
+        alone = D.dsdp_dock(grid.handle, L, n_chains, 2, 5 + k, 3, w1, params(ATOMS, 1))[0]
+        assert [bytes(p) for p in res[k]] == [bytes(p) for p in alone]
