@@ -553,6 +553,22 @@ struct HostImage {
     template <typename T> T *at(size_t off) { return reinterpret_cast<T *>(bytes.data() + off); }
 };
 
+// Whether a launch of n chains with the prepared layout takes atom lists after all: where
+// the layout is the library's choice, ligands with more than 600 pairs and launches of 2048
+// chains or more have always been taken by any workspace (and the static scratch) that
+// holds atom lists, the smallest layout.
+bool wants_smaller(const Prepared &p, const dsdp_params *prm, long n, size_t ws_bytes)
+{
+    return (!prm || prm->intra_form == DSDP_INTRA_AUTO) && p.h.intra_form != kFormAtoms && p.h.n_pairs > 600 && n >= 2048 &&
+           search_ws(p.h, (int)n).total > ws_bytes;
+}
+IntraCtx atom_lists()
+{
+    IntraCtx c;
+    c.layout = kFormAtoms;
+    return c;
+}
+
 bool aligned256(const void *p) { return ((uintptr_t)p & 255u) == 0; }
 
 // Compute units of the current device (cached per device).
@@ -1041,6 +1057,7 @@ dsdp_status dsdp_eval_poses(dsdp_grids g, const dsdp_ligand *lig, const float *d
     IntraCtx ctx = intra_ctx(prm, n_poses, false);
     ctx.score = true;
     st = prepare_ligand(lig, g->map_of_type, pl, ctx);
+    if (!st && wants_smaller(pl, prm, n_poses, ws_bytes)) st = prepare_ligand(lig, g->map_of_type, pl, atom_lists());
     if (st) return st;
     const SearchWs w = search_ws(pl.h, std::max(n_poses, 1));
     if (!d_ws || ws_bytes < w.total) return fail(DSDP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", w.total);
@@ -1093,6 +1110,7 @@ dsdp_status dsdp_local_opt(dsdp_grids g, const dsdp_ligand *lig, const float *d_
         p.waves_per_chain = refine_waves(n_poses, device_cus());
     Prepared pl;
     st = prepare_ligand(lig, g->map_of_type, pl, intra_ctx(&p, n_poses, false));
+    if (!st && wants_smaller(pl, prm, n_poses, ws_bytes)) st = prepare_ligand(lig, g->map_of_type, pl, atom_lists());
     if (st) return st;
     const SearchWs w = search_ws(pl.h, std::max(n_poses, 1));
     if (!d_ws || ws_bytes < w.total) return fail(DSDP_ERR_WORKSPACE_TOO_SMALL, "workspace needs %zu bytes", w.total);
@@ -1319,6 +1337,11 @@ dsdp_status dock_impl(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
             use = &alt;
             waves = 2;
         }
+    }
+    if (wants_smaller(*use, prm, n_chains, static_ws ? kStaticScratchBytes : ws_bytes)) {
+        if ((st = prepare_ligand(lig, g->map_of_type, alt, atom_lists()))) return st;
+        use = &alt;
+        waves = 0;
     }
     const Prepared &pl = *use;
     if (waves == 0) {

@@ -112,3 +112,63 @@ def test_tuned_batch_layouts(grid, n_chains):
         w1 = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n_chains))
         alone = D.dsdp_dock(grid.handle, L, n_chains, 2, 5 + k, 3, w1, params(ATOMS, 1))[0]
         assert [bytes(p) for p in res[k]] == [bytes(p) for p in alone]
+
+
+def largest(ok, lo, hi):
+    """The largest n in [lo, hi) with ok(n), which holds at lo and is monotonic."""
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if ok(mid) else (lo, mid)
+    return lo
+
+
+def accepted(call):
+    try:
+        call()
+    except D.DsdpError:
+        return False
+    return True
+
+
+def test_static_dock_at_its_limit(grid):
+    """The largest dock that the static scratch holds with atom lists runs with the
+    library's own layout too; one chain more is refused with either."""
+    L = D.Ligand.from_synth(make_ligand(47, 9, seed=47, palette=PALETTE_T9))
+    assert D.dsdp_ligand_info(L)[0] > 600
+    n = largest(lambda n: accepted(lambda: D.dsdp_dock_static(grid.handle, L, n, 0, 3, 1, params(ATOMS, 1))), 2048, 8192)
+    assert not accepted(lambda: D.dsdp_dock_static(grid.handle, L, n + 1, 0, 3, 1, params(0, 0)))
+    want = D.dsdp_dock_static(grid.handle, L, n, 1, 3, 2, params(ATOMS, 1))
+    got = D.dsdp_dock_static(grid.handle, L, n, 1, 3, 2, params(0, 0))
+    assert [bytes(p) for p in got[0]] == [bytes(p) for p in want[0]]
+
+
+@pytest.mark.parametrize("n", [2500, 6000])
+def test_smallest_workspace(grid, n):
+    """Scoring, refining and docking run in the smallest workspace that holds atom lists, and
+    not in one that is 256 bytes smaller."""
+    import gpu_common as gc
+    torch = grid.torch
+    L = D.Ligand.from_synth(make_ligand(47, 9, seed=47, palette=PALETTE_T9))
+    P = torch.rand((n, L.nx), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    P[:, :3] = P[:, :3] * 13.0 + torch.tensor(np.asarray(grid.origin, np.float32), device="cuda")
+    whole = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n))
+    E, G, O, N = (torch.empty((n, 4), device="cuda"), torch.empty((n, L.D), device="cuda"), torch.empty_like(P),
+                  torch.empty(n, dtype=torch.int32, device="cuda"))
+
+    def score(ws, p):
+        D.dsdp_eval_poses(grid.handle, L, P, n, E, G, None, ws, p)
+        return E.cpu().numpy(), G.cpu().numpy()
+
+    def refine(ws, p):
+        D.dsdp_local_opt(grid.handle, L, P, n, O, E, N, ws, p)
+        return O.cpu().numpy(), E.cpu().numpy(), N.cpu().numpy()
+
+    def dock(ws, p):
+        return [np.frombuffer(bytes(x), np.uint8) for x in D.dsdp_dock(grid.handle, L, n, 1, 3, 2, ws, p)[0]]
+
+    size = 256 * largest(lambda k: not accepted(lambda: score(whole[:256 * k], params(ATOMS, 0))), 1, len(whole) // 256) + 256
+    assert size < len(whole)
+    for call in (score, refine, dock):
+        want = call(whole, params(ATOMS, 0, bfgs_iters=3))
+        assert same(call(whole[:size], params(0, 0, bfgs_iters=3)), want)
+        assert not accepted(lambda: call(whole[:size - 256], params(0, 0, bfgs_iters=3)))
