@@ -52,12 +52,13 @@ struct Request {
     int receptor = 0;
     Prepared pl;
     Prepared stream;         // the pair stream of the ligand, where the layout is the library's choice
-    bool has_stream = false; // it is in the pool too, behind pl's blob
+    bool has_stream = false; // it is in the pool too
     int n_chains = 0, n_steps = 0, top_k = 0;
     uint64_t seed = 0;
     int state = kQueued;
     bool cancel = false;
     size_t slot0 = 0, arena_off = 0, arena_bytes = 0;
+    size_t stream_off = 0, stream_bytes = 0;
     int steps_done = 0;
     bool fresh = false;
     int passed_over = 0;     // admission rounds in which it did not fit
@@ -186,6 +187,7 @@ void finish(dsdp_sched s, Request *q, int state)
     if (q->state == kRunning) {
         s->slots.release(q->slot0, (size_t)q->n_chains);
         s->mem.release(q->arena_off, q->arena_bytes);
+        if (q->has_stream) s->mem.release(q->stream_off, q->stream_bytes);
         s->receptors[(size_t)q->receptor].active--;
     }
     q->state = state;
@@ -212,17 +214,9 @@ dsdp_status admit(dsdp_sched s)
         }
         if (blocked) break;
         size_t so = 0, ao = 0;
-        const size_t first = align256(q->pl.blob.size() * 4);
-        size_t ab = first;
+        const size_t ab = align256(q->pl.blob.size() * 4);
         bool ok = s->slots.alloc((size_t)q->n_chains, so);
-        q->has_stream = false;
-        if (ok && !q->stream.blob.empty()) {
-            // both layouts where the pool has room for them, else the first alone
-            const size_t both = first + align256(q->stream.blob.size() * 4);
-            q->has_stream = s->receptors[(size_t)q->receptor].resident && s->mem.alloc(both, ao);
-            if (q->has_stream) ab = both;
-        }
-        if (ok && !q->has_stream && !s->mem.alloc(ab, ao)) {
+        if (ok && !s->mem.alloc(ab, ao)) {
             s->slots.release(so, (size_t)q->n_chains);
             ok = false;
         }
@@ -248,8 +242,11 @@ dsdp_status admit(dsdp_sched s)
         }
         HIP_TRY(hipMemcpyAsync(s->pool + ao, q->pl.blob.data(), q->pl.blob.size() * 4, hipMemcpyHostToDevice, s->stream),
                 "ligand upload");
+        // the pair stream too where the pool has room, once the maps have theirs
+        q->stream_bytes = align256(q->stream.blob.size() * 4);
+        q->has_stream = !q->stream.blob.empty() && s->mem.alloc(q->stream_bytes, q->stream_off);
         if (q->has_stream)
-            HIP_TRY(hipMemcpyAsync(s->pool + ao + first, q->stream.blob.data(), q->stream.blob.size() * 4,
+            HIP_TRY(hipMemcpyAsync(s->pool + q->stream_off, q->stream.blob.data(), q->stream.blob.size() * 4,
                                    hipMemcpyHostToDevice, s->stream),
                     "ligand upload");
         q->slot0 = so;
@@ -496,7 +493,7 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
             const Request *q = s->running[(size_t)m];
             const bool stream = one_wave && q->has_stream;
             const Prepared &pl = stream ? q->stream : q->pl;
-            const size_t off = q->arena_off + (stream ? align256(q->pl.blob.size() * 4) : 0);
+            const size_t off = stream ? q->stream_off : q->arena_off;
             for (int c = 0; c < q->n_chains; c++) {
                 ChainTask t{};
                 t.blob_off = (uint32_t)(off / 4);
