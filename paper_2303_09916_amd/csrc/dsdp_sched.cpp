@@ -52,7 +52,7 @@ struct Request {
     int receptor = 0;
     Prepared pl;
     Prepared stream;         // the pair stream of the ligand, where the layout is the library's choice
-    bool has_stream = false; // it is in the pool too
+    bool has_stream = false; // it is in the pool too (grant_streams)
     int n_chains = 0, n_steps = 0, top_k = 0;
     uint64_t seed = 0;
     int state = kQueued;
@@ -121,6 +121,38 @@ void evict(dsdp_sched s, Receptor &r)
     s->evictions++;
 }
 
+// Pool memory for what a request cannot run without (its ligand, its receptor's maps).
+// The running requests' pair streams lie in what that leaves; they are all given back
+// when it would not be enough otherwise.  No kernel is running between ticks.
+bool alloc_needed(dsdp_sched s, size_t n, size_t &off)
+{
+    if (s->mem.alloc(n, off)) return true;
+    size_t held = 0;
+    for (const Request *q : s->running) held += q->has_stream ? q->stream_bytes : 0;
+    if (held == 0 || s->mem.total - s->mem.used + held < n) return false;
+    for (Request *q : s->running) {
+        if (q->has_stream) s->mem.release(q->stream_off, q->stream_bytes);
+        q->has_stream = false;
+    }
+    return s->mem.alloc(n, off);
+}
+
+// Pair streams of the running requests that have none yet into what the pool has left,
+// from its upper end, so that they do not come between ligands and maps.
+dsdp_status grant_streams(dsdp_sched s)
+{
+    for (Request *q : s->running) {
+        if (q->has_stream || q->stream.blob.empty()) continue;
+        q->stream_bytes = align256(q->stream.blob.size() * 4);
+        if (!s->mem.alloc_high(q->stream_bytes, q->stream_off)) continue;
+        q->has_stream = true;
+        HIP_TRY(hipMemcpyAsync(s->pool + q->stream_off, q->stream.blob.data(), q->stream.blob.size() * 4,
+                               hipMemcpyHostToDevice, s->stream),
+                "ligand upload");
+    }
+    return DSDP_OK;
+}
+
 // Make receptor `id` resident, evicting idle receptors (LRU) when needed.
 // Returns DSDP_OK, DSDP_ERR_BUSY when memory cannot be found now, or an error.
 dsdp_status ensure_resident(dsdp_sched s, int id)
@@ -132,8 +164,8 @@ dsdp_status ensure_resident(dsdp_sched s, int id)
     const size_t wsb = align256(dsdp_build_grids_workspace_bytes((int32_t)r.atoms.size(), &r.box));
     size_t mo = 0, wo = 0;
     for (;;) {
-        bool ok_m = s->mem.alloc(maps, mo);
-        bool ok_w = ok_m && s->mem.alloc(wsb, wo);
+        bool ok_m = alloc_needed(s, maps, mo);
+        bool ok_w = ok_m && alloc_needed(s, wsb, wo);
         if (ok_m && ok_w) break;
         if (ok_m) s->mem.release(mo, maps);
         // evict the least recently used resident receptor with no running request
@@ -216,7 +248,7 @@ dsdp_status admit(dsdp_sched s)
         size_t so = 0, ao = 0;
         const size_t ab = align256(q->pl.blob.size() * 4);
         bool ok = s->slots.alloc((size_t)q->n_chains, so);
-        if (ok && !s->mem.alloc(ab, ao)) {
+        if (ok && !alloc_needed(s, ab, ao)) {
             s->slots.release(so, (size_t)q->n_chains);
             ok = false;
         }
@@ -242,13 +274,6 @@ dsdp_status admit(dsdp_sched s)
         }
         HIP_TRY(hipMemcpyAsync(s->pool + ao, q->pl.blob.data(), q->pl.blob.size() * 4, hipMemcpyHostToDevice, s->stream),
                 "ligand upload");
-        // the pair stream too where the pool has room, once the maps have theirs
-        q->stream_bytes = align256(q->stream.blob.size() * 4);
-        q->has_stream = !q->stream.blob.empty() && s->mem.alloc(q->stream_bytes, q->stream_off);
-        if (q->has_stream)
-            HIP_TRY(hipMemcpyAsync(s->pool + q->stream_off, q->stream.blob.data(), q->stream.blob.size() * 4,
-                                   hipMemcpyHostToDevice, s->stream),
-                    "ligand upload");
         q->slot0 = so;
         q->arena_off = ao;
         q->arena_bytes = ab;
@@ -408,7 +433,7 @@ dsdp_status dsdp_sched_submit(dsdp_sched s, int32_t receptor_id, const dsdp_liga
     std::unique_ptr<Request> q(new Request());
     // the layout is chosen at each tick by the running chains, where the caller
     // leaves it to the library: atom lists, or the pair stream from one wave per chain on
-    const bool choose = s->prm.intra_form == DSDP_INTRA_AUTO && s->prm.waves_per_chain == 0;
+    const bool choose = s->prm.intra_form == DSDP_INTRA_AUTO && s->prm.waves_per_chain <= 1;
     IntraCtx ctx = intra_ctx(&s->prm, s->capacity, true);
     if (choose) {
         ctx.layout = kFormStream;
@@ -477,7 +502,8 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
         std::vector<long> ch;
         long total = 0;
         for (Request *q : s->running) total += q->n_chains;
-        one_wave = total > kListWaves * device_cus() / 2;
+        one_wave = s->prm.waves_per_chain == 1 || total > kListWaves * device_cus() / 2;
+        if (one_wave && (st = grant_streams(s))) return st;
         for (Request *q : s->running) {
             hdr.push_back(one_wave && q->has_stream ? &q->stream.h : &q->pl.h);
             ch.push_back(q->n_chains);

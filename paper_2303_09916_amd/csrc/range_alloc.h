@@ -1,4 +1,4 @@
-// First-fit range allocator of the serving scheduler's device pool: plain C++,
+// Range allocator of the serving scheduler's device pool: plain C++,
 // no device code, so it can be unit-tested on the host.  Private to the library.
 #pragma once
 
@@ -9,7 +9,7 @@
 namespace dsdp {
 namespace host {
 
-// First-fit allocator over [0, total) with coalescing of freed ranges.
+// First-fit allocator (from either end) over [0, total) with coalescing of freed ranges.
 struct RangeAlloc {
     std::map<size_t, size_t> free_;   // offset -> length
     size_t total = 0, used = 0;
@@ -29,6 +29,23 @@ struct RangeAlloc {
                 const size_t rest = it->second - n;
                 free_.erase(it);
                 if (rest) free_[off + n] = rest;
+                used += n;
+                return true;
+            }
+        return false;
+    }
+    // The same from the other end: the upper part of the highest range that fits.
+    bool alloc_high(size_t n, size_t &off)
+    {
+        if (n == 0) n = 1;
+        for (auto it = free_.rbegin(); it != free_.rend(); ++it)
+            if (it->second >= n) {
+                const size_t at = it->first, rest = it->second - n;
+                off = at + rest;
+                if (rest)
+                    it->second = rest;
+                else
+                    free_.erase(at);
                 used += n;
                 return true;
             }

@@ -80,3 +80,70 @@ def test_first_request_of_a_receptor_gets_the_stream():
             free.append(s.info().pool_free)
             s.finish()
     assert free[0] == free[1]
+
+
+def ligand_bytes(L):
+    """Pool bytes of a request's ligand as atom lists."""
+    with Sched(64 << 20, slots=64, params=D.dsdp_params_default(intra_form=D.DSDP_INTRA_ATOMS)) as s:
+        s.submit(L, 4, 1, 1)
+        s.tick()
+        free = s.info().pool_free
+        s.submit(L, 4, 2, 1)
+        s.tick()
+        return free - s.info().pool_free
+
+
+def maps_bytes(k):
+    rec, box = receptor(4 + k)
+    return (-(-D.dsdp_grids_bytes(box, len(TYPES)) // 256) * 256,
+            -(-D.dsdp_build_grids_workspace_bytes(rec.n, box) // 256) * 256)
+
+
+def alone(L, chains, steps, seed, rec=0, top_k=3, params=None, site=None):
+    import gpu_common as gc
+    r, box = receptor(4 + rec)
+    g = gc.GpuGrid(r.xyz, r.types, box, TYPES)
+    if site is not None:
+        D.dsdp_grids_set_site(g.handle, *site)
+    ws = gc.dev_bytes(g.torch, D.dsdp_dock_workspace_bytes(L, chains))
+    return [bytes(p) for p in D.dsdp_dock(g.handle, L, chains, steps, seed, top_k, ws, params)[0]]
+
+
+@pytest.mark.parametrize("waves", [0, 1])
+def test_pool_sized_for_atom_lists_admits_as_many(waves):
+    """A pool with room for the maps and the atom lists of 30 requests runs 30 at once,
+    above the chain count from which they would search by the pair stream."""
+    L = ligand(47, 9)
+    maps, build = maps_bytes(0)
+    one = ligand_bytes(L)
+    assert build <= 30 * one
+    with Sched(maps + 30 * one, params=D.dsdp_params_default(waves_per_chain=waves)) as s:
+        s.submit(L, 4, 1, 1)     # brings the maps in
+        s.tick()
+        assert s.info().completed == 1
+        t = [s.submit(L, 40, 3, 50 + k) for k in range(31)]
+        s.tick()
+        assert s.info().running == 30 and s.info().queued == 1
+        s.finish()
+        for k in (0, 29, 30):
+            assert s.poses(t[k]) == alone(L, 40, 3, 50 + k)
+
+
+def test_streams_make_way_for_maps():
+    """Pair streams that lie in the pool do not keep another receptor's maps, or another
+    request's ligand, out of it."""
+    L = ligand(47, 9)
+    (m0, b0), (m1, b1) = maps_bytes(0), maps_bytes(1)
+    one = ligand_bytes(L)
+    with Sched(m0 + m1 + b1 + 3 * one + 256, recs=2) as s:
+        t = [s.submit(L, 700, 6, 60 + k) for k in range(2)]
+        s.tick()
+        s.tick()
+        assert s.info().running == 2
+        t.append(s.submit(L, 24, 4, 62, rec=1))
+        s.tick()
+        assert s.info().running == 3 and s.info().resident_receptors == 2 and s.info().evictions == 0
+        s.finish()
+        assert s.info().free_slots == 4096
+        want = [alone(L, 700, 6, 60), alone(L, 700, 6, 61), alone(L, 24, 4, 62, rec=1)]
+        assert [s.poses(x) for x in t] == want
