@@ -147,3 +147,35 @@ def test_streams_make_way_for_maps():
         assert s.info().free_slots == 4096
         want = [alone(L, 700, 6, 60), alone(L, 700, 6, 61), alone(L, 24, 4, 62, rec=1)]
         assert [s.poses(x) for x in t] == want
+
+
+@pytest.mark.parametrize("tight", [False, True])
+@pytest.mark.parametrize("sites", [False, True])
+@pytest.mark.parametrize("optimizer", [D.DSDP_OPT_BFGS, D.DSDP_OPT_BB])
+def test_layout_changes_between_ticks(optimizer, sites, tight):
+    """A small request ticks alone (atom lists), beside one that lifts the running chains
+    over the limit (pair stream, where the pool holds it) and is cancelled, alone again,
+    and beside a second such request; it and the second equal docking alone."""
+    params = D.dsdp_params_default(optimizer=optimizer, bb_iters=12)
+    small, large, other = ligand(33, 8), ligand(47, 9), ligand(26, 6)
+    rec, _ = receptor(4)
+    site = (make_site_points(rec, n=70, radius=5.0, clearance=2.5), 6.0) if sites else None
+    maps, build = maps_bytes(0)
+    room = maps + build + 2048 + ligand_bytes(small) + max(ligand_bytes(large), ligand_bytes(other)) if tight else 64 << 20
+    with Sched(room, spt=2, params=params) as s:
+        if sites:
+            D.dsdp_sched_set_site(s.h, s.ids[0], *site)
+        a = s.submit(small, 30, 13, 7)
+        s.tick()
+        b = s.submit(large, 1200, 40, 8)
+        s.tick(2)
+        assert s.info().running == 2
+        D.dsdp_sched_cancel(s.h, b)
+        s.tick()
+        assert s.info().running == 1
+        c = s.submit(other, 1100, 5, 9)
+        s.finish()
+        assert D.dsdp_sched_poll(s.h, b, 3)[0] == D.DSDP_REQ_CANCELLED
+        assert s.poses(a) == alone(small, 30, 13, 7, params=params, site=site)
+        assert s.poses(c) == alone(other, 1100, 5, 9, params=params, site=site)
+        assert s.info().free_slots == 4096
