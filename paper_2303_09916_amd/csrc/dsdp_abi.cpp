@@ -904,7 +904,7 @@ dsdp_status dsdp_build_grids(const dsdp_atom *rec, int32_t n_rec, const dsdp_box
         g->map_of_type[tl[t]] = t;
         g->types[t] = tl[t];
     }
-    hipError_t e = launch_grid_build(d_atoms, d_start, cg.cn, cg.clo, cg.cell, g->view, tl, (float4 *)d_maps, s);
+    hipError_t e = launch_grid_build(d_atoms, d_start, cg.cn, cg.clo, cg.cell, g->view, tl, (float4 *)d_maps, device_cus(), s);
     if (e != hipSuccess) {
         delete g;
         return hip_fail(e, "grid build launch");

@@ -177,9 +177,10 @@ struct SearchParams {
 // arguments: the caller's copy is free on return and nothing waits.
 constexpr size_t kPutBytes = 4 * 4000;
 hipError_t launch_put(const void *src, size_t bytes, void *dst, hipStream_t stream);
+// cus: the device's compute units.
 hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const int *cn, const float *clo,
                              float cell, const GridView &g, const int *map_types_host, float4 *maps,
-                             hipStream_t stream);
+                             long cus, hipStream_t stream);
 // LDS of a workgroup of `waves` waves that serve one chain, or (solo) one each.
 size_t search_lds_bytes(const LigHeader &h, int waves, bool solo = false);
 // Gather-throughput probe: blocks x 256 threads, rounds of 8-corner gathers each;

@@ -29,6 +29,7 @@
 // atoms 275 -> 120 us; 107^3, 9 types, 12000 atoms 610 -> 243 us; 43^3, 4 types, 300
 // atoms 72 -> 26 us (37 us without the split into runs of maps, see kFillWaves).
 #include "dsdp_internal.h"
+#include "map_runs.h"
 
 #include <algorithm>
 #include <utility>
@@ -42,7 +43,7 @@ constexpr int BX = 4, BY = 4;        // a wave's block of nodes (x and y; all of
 constexpr int kStageCap = 512;       // atoms staged per pass (8 KB of LDS)
 constexpr int kMaxRows = 128;        // cell rows per tile (at most 9 x 9 by the choice of the cell edge)
 constexpr uint32_t kPolar = 1u << 31;
-constexpr long kFillWaves = 4096;    // four waves per SIMD of the device's 1024
+constexpr long kFillWaves = 12;      // waves per compute unit: three per SIMD
 
 struct BuildArgs {
     const float4 *atoms;      // sorted by cell: x, y, z, XS type bits
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(kThreads) void grid_build_kernel(const BuildArgs a)
 }  // namespace
 
 hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const int *cn, const float *clo, float cell,
-                             const GridView &g, const int *map_types_host, float4 *maps, hipStream_t stream)
+                             const GridView &g, const int *map_types_host, float4 *maps, long cus, hipStream_t stream)
 {
     BuildArgs a;
     a.atoms = atoms;
@@ -295,30 +296,11 @@ hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const i
     }
     a.maps = maps;
 
-    // Runs of maps: one, unless the box gives fewer than kFillWaves waves; then
-    // as many as fill that (at most one per radius), since a wave's time is its
-    // own chain of atoms and the chip has idle issue slots.  The part that does
-    // not depend on the map (about 25 of 100 to 150 instructions an atom) is then
-    // repeated.
     const dim3 tiles((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, (g.n[2] + TZ - 1) / TZ);
     const long waves = (long)((g.n[0] + BX - 1) / BX) * ((g.n[1] + BY - 1) / BY) * tiles.z;
-    const int radii = __builtin_popcount(a.first);
-    const int want = (int)std::max(1L, std::min((long)radii, kFillWaves / waves));
-    // cut at the changes of radius nearest to equal shares of the cost (a radius
-    // about 18 instructions, a map 4)
-    a.n_parts = 0;
-    a.part[0] = 0;
-    int max_maps = 0, left = 18 * radii + 4 * g.T, cost = 0;
-    for (int k = 0; k < g.T; k++) {
-        cost += 4 + ((a.first >> k & 1u) ? 18 : 0);
-        const bool can_cut = k + 1 == g.T || (a.first >> (k + 1) & 1u);
-        if (k + 1 == g.T || (can_cut && a.n_parts + 1 < want && cost * (want - a.n_parts) >= left)) {
-            max_maps = std::max(max_maps, k + 1 - a.part[a.n_parts]);
-            a.part[++a.n_parts] = k + 1;
-            left -= cost;
-            cost = 0;
-        }
-    }
+    a.n_parts = split_maps(a.first, g.T, runs_wanted(waves, kFillWaves * cus, g.T), a.part);
+    int max_maps = 0;
+    for (int r = 0; r < a.n_parts; r++) max_maps = std::max(max_maps, a.part[r + 1] - a.part[r]);
     const dim3 grid(tiles.x, tiles.y, tiles.z * a.n_parts);
 #define DSDP_BUILD(N) grid_build_kernel<N><<<grid, kThreads, 0, stream>>>(a)
     switch (max_maps) {
