@@ -7,6 +7,7 @@
 // kernels and turns the ranked chain results into output poses.
 #include "../../include/dsdp.h"
 #include "dsdp_internal.h"
+#include "map_runs.h"
 #include "dsdp_host.h"
 #include "tuner.h"
 
@@ -66,8 +67,7 @@ dsdp_status geometry(const dsdp_box *box, int n[3], double origin[3])
     return DSDP_OK;
 }
 
-// cell binning geometry: the box grown by the cutoff, cell edge chosen so that a
-// 8x8x4 node tile plus the cutoff spans at most 9 cells per axis
+// cell binning geometry: the box grown by the cutoff (cell_edge)
 struct CellGeom {
     int cn[3];
     float clo[3];
@@ -77,7 +77,7 @@ struct CellGeom {
 CellGeom cell_geometry(const int n[3], const double origin[3], double h)
 {
     CellGeom c;
-    c.cell = (float)std::max(4.0, (8.0 * h + 2.0 * kCutoff) / 9.0);
+    c.cell = (float)cell_edge(h);
     c.ncell = 1;
     for (int a = 0; a < 3; a++) {
         const double lo = origin[a] - kCutoff, hi = origin[a] + (n[a] - 1) * h + kCutoff;

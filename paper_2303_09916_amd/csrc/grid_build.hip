@@ -37,11 +37,10 @@
 namespace dsdp {
 namespace {
 
-constexpr int TX = 8, TY = 8, TZ = 4;
+constexpr int TX = kTileX, TY = kTileY, TZ = kTileZ;
 constexpr int kThreads = TX * TY * TZ;
 constexpr int BX = 4, BY = 4;        // a wave's block of nodes (x and y; all of TZ)
 constexpr int kStageCap = 512;       // atoms staged per pass (8 KB of LDS)
-constexpr int kMaxRows = 128;        // cell rows per tile (at most 9 x 9 by the choice of the cell edge)
 constexpr uint32_t kPolar = 1u << 31;
 constexpr long kFillWaves = 12;      // waves per compute unit: three per SIMD
 
@@ -120,7 +119,7 @@ __global__ __launch_bounds__(kThreads) void grid_build_kernel(const BuildArgs a)
         hi[ax] = min(a.cn[ax] - 1, (int)floorf((phi - a.clo[ax]) / a.cell));
     }
     const int ny = hi[1] - lo[1] + 1, nz = hi[2] - lo[2] + 1;
-    const int nrows = lo[0] > hi[0] || ny <= 0 || nz <= 0 ? 0 : min(ny * nz, kMaxRows);
+    const int nrows = lo[0] > hi[0] || ny <= 0 || nz <= 0 ? 0 : min(ny * nz, kMaxRows);   // (the host has checked)
     int begin = 0, len = 0, pre = 0;
     if (tid < nrows) {
         const int base = ((lo[2] + tid / ny) * a.cn[1] + lo[1] + tid % ny) * a.cn[0];
@@ -264,6 +263,7 @@ __global__ __launch_bounds__(kThreads) void grid_build_kernel(const BuildArgs a)
 hipError_t launch_grid_build(const float4 *atoms, const int *cell_start, const int *cn, const float *clo, float cell,
                              const GridView &g, const int *map_types_host, float4 *maps, long cus, hipStream_t stream)
 {
+    if (cell_rows(g.h, cell) > kMaxRows) return hipErrorInvalidValue;
     BuildArgs a;
     a.atoms = atoms;
     a.cell_start = cell_start;

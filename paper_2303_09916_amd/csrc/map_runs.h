@@ -1,5 +1,6 @@
-// How the map build splits the maps of a small box into runs: plain C++, no device
-// code, so it can be unit-tested on the host.  Private to the library.
+// Host rules of the map build (receptor cells, and how the maps of a small box are split
+// into runs): plain C++, no device code, so they can be unit-tested on the host.
+// Private to the library.
 #pragma once
 
 #include <algorithm>
@@ -8,6 +9,19 @@
 namespace dsdp {
 
 constexpr int kMaxRadii = 8;   // distinct XS radii
+constexpr int kTileX = 8, kTileY = 8, kTileZ = 4;   // nodes of a workgroup's tile
+constexpr int kMaxRows = 128;                       // rows of cells that a tile can gather
+
+// Edge of the receptor cells for node spacing h and the 8 A cutoff.
+inline double cell_edge(double h) { return std::max(4.0, (8.0 * h + 16.0) / 9.0); }
+
+// Rows of cells (along x) that a tile and the cutoff around it can touch, at most: a span of
+// s cell edges touches floor(s) + 2 with its ends anywhere.  10 in y by 7 in z at spacing 2.5
+// to 4, 6 by 6 below 0.57.
+inline int cell_rows(double h, double edge)
+{
+    return ((int)(((kTileY - 1) * h + 16.0) / edge) + 2) * ((int)(((kTileZ - 1) * h + 16.0) / edge) + 2);
+}
 
 // Issue cost per atom of maps [a, b): about 18 instructions a radius, 4 a map.  Bit k of
 // `first`: map k is the first of its radius.

@@ -36,6 +36,21 @@ int main()
     CHECK(split_maps(0x7u, 4, 3, part) == 3 && part[1] == 1 && part[2] == 2 && part[3] == 4);
     CHECK(split_maps(0x7u, 4, 1, part) == 1 && part[1] == 4);
     CHECK(split_maps(0x1u, 9, 4, part) == 1 && part[1] == 9);   // one radius: never cut
+    // rows of cells over every spacing that a box may have (the edge is a float where it is
+    // used), and that no position of a tile touches more
+    int most = 0;
+    for (double h = 0.05; h <= 4.0; h += 0.001) {
+        const double edge = (double)(float)cell_edge(h);
+        most = std::max(most, cell_rows(h, edge));
+        for (double at = 0.0; at < 1.0; at += 0.05) {
+            const auto touched = [&](int nodes) {
+                const double lo = at * edge, hi = lo + (nodes - 1) * h + 16.0;
+                return (int)(hi / edge) - (int)(lo / edge) + 1;
+            };
+            CHECK(touched(kTileY) * touched(kTileZ) <= cell_rows(h, edge));
+        }
+    }
+    CHECK(most == 70 && most <= kMaxRows && cell_rows(4.0, 2.0) > kMaxRows);
     // the runs wanted: what fills the device, one to six, three from 13 maps on
     CHECK(runs_wanted(1, 3072, 4) == 6 && runs_wanted(512, 3072, 17) == 6 && runs_wanted(513, 3072, 17) == 5);
     CHECK(runs_wanted(1024, 3072, 9) == 3 && runs_wanted(1025, 3072, 9) == 2 && runs_wanted(1537, 3072, 9) == 1);
