@@ -2067,15 +2067,23 @@ int search_class(const LigHeader &h, int waves)
 }
 
 // One switch over the kernel variants: pair slots per lane (or kAtoms, kStream),
-// a chain per wave.
-#define DSDP_DISPATCH(cls, F)             \
-    switch (cls) {                        \
+// a chain per wave.  Barzilai-Borwein has no pair stream of several waves per chain
+// (choose_layout, pick_waves).
+#define DSDP_VARIANTS(F)                  \
     case 0: F(8, false); break;           \
     case 1: F(16, false); break;          \
     case 2: F(32, false); break;          \
     case 3: F(kAtoms, false); break;      \
-    case 4: F(kStream, true); break;      \
+    case 4: F(kStream, true); break;
+#define DSDP_DISPATCH(cls, F)             \
+    switch (cls) {                        \
+        DSDP_VARIANTS(F)                  \
     case 5: F(kStream, false); break;     \
+    default: return hipErrorInvalidValue; \
+    }
+#define DSDP_DISPATCH_BB(cls, F)          \
+    switch (cls) {                        \
+        DSDP_VARIANTS(F)                  \
     default: return hipErrorInvalidValue; \
     }
 
@@ -2148,13 +2156,14 @@ hipError_t launch_local_opt(const uint32_t *blob, int blob_words, const LigHeade
 #define DSDP_LOPT_OF(A, BB, SOLO)                                                                                        \
     local_opt_kernel<A, BB, SOLO><<<blocks, 64 * waves, lds, stream>>>(blob, blob_words, g, p, poses_in, n, poses_out, energy, \
                                                             evals)
-#define DSDP_LOPT(A, SOLO)             \
-    if (p.optimizer == kOptBB)         \
-        DSDP_LOPT_OF(A, true, SOLO);   \
-    else                               \
-        DSDP_LOPT_OF(A, false, SOLO)
-    DSDP_DISPATCH(cls, DSDP_LOPT)
-#undef DSDP_LOPT
+#define DSDP_LOPT_BFGS(A, SOLO) DSDP_LOPT_OF(A, false, SOLO)
+#define DSDP_LOPT_BB(A, SOLO) DSDP_LOPT_OF(A, true, SOLO)
+    if (p.optimizer == kOptBB)
+        DSDP_DISPATCH_BB(cls, DSDP_LOPT_BB)
+    else
+        DSDP_DISPATCH(cls, DSDP_LOPT_BFGS)
+#undef DSDP_LOPT_BFGS
+#undef DSDP_LOPT_BB
 #undef DSDP_LOPT_OF
     return hipGetLastError();
 }
@@ -2169,17 +2178,20 @@ hipError_t launch_tick(int cls, int waves, size_t lds_bytes, const uint32_t *are
 #define DSDP_TICK_OF(A, BB, SOLO)                                                                                         \
     tick_kernel<A, BB, SOLO><<<grid, block, lds_bytes, stream>>>(arena, tasks, grids, p, tick_steps, init, state, records, \
                                                            best_xyz)
-#define DSDP_TICK(A, SOLO)             \
-    if (p.optimizer == kOptBB)         \
-        DSDP_TICK_OF(A, true, SOLO);   \
-    else                               \
-        DSDP_TICK_OF(A, false, SOLO)
-    DSDP_DISPATCH(cls, DSDP_TICK)
-#undef DSDP_TICK
+#define DSDP_TICK_BFGS(A, SOLO) DSDP_TICK_OF(A, false, SOLO)
+#define DSDP_TICK_BB(A, SOLO) DSDP_TICK_OF(A, true, SOLO)
+    if (p.optimizer == kOptBB)
+        DSDP_DISPATCH_BB(cls, DSDP_TICK_BB)
+    else
+        DSDP_DISPATCH(cls, DSDP_TICK_BFGS)
+#undef DSDP_TICK_BFGS
+#undef DSDP_TICK_BB
 #undef DSDP_TICK_OF
     return hipGetLastError();
 }
 #undef DSDP_DISPATCH
+#undef DSDP_DISPATCH_BB
+#undef DSDP_VARIANTS
 
 hipError_t launch_rank(const float *records, const float4 *best_xyz, const RankSeg *segs, int n_segs, int max_chains,
                        float rmsd_cut, int *sel, hipStream_t stream)

@@ -55,6 +55,11 @@ int main()
     CHECK(pick(ctx(AUTO, 0, 512)) == kFormPairs && pick(ctx(AUTO, 0, 513)) == kFormStream);
     CHECK(pick(ctx(PAIRS, 4, 512)) == kFormPairs && pick(ctx(PAIRS, 4, 4096)) == kFormStream);
     CHECK(pick(ctx(AUTO, 4, 4096, false, true)) == kFormPairs && pick(ctx(PAIRS, 2, 4096, false, true)) == kFormPairs);
+    // Barzilai-Borwein never has the stream at several waves (no such kernel)
+    for (int form : {AUTO, PAIRS, ATOMS})
+        for (int waves = 2; waves <= 4; waves++)
+            for (long chains : {1L, 512L, 1025L, 100000L})
+                for (bool mixed : {false, true}) CHECK(pick(ctx(form, waves, chains, mixed, true)) != kFormStream);
     // several ligands: atom lists until a wave per chain fills the device
     CHECK(pick(ctx(AUTO, 0, 1024, true)) == kFormAtoms && pick(ctx(AUTO, 0, 1025, true)) == kFormStream);
     CHECK(pick(ctx(AUTO, 1, 9, true)) == kFormStream && pick(ctx(AUTO, 2, 9000, true)) == kFormAtoms);
