@@ -1,5 +1,6 @@
 """Build libdsdp.so (HIP kernels for gfx950 + the C-ABI host code) in-tree with hipcc,
-and the plain C client of its ABI that the tests run (tests/c_client)."""
+and the programs that the tests run: a plain C client of its ABI (tests/c_client) and a
+check of the kernels' rounding (tests/rounding_check)."""
 import os
 import subprocess
 import sys
@@ -40,6 +41,19 @@ def build_c_client(verbose=False):
            os.path.join(ROOT, "tests", "c_client.c"), "-o", exe + ".tmp",
            "-L", HERE, "-ldsdp", "-Wl,-rpath,$ORIGIN/../paper_2303_09916_amd",
            "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(exe + ".tmp", exe)
+    return exe
+
+
+def build_rounding_check(verbose=False):
+    """tests/rounding_check: a program that compares the kernels' root, reciprocal and
+    quotient with correctly rounded ones on the GPU."""
+    exe = os.path.join(ROOT, "tests", "rounding_check")
+    flags = [f for f in FLAGS if f not in ("-fPIC", "-shared")]
+    cmd = [HIPCC] + flags + [os.path.join(ROOT, "tests", "rounding_check.hip"), "-o", exe + ".tmp"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

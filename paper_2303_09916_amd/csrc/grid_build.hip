@@ -24,12 +24,13 @@
 //  - a 4x4x4 block is within the cutoff of 72 atoms at protein density where an
 //    8x8x1 slab is of 83, and wastes fewer lanes at the box faces;
 //  - the root and the reciprocal are the shortest sequences that still round
-//    correctly (both checked against sqrtf and 1/x over every input in range).
+//    correctly (rounding.h).
 // Measured on MI355X, kernel alone, before and after: 81^3 nodes, 8 types, 4000
 // atoms 275 -> 120 us; 107^3, 9 types, 12000 atoms 610 -> 243 us; 43^3, 4 types, 300
 // atoms 72 -> 26 us (37 us without the split into runs of maps, see kFillWaves).
 #include "dsdp_internal.h"
 #include "map_runs.h"
+#include "rounding.h"
 
 #include <algorithm>
 #include <utility>
@@ -188,15 +189,10 @@ __global__ __launch_bounds__(kThreads) void grid_build_kernel(const BuildArgs a)
                 const uint32_t cls = (uint32_t)__builtin_amdgcn_readlane((int)cls_l, l);
                 const float r2 = fmaf(dz, dz, fmaf(dx, dx, dy * dy));
                 if (r2 < kCutoff2) {
-                    // r = sqrt(r2) and 1 / r, correctly rounded: the estimates of
-                    // the hardware and one residual step each.  A distance below
-                    // 2^-45 is as good as 0 (every radius sum is above 1).
-                    const float x = __int_as_float(max(__float_as_int(r2), 0x12800000));
-                    const float y = __builtin_amdgcn_rsqf(x);
-                    const float s0 = x * y;
-                    const float r = fmaf(fmaf(-s0, s0, x), 0.5f * y, s0);
-                    float inv = __builtin_amdgcn_rcpf(r);
-                    inv = fmaf(fmaf(-r, inv, 1.0f), inv, inv);
+                    // r and 1 / r, correctly rounded.  A distance below 2^-45 is as good as
+                    // 0 (every radius sum is above 1).
+                    const float r = sqrt_normal(__int_as_float(max(__float_as_int(r2), 0x12800000)));
+                    const float inv = rcp_normal(r);
                     const float half_inv = r > 1e-9f ? 0.5f * inv : 0.0f;
                     // Vina's pair term on the surface distance d; the derivative is
                     // carried doubled (de2), which scales every product exactly

@@ -19,6 +19,7 @@
 // traffic is LDS, DPP or lane reads in a fixed order, so a chain's arithmetic
 // does not depend on which wave, workgroup or launch runs it.
 #include "dsdp_internal.h"
+#include "rounding.h"
 
 #include <cstring>
 #include <mutex>
@@ -168,39 +169,6 @@ __device__ __forceinline__ float3 operator+(float3 a, float3 b) { return make_fl
 __device__ __forceinline__ float3 operator-(float3 a, float3 b) { return make_float3(a.x - b.x, a.y - b.y, a.z - b.z); }
 __device__ __forceinline__ float3 operator*(float s, float3 a) { return make_float3(s * a.x, s * a.y, s * a.z); }
 __device__ __forceinline__ float dot3(float3 a, float3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
-
-// Correctly rounded square root, quotient and reciprocal square root without the
-// compiler's handling of denormal and extreme arguments, for arguments in
-// kNormalLo..kNormalHi (a quotient also wants one there): the hardware estimate
-// and one residual step (Markstein).  Root and reciprocal were compared with
-// sqrtf and 1/x over every float in [2^-96, 64), the quotient on 1.7e10 pairs;
-// rsqrtf is the bare estimate there.  41 to 101 cycles of one wave become 9 to 40.
-constexpr float kNormalLo = 0x1p-80f, kNormalHi = 64.0f;
-__device__ __forceinline__ bool in_normal(float x)
-{
-    return __float_as_uint(x) - __float_as_uint(kNormalLo) < __float_as_uint(kNormalHi) - __float_as_uint(kNormalLo);
-}
-// whether any active lane's x lies outside the range
-__device__ __forceinline__ bool any_odd(float x) { return __builtin_amdgcn_ballot_w64(!in_normal(x)) != 0; }
-__device__ __forceinline__ float sqrt_normal(float x)
-{
-#pragma clang fp contract(off)
-    const float y = __builtin_amdgcn_rsqf(x), g = x * y;
-    return fmaf(fmaf(-g, g, x), 0.5f * y, g);
-}
-__device__ __forceinline__ float rcp_normal(float b)
-{
-#pragma clang fp contract(off)
-    const float y = __builtin_amdgcn_rcpf(b);
-    return fmaf(fmaf(-b, y, 1.0f), y, y);
-}
-__device__ __forceinline__ float div_normal(float a, float b)
-{
-#pragma clang fp contract(off)
-    const float y = rcp_normal(b);
-    const float q = a * y;
-    return fmaf(fmaf(-b, q, a), y, q);
-}
 
 // unit quaternion of rotation vector v (angle |v| about v/|v|), (w, x, y, z);
 // the identity for v = 0
