@@ -172,3 +172,86 @@ def test_smallest_workspace(grid, n):
         want = call(whole, params(ATOMS, 0, bfgs_iters=3))
         assert same(call(whole[:size], params(0, 0, bfgs_iters=3)), want)
         assert not accepted(lambda: call(whole[:size - 256], params(0, 0, bfgs_iters=3)))
+
+
+def test_scoring_from_the_copy_of_the_maps():
+    """A large set of poses is scored from a copy of the maps with contiguous cells, in the
+    part of the workspace that scoring leaves alone otherwise; the results are those of
+    small sets, on maps with odd node counts (the copy pads z) and for poses that are not
+    finite, far outside, or have a quaternion of any length."""
+    import gpu_common as gc
+    rec = make_receptor(300, radius=12.0, seed=4)
+    g = gc.GpuGrid(rec.xyz, rec.types, box32(make_box(rec.pocket, (12.4, 13.3, 11.5), spacing=0.15)), PALETTE_T9)
+    torch = g.torch
+    nodes = int(np.prod(g.n)) * len(PALETTE_T9)
+    assert g.n[2] % 2 == 1 and nodes * 16 >= 32 << 20
+    L = D.Ligand.from_synth(make_ligand(30, 5, seed=2, palette=PALETTE_T9))
+    n = 4 * nodes // L.n_atoms + 777
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    P = torch.rand((n, L.nx), generator=gen, device="cuda")
+    lo = torch.tensor(np.asarray(g.origin, np.float32), device="cuda")
+    ext = torch.tensor([(a - 1) * 0.15 for a in g.n], device="cuda", dtype=torch.float32)
+    P[:, :3] = lo - 2.0 + P[:, :3] * (ext + 4.0)
+    P[:, 3:] = P[:, 3:] * 2 - 1
+    P[:, 7:] *= np.pi
+    odd = [(0, np.nan), (1, np.inf), (2, -np.inf), (0, 1e30), (3, np.nan), (4, np.inf), (5, 1e-30), (6, 3e38), (7, np.nan),
+           (8, np.inf), (9, 1e20), (11, -np.inf)]
+    for k, (c, v) in enumerate(odd):
+        P[3 * k, c] = v
+    P[1, 3:7] = 0.0
+    ws = gc.dev_bytes(torch, D.dsdp_dock_workspace_bytes(L, n))
+    ws.fill_(0x5A)
+    at = 64 * n + (1 << 20)          # behind what scoring writes for itself
+    mark = ws[at:at + (1 << 20)]
+
+    def score(p):
+        e, gr = torch.empty((len(p), 4), device="cuda"), torch.empty((len(p), L.D), device="cuda")
+        D.dsdp_eval_poses(g.handle, L, p, len(p), e, gr, None, ws)
+        return e.cpu().numpy(), gr.cpu().numpy()
+
+    small = n // 9
+    parts = [score(P[k:k + small].contiguous()) for k in range(0, n, small)]
+    assert bool((mark == 0x5A).all())
+    whole = score(P)
+    assert not bool((mark == 0x5A).all())
+    assert same(whole, [np.concatenate([p[c] for p in parts]) for c in (0, 1)])
+    head = [np.concatenate(c) for c in zip(*(score(P[k:k + 36].contiguous()) for k in (0, 36)))]
+    assert same([w[:72] for w in whole], head)
+    assert not np.isfinite(whole[0][0, 0]) and np.isfinite(whole[0][40:]).all()
+
+
+@pytest.mark.parametrize("atoms,tors", [(12, 2), (30, 6), (47, 9), (64, 31)])
+@pytest.mark.parametrize("sites", [False, True])
+def test_poses_that_are_not_finite(grid, atoms, tors, sites):
+    """Scores of poses with a coordinate that is NaN, infinite or huge are the same in every
+    layout, and leave the other poses' alone."""
+    import gpu_common as gc
+    lig = make_ligand(atoms, tors, seed=atoms, palette=PALETTE_T9)
+    L = D.Ligand.from_synth(lig)
+    rng = np.random.default_rng(3)
+    n = 5200                           # enough for the stream as the library's choice
+    P = np.zeros((n, L.nx), np.float32)
+    P[:, :3] = np.asarray(grid.origin) + rng.uniform(0, 13.0, (n, 3))
+    P[:, 3:7] = rng.normal(size=(n, 4))
+    P[:, 7:] = rng.uniform(-np.pi, np.pi, (n, L.n_tors))
+    clean = P.copy()
+    rows = []
+    for c in sorted({0, 2, 3, 6, 7, L.nx - 1}):
+        for v in (np.nan, np.inf, -np.inf, 3e38, 1e-42):
+            rows.append(5 * len(rows))
+            P[rows[-1], c] = v
+    if sites:
+        mid = np.asarray(grid.origin) + 6.5
+        D.dsdp_grids_set_site(grid.handle, mid + rng.uniform(-4, 4, (20, 3)), 3.0)
+    try:
+        ref = gc.gpu_eval(grid, lig, P, params(ATOMS, 1))
+        rest = np.setdiff1d(np.arange(n), rows)
+        for form in (0, PAIRS):
+            assert same(gc.gpu_eval(grid, lig, P, params(form, 0)), ref)
+        few = np.arange(200)
+        assert same(gc.gpu_eval(grid, lig, P[few], params(PAIRS, 0)), [a[few] for a in ref])
+        assert all(np.array_equal(a[rest], b[rest]) for a, b in zip(gc.gpu_eval(grid, lig, clean, params(0, 0)), ref))
+        assert np.isfinite(ref[0][rest]).all() and not np.isfinite(ref[0][rows[0]]).all()
+    finally:
+        if sites:
+            D.dsdp_grids_set_site(grid.handle, np.zeros((0, 3)), 0.0)
