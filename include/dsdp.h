@@ -107,8 +107,9 @@ typedef struct {
     int32_t waves_per_chain; /* wavefronts per chain, 1..4: with BFGS that many line-search
                                 trials are evaluated at once; with Barzilai-Borwein and pair
                                 lists each evaluation's pairs are spread over them (atom lists:
-                                one wave works).  Results do not depend on it.  0 = chosen by
-                                the library from the chain count and the device (0) */
+                                one wave works); dsdp_eval_poses always runs one wave per
+                                pose.  Results do not depend on it.  0 = chosen by the
+                                library from the chain count and the device (0) */
     int32_t intra_form;      /* layout of the intra-ligand term on the device: DSDP_INTRA_AUTO
                                 (chosen by the library for the launch), DSDP_INTRA_PAIRS or
                                 DSDP_INTRA_ATOMS.  Results do not depend on it (0) */
@@ -135,7 +136,8 @@ typedef struct {
 #define DSDP_OPT_BB 1
 
 #define DSDP_INTRA_AUTO 0
-#define DSDP_INTRA_PAIRS 1   /* each pair evaluated once, its force stored and gathered per atom */
+#define DSDP_INTRA_PAIRS 1   /* each pair evaluated once, its force stored and gathered per atom: all pairs
+                                at a time or in chunks, by what the launch leaves room for */
 #define DSDP_INTRA_ATOMS 2   /* each pair evaluated from both atoms; no per-pair device scratch */
 
 /* One ranked output pose. */
@@ -220,7 +222,7 @@ void dsdp_grids_release(dsdp_grids g);
  * points falling in a ball, else the first site point), and outside it the
  * ligand's root position pays wall_slope per A of its distance to the nearest
  * ball.  Applies to dsdp_eval_poses, dsdp_local_opt, dsdp_dock and
- * dsdp_dock_batch on this handle (the serving scheduler uses plain boxes).
+ * dsdp_dock_batch on this handle (the serving scheduler: dsdp_sched_set_site).
  */
 dsdp_status dsdp_grids_set_site(dsdp_grids g, const float *points, int32_t n_points, float radius);
 
@@ -351,9 +353,10 @@ dsdp_status dsdp_dock(dsdp_grids g, const dsdp_ligand *lig, int32_t n_chains, in
  * callers that cannot allocate device memory (code under HIP graph capture,
  * serving loops and harnesses that forbid hipMalloc).  The workspace is a static
  * array of DSDP_STATIC_SCRATCH_BYTES in the library, one per device (the current
- * device at the call), held until the process ends; a dock whose
- * dsdp_dock_workspace_bytes exceeds it fails with DSDP_ERR_UNSUPPORTED before
- * any launch (about 1.7 KB per chain: some 4900 chains of a 32-atom ligand).
+ * device at the call), held until the process ends; a dock that it does not hold
+ * fails with DSDP_ERR_UNSUPPORTED before any launch (about 1.7 KB per chain: some
+ * 4900 chains of a 32-atom ligand; a dock whose dsdp_dock_workspace_bytes does not
+ * exceed it always fits).
  * Arguments, results and synchronisation are those of dsdp_dock, and the
  * results are bitwise the same.  Every call on a device shares that device's
  * array: calls that overlap on one device (from several threads or streams)
@@ -372,7 +375,8 @@ dsdp_status dsdp_dock_static(dsdp_grids g, const dsdp_ligand *lig, int32_t n_cha
  * candidates) gives the intra-ligand layout of ligands with at most 512 pairs
  * and of larger ones, and the waves per chain; ligands that share a kernel
  * variant and a wave count share a launch.  A dock candidate (8) gives the
- * ligand's layout (pair lists, then atom lists) and the waves (4, 3, 2, 1).
+ * ligand's layout (DSDP_INTRA_PAIRS, then DSDP_INTRA_ATOMS) and the waves (4, 3,
+ * 2, 1).  Candidates that a short trial would rate too well are left out.
  */
 #define DSDP_TUNE_CANDIDATES 8
 #define DSDP_TUNE_BATCH 0       /* dsdp_dock_batch with BFGS */
@@ -406,9 +410,9 @@ size_t dsdp_dock_batch_workspace_bytes(const dsdp_ligand *ligs, int32_t n_ligs, 
  * gets n_chains chains of n_steps steps seeded by seeds[l], exactly as dsdp_dock
  * would run them alone (a chain's result depends only on its seed, its index,
  * its ligand, the grids and the parameters), then its own ranking.  Ligands of
- * uneven size share the launches: chains are grouped by the ligand's pair-list
- * size class, each group launched with the wave count the library's tuner picks
- * for the group's chain count; the MC steps run in ticks of steps_per_tick steps
+ * uneven size share the launches: chains are grouped by the kernel variant that
+ * serves the ligand's layout, each group launched with the wave count of the tuner's
+ * plan (with tune = 0, of the group's chain count); the MC steps run in ticks of steps_per_tick steps
  * (0 = about eight ticks, of at least 250 steps) that continue from saved chain state, and the ticks
  * and the ranking are captured once into a HIP graph and launched as one unit.
  *   ligs, seeds  host [n_ligs];
@@ -483,7 +487,9 @@ dsdp_status dsdp_sched_set_site(dsdp_sched s, int32_t receptor_id, const float *
 /*
  * Queue a dock request (as dsdp_dock with the scheduler's parameters).  The ligand
  * is validated and copied now.  Admission happens in dsdp_sched_tick, in arrival
- * order, as soon as n_chains slots, arena space and the receptor's maps fit.
+ * order, as soon as n_chains slots, the ligand and the receptor's maps fit the pool.
+ * (Running requests may hold a second layout of their ligand in what the pool has
+ * left; it is given back when a request needs the room.)
  */
 dsdp_status dsdp_sched_submit(dsdp_sched s, int32_t receptor_id, const dsdp_ligand *lig, int32_t n_chains,
                               int32_t n_steps, uint64_t seed, int32_t top_k, int64_t *ticket);

@@ -603,10 +603,11 @@ size_t device_max_lds()
     return bytes;
 }
 
-// Waves per chain: the caller's choice, else about 8 waves per compute unit (12
-// with the pair stream, whose registers leave room for them: 1024 chains of 47 atoms ran
-// in 4.8 ms at three waves, 5.5 at two); every choice gives the same results.  Reduced
-// until the workgroup's LDS fits the device's limit.
+// Waves per chain of a launch whose layout is chosen: the caller's choice, else about 8
+// waves per compute unit (12 with the pair stream, whose registers leave room for them: 1024
+// chains of 47 atoms ran in 4.8 ms at three waves, 5.5 at two; for launches that mix
+// ligands see choose_layout); every choice gives the same results.  Reduced until the
+// workgroup's LDS fits the device's limit.
 dsdp_status pick_waves(const dsdp_params *prm, const LigHeader &h, int n_chains, int &waves)
 {
     int w = (prm && prm->waves_per_chain > 0) ? prm->waves_per_chain : 0;

@@ -5,7 +5,7 @@
 // slots, arena space for the ligand blob and, when the receptor's maps are not
 // resident, pool memory for them (evicting maps of receptors without running
 // requests, least recently used first) -- then advances every running chain by
-// one tick of MC steps in shared launches (one per pair-list size class), and
+// one tick of MC steps in shared launches (one per kernel variant), and
 // ranks the requests whose chains finished.  All device memory comes from one
 // caller-owned pool.  A request's chains run the same arithmetic as dsdp_dock
 // on the same maps, so results do not depend on what else is in flight.
@@ -50,7 +50,7 @@ enum { kQueued = 0, kRunning = 1, kDone = 2, kCancelled = 3 };
 struct Request {
     int64_t ticket = 0;
     int receptor = 0;
-    Prepared pl;
+    Prepared pl;             // the layout it is admitted with (atom lists, unless the caller fixed another)
     Prepared stream;         // the pair stream of the ligand, where the layout is the library's choice
     bool has_stream = false; // it is in the pool too (grant_streams)
     int n_chains = 0, n_steps = 0, top_k = 0;
@@ -496,7 +496,7 @@ dsdp_status dsdp_sched_tick(dsdp_sched s, int32_t *n_completed)
     // tasks of every running chain, in launch groups (kernel variant and LDS need)
     s->h_tasks.clear();
     std::vector<LaunchGroup> groups;
-    bool one_wave = false;   // enough chains for one wave each (choose_intra_form's rule)
+    bool one_wave = false;   // enough chains for one wave each (choose_layout's rule)
     {
         std::vector<const LigHeader *> hdr;
         std::vector<long> ch;

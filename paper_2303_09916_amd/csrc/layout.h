@@ -88,8 +88,13 @@ inline int refine_waves(long poses, long cus)
 //    call: 33 atoms 35.5 us, lists 39.8, stream 41.8; 60 atoms 82, 144 and 85), and
 //    the stream where the kernel is what counts (20000 poses: 33 atoms 60 us, lists 64, atoms
 //    76; 60 atoms 125, 471 and 126).
-//  - Launches that mix ligands take the stream from one wave per chain on (by
-//    kListWaves), else atom lists, whose launches need not be split by pair count.
+//  - Launches that mix ligands take atom lists, whose launches need not be split by pair
+//    count, up to four chains a unit (1024), and the stream beyond, where lists would get one
+//    wave per chain.  The stream's own waves are then those of kStreamWaves (pick_waves): two
+//    up to six chains a unit (1536), one beyond.  Eight ligands of 14 to 60 atoms, 100 steps:
+//    768 chains, atom lists 37.7 ms at two waves, stream 39.4; 1152 to 1536 chains, stream
+//    45.5 at two waves and 73 at one, atom lists 46.2 and 75; 1600 chains, stream 73.7 at one
+//    wave, atom lists 75.8.
 template <typename ListsLds>
 int choose_layout(const IntraCtx &ctx, int n_pairs, const Device &dev, ListsLds lists_lds)
 {

@@ -7,11 +7,11 @@
 // ligand's dock has the same two choices, layout and waves.  The candidates
 // (kPlans for batches, kDockCandidates for docks) are fixed; for a request not
 // yet in the cache of the current device, the caller's `measure` callback
-// times every candidate on a short trial of that request (all of its chains, a
+// times the candidates on a short trial of that request (all of its chains, a
 // few steps) and the fastest is cached by the request's make-up: the kind of
 // request, the histogram of ligand shapes (heavy atoms, intra-ligand pairs,
-// tangent dimension) and the chain count.  Candidates the callback reports as
-// impossible (negative time) are skipped.  Search results do not depend on the
+// tangent dimension) and the chain count.  Candidates the callback does not
+// time (negative time: they cannot run, or a trial would rate them too well) are skipped.  Search results do not depend on the
 // choice, so the tuner only moves speed.
 #pragma once
 
@@ -93,11 +93,11 @@ inline TuneKey tune_key(int device, int chains, const std::vector<ShapeBucket> &
 
 // The candidate plans: for each, the layout of a ligand's intra-ligand term as
 // a function of its pair class (1 each pair once: pair lists or the pair stream, by
-// the rule of choose_intra_form; 2 atom lists) and the waves per
-// chain.  Plan 0 is the library's fixed rule for batches that fill the device.
+// whether the batch's chains are all resident with lists; 2 atom lists) and the waves
+// per chain.
 struct Plan {
-    int form_small;   // layout of ligands with at most 512 pairs
-    int form_large;   // layout of ligands with more
+    int form_small;   // form of ligands with at most 512 pairs
+    int form_large;   // form of ligands with more
     int waves;
 };
 constexpr int kPlans = 6;
@@ -106,9 +106,9 @@ inline Plan plan(int i)
     static const Plan p[kPlans] = {
         {2, 2, 1},   // atom lists, one wave per chain
         {2, 2, 2},   // atom lists, two waves
-        {1, 1, 1},   // pair lists, one wave
-        {1, 1, 2},   // pair lists, two waves
-        {1, 2, 1},   // pair lists for small pair sets, atom lists for the rest, one wave
+        {1, 1, 1},   // each pair once, one wave
+        {1, 1, 2},   // each pair once, two waves
+        {1, 2, 1},   // each pair once for small pair sets, atom lists for the rest, one wave
         {1, 2, 2},   // the same, two waves
     };
     return p[(i >= 0 && i < kPlans) ? i : 0];
@@ -132,14 +132,14 @@ inline int candidates_of(int kind) { return kind == kTuneBatch ? kPlans : kDockC
 struct TuneEntry {
     TuneKey key;
     int pick = 0;                 // index into the kind's candidates
-    std::vector<float> trial_ms;  // per candidate (< 0: could not run)
+    std::vector<float> trial_ms;  // per candidate (< 0: not run)
     int trial_steps = 0;
     long trial_chains = 0;
 };
 
 class Tuner {
 public:
-    // measure(plan index) -> trial milliseconds, or < 0 when the plan cannot run.
+    // measure(candidate) -> trial milliseconds, or < 0 when it is left out.
     using Measure = std::function<float(int)>;
 
     // The cached pick of `key`, else the fastest of its kind's candidates by
