@@ -80,8 +80,9 @@ inline int refine_waves(long poses, long cus)
 //    One wave (Barzilai-Borwein, 10 steps): 47 atoms, 1024 chains 6.7 and 8.2 ms, 1300
 //    chains (in rounds) 13.2 and 9.4; 33 atoms, 2048 chains 5.5 and 6.0, 2500 chains 9.2
 //    and 7.5.
-//  - One wave and a single chunk of pairs: the stream, which is one go too (12 atoms, 384
-//    to 2048 chains: 2.8 to 3.2 ms, lists 3.0 to 3.6).
+//  - One wave and hardly more than a chunk of pairs: the stream, which is one go too (12
+//    atoms, 30 pairs, 384 to 2048 chains, 10 steps: 2.8 to 3.2 ms, lists 3.0 to 3.6; 60 steps of
+//    1536 chains: 141 pairs 24.0 and 25.0, 154 pairs 25.0 both, 219 pairs 27.8 and 25.9).
 //  - Barzilai-Borwein chains of several waves share each evaluation's pairs: lists.
 //  - Scoring prepares the ligand in every call and is bound by that up to some 20 poses a
 //    unit: pair lists while resident, then atom lists, the smaller sections (5000 poses a
@@ -109,7 +110,7 @@ int choose_layout(const IntraCtx &ctx, int n_pairs, const Device &dev, ListsLds 
     const int waves = ctx.waves > 0 ? ctx.waves
                                     : waves_for(ctx.chains, ctx.bb || by_mix ? kListWaves : kStreamWaves, dev.cus);
     if (by_mix) return waves == 1 ? kFormStream : kFormAtoms;
-    if (waves == 1 && n_pairs <= kStreamPairs) return kFormStream;
+    if (waves == 1 && n_pairs <= kStreamPairs * 5 / 4) return kFormStream;
     if (waves > 1 && ctx.bb) return kFormPairs;
     return ctx.chains <= resident_lists(lists_lds(waves), waves, dev) ? kFormPairs : kFormStream;
 }

@@ -49,8 +49,8 @@ int main()
             CHECK(pick(ctx(form, 1, 1025, false, bb)) == kFormStream);
             CHECK(pick(ctx(form, 1, 1 << 20, false, bb)) == kFormStream);
         }
-    // a single chunk of pairs: the stream at once
-    CHECK(pick(ctx(AUTO, 1, 9), kStreamPairs) == kFormStream && pick(ctx(AUTO, 1, 9), kStreamPairs + 1) == kFormPairs);
+    // a chunk and a quarter of pairs: the stream at once
+    CHECK(pick(ctx(AUTO, 1, 9), 158) == kFormStream && pick(ctx(AUTO, 1, 9), 159) == kFormPairs);
     // several waves: the same rule for BFGS; lists for Barzilai-Borwein
     CHECK(pick(ctx(AUTO, 0, 512)) == kFormPairs && pick(ctx(AUTO, 0, 513)) == kFormStream);
     CHECK(pick(ctx(PAIRS, 4, 512)) == kFormPairs && pick(ctx(PAIRS, 4, 4096)) == kFormStream);
