@@ -25,9 +25,10 @@
 //    8x8x1 slab is of 83, and wastes fewer lanes at the box faces;
 //  - the root and the reciprocal are the shortest sequences that still round
 //    correctly (rounding.h).
-// Measured on MI355X, kernel alone, before and after: 81^3 nodes, 8 types, 4000
-// atoms 275 -> 120 us; 107^3, 9 types, 12000 atoms 610 -> 243 us; 43^3, 4 types, 300
-// atoms 72 -> 26 us (37 us without the split into runs of maps, see kFillWaves).
+// Measured on MI355X, kernel alone (medians of one box), in the form that evaluated every
+// map on its own over 8x8x1 slabs, and in this one: 81^3 nodes, 8 types, 4000 atoms 272 and
+// 120 us; 107^3, 9 types, 12000 atoms 589 and 243 us; 43^3, 4 types, 300 atoms 72 and 26 us
+// (35 with all maps in one run, see runs_wanted).
 #include "dsdp_internal.h"
 #include "map_runs.h"
 #include "rounding.h"
